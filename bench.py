@@ -553,14 +553,22 @@ def main():
 
     flops_per_launch = 2.0 * m * n * k
     ms_launch = 0.5 * (stats["ms_mm_aht"] + stats["ms_mm_wta"]) / args.steps
-    peak = PEAK_FP32_TFLOPS if wl["dtype"] == "f32" else PEAK_FP64_TFLOPS
     achieved = flops_per_launch / (ms_launch * 1e-3) / 1e12
     src_hash = kernel_source_hash()
     tr = load_traffic(src_hash, TRAFFIC_FILE, args.workload)
-    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
-                "frac": round(achieved / peak, 4),
+    if wl["dtype"] == "f32":
+        # three-way bfloat16 splits on the bfloat16 matrix cores: A's read from HBM bounds it
+        gbs = 4.0 * m * n / (ms_launch * 1e-3) / 1e9
+        bound = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                 "frac": round(gbs / PEAK_HBM_GBS, 4), "tflops": round(achieved, 2)}
+        kname = "dense products A H^T and W^T A (six bf16 MFMA 16x16x32 terms per float product)"
+    else:
+        bound = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_FP64_TFLOPS,
+                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP64_TFLOPS, 4)}
+        kname = "dense products A H^T and W^T A (MFMA 16x16x4 f64)"
+    roofline = {**bound,
                 "traffic": (tr["hbm_bytes_per_launch"] if tr else None),
-                "kernel": "dense products A H^T and W^T A (MFMA 16x16x4 %s)" % wl["dtype"],
+                "kernel": kname,
                 "ms_per_launch": round(ms_launch, 4),
                 "ms_aht": round(stats["ms_mm_aht"] / args.steps, 4),
                 "ms_wta": round(stats["ms_mm_wta"] / args.steps, 4),

@@ -32,7 +32,9 @@
  *   nmf_last_error() describes the most recent failure on a context.
  * - Element types: NMF_F64 runs everything in double; NMF_F32 stores A, W, H
  *   in float and accumulates the large products in float on the matrix
- *   cores, with the Gram split-sums and the objective accumulated in double.
+ *   cores (each float taken as an exact sum of three bfloat16 values; results
+ *   are as accurate as with float operands), with the Gram split-sums and the
+ *   objective accumulated in double.
  *   NMF_BF16 (dense A only) stores A as bfloat16 (each element the 16 bits
  *   of the value, row pitch lda a multiple of 8 elements, rows 16-byte
  *   aligned) with W, H and every other array in float: the two large
@@ -111,9 +113,11 @@ typedef struct {
   int timers;        /* nonzero: fill the per-phase times in nmf_stats       */
   int check_input;   /* nonzero: scan A for NaN/Inf/negative entries and the */
                      /* CSR arrays for out-of-range or unsorted columns      */
-  int transpose_a;   /* dense A: 0 (default) keeps a transposed copy of A in */
-                     /* device memory for the call when it fits (both large  */
-                     /* products then stream A row by row); -1 never does.   */
+  int transpose_a;   /* NMF_F64 A: 0 (default) keeps a transposed copy of A  */
+                     /* in device memory for the call when it fits (both     */
+                     /* large products then stream A row by row); -1 never   */
+                     /* does. NMF_F32 products read A itself in both         */
+                     /* directions and take either value.                    */
                      /* NMF_BF16 and NMF_FP8_E4M3 A always need the copy: */
                      /* -1 is rejected and                                  */
                      /* a copy that does not fit returns NMF_ENOMEM          */

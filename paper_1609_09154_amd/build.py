@@ -11,7 +11,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["gemm.hip", "gemm_bf16.hip", "update.hip", "objective.hip", "sparse.hip", "bpp.hip", "autograd.hip", "api.hip"]
+SOURCES = ["hals_f32.hip", "hals_f64.hip", "bpp.hip", "gemm.hip", "update.hip", "gemm_f64.hip", "autograd.hip",
+           "gemm_bf16.hip", "objective.hip", "sparse.hip", "api.hip"]
 LIB_NAME = "libnmf_mi355x.so"
 ARCH = "gfx950"
 

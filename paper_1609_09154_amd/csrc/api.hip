@@ -302,7 +302,7 @@ template <> nmf_dtype dtype_of<double>() { return NMF_F64; }
 // Everything one AU-NMF call needs on the device.
 template <typename T> struct Work {
   T *W, *Ht, *P, *R, *Q, *S, *norms, *part;
-  T *Wt, *Hk;  // W^T (KP x m) and H (KP x n): the rank side of the dense products
+  T *Wt, *Hk;  // the copies of W and H the dense products read (copy_elems)
   double* ginv;  // KP x KP, ABPP
   double *obj_part, *relerr, *normA;
   double *pg_part, *pg_val;  // projected-gradient partials; [0] H half, [1] W half
@@ -347,10 +347,22 @@ nmf_status local_update(nmf_ctx* ctx, int algo, T* X, nmfk::Split<T> P, const T*
   return NMF_OK;
 }
 
+// The copy of a rows x KP factor that a dense product reads: its packed
+// bfloat16 planes for float (every float product needs them), its transpose
+// for double.
+template <typename T> int64_t copy_elems(int64_t rows, int KP) {
+  return sizeof(T) == 4 ? nmfk::split_floats(rows, KP) : rows * KP;
+}
+template <typename T>
+hipError_t factor_copy(const T* X, int64_t rows, int KP, T* dst, hipStream_t st) {
+  if constexpr (sizeof(T) == 4) return nmfk::pack_split(X, rows, KP, KP, KP, dst, st);
+  else return nmfk::transpose_rows<T>(X, rows, KP, dst, st);
+}
+
 template <typename T>
 nmf_status gram(nmf_ctx* ctx, const T* X, int64_t rows, int KP, T* G, T* part,
                 T* Gt = nullptr) {
-  nmfk::GemmArgs<T> a{X, KP, X, KP, G, KP, KP, KP, rows, false, 0, Gt};
+  nmfk::GemmArgs<T> a{X, KP, X, KP, G, KP, KP, KP, rows, false, Gt};
   HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN_GRAM, a, gram_splits(rows), part, ctx->stream));
   return NMF_OK;
 }
@@ -379,9 +391,9 @@ size_t plan_work(int64_t m, int64_t n, int KP, int iters, int64_t obj_np, int64_
   off[9] = cv.take<double>(iters + 2);
   off[10] = cv.take<int>(4);
   off[11] = cv.take<unsigned long long>(nmfk::BPP_TALLIES);
-  // transposed factor copies for the dense products (unused for sparse A)
-  off[12] = cv.take<T>(sparse ? 0 : m * KP);
-  off[13] = cv.take<T>(sparse ? 0 : n * KP);
+  // the factor copies the dense products read (unused for sparse A)
+  off[12] = cv.take<T>(sparse ? 0 : copy_elems<T>(m, KP));
+  off[13] = cv.take<T>(sparse ? 0 : copy_elems<T>(n, KP));
   off[14] = cv.take<double>(KP * KP);
   off[15] = cv.take<double>(nmfk::pgrad_partials(std::max(m, n)));
   off[16] = cv.take<double>(4);
@@ -479,8 +491,8 @@ nmf_status lp_product(nmf_ctx* ctx, const Prob<float>& pb, const void* X, int64_
   return NMF_OK;
 }
 
-// Ft (nullable) is F transposed (KP x rows of F); the dense kernels then read
-// the rank-side operand with 16-byte loads.
+// Ft is the factor's copy (factor_copy): float dense products need it; double
+// ones (nullable there) then read the rank side with 16-byte loads.
 template <typename T>
 nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F,
                       const T* Ft, int k, int KP, T* Pout, T* part, int* nsplit = nullptr) {
@@ -497,17 +509,24 @@ nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, con
     if constexpr (sizeof(T) == 4) return lp_product(ctx, pb, pb.Alp, pb.lda, m, n, F, KP, Pout, part);
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
-  if (pb.At) {
-    // A H^T = (A^T)^T H^T: the TN kernel streaming A^T row by row.
-    nmfk::GemmArgs<T> a{pb.At, m, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
-                        Ft != nullptr, k};
-    HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
+  if constexpr (sizeof(T) == 4) {
+    if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
+    HIP_TRY(nmfk::gemm_split(false, pb.A, pb.lda, Ft, F, KP, KP, Pout, KP, KP, m, KP, n, part,
+                             ctx->stream, nsplit));
+    return NMF_OK;
+  } else {
+    if (pb.At) {
+      // A H^T = (A^T)^T H^T: the TN kernel streaming A^T row by row.
+      nmfk::GemmArgs<T> a{pb.At, m, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
+                          Ft != nullptr};
+      HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
+      return NMF_OK;
+    }
+    nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
+                        Ft != nullptr};
+    HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::NN, a, 0, part, ctx->stream, nsplit));
     return NMF_OK;
   }
-  nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
-                      Ft != nullptr, k};
-  HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::NN, a, 0, part, ctx->stream, nsplit));
-  return NMF_OK;
 }
 
 template <typename T>
@@ -528,10 +547,17 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
       return lp_product(ctx, pb, pb.Alpt, pb.ldat, n, m, F, KP, Rout, part);
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
-  nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? m : (int64_t)KP, Rout, KP, n, KP, m,
-                      Ft != nullptr, k};
-  HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
-  return NMF_OK;
+  if constexpr (sizeof(T) == 4) {
+    if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
+    HIP_TRY(nmfk::gemm_split(true, pb.A, pb.lda, Ft, F, KP, KP, Rout, KP, KP, n, KP, m, part,
+                             ctx->stream, nsplit));
+    return NMF_OK;
+  } else {
+    nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? m : (int64_t)KP, Rout, KP, n, KP, m,
+                        Ft != nullptr};
+    HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
+    return NMF_OK;
+  }
 }
 
 // Relative error of the current (W, Ht) into relerr[slot]. q_current says
@@ -637,21 +663,23 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
     RUN(norm_sq_A<T>(ctx, pb, m, n, w));
     RUN(objective<T>(ctx, pb, m, n, k, KP, w, 0));
   }
+  // The factors' copies for the dense products: float products always read
+  // them; double ones read 16-byte runs of them, so their rows must stay
+  // 16-byte aligned, and below 2^22 entries of A they read the factors in
+  // place (the copy's launch would cost more than its loads save).
+  const bool dense = !pb.sparse && !pb.lp;
+  const bool big = m * n >= ((int64_t)1 << 22);
+  const bool tH = dense && (sizeof(T) == 4 || (big && (n * (int64_t)sizeof(T)) % 16 == 0));
+  const bool tW = dense && (sizeof(T) == 4 || (big && (m * (int64_t)sizeof(T)) % 16 == 0));
   if (pgstop) {
     // H half at the initial factors
     tm.mark(PH_OBJ);
     RUN(gram<T>(ctx, w.W, m, KP, w.S, w.part));
-    RUN(product_AtF<T>(ctx, pb, m, n, w.W, nullptr, k, KP, w.R, w.part));
+    if (tW) HIP_TRY(factor_copy<T>(w.W, m, KP, w.Wt, st));
+    RUN(product_AtF<T>(ctx, pb, m, n, w.W, tW ? w.Wt : nullptr, k, KP, w.R, w.part));
     RUN(pg_half<T>(ctx, w.Ht, w.R, w.S, n, k, KP, w, 0));
   }
-  // Transposed factor copies for the dense products (read with 16-byte loads,
-  // so their rows must stay 16-byte aligned). Below 2^22 entries of A the
-  // products read the factors in place: the copy's launch would cost more
-  // than its loads save.
-  const bool big = m * n >= ((int64_t)1 << 22);
-  const bool tH = big && !pb.sparse && !pb.lp && (n * (int64_t)sizeof(T)) % 16 == 0;
-  const bool tW = big && !pb.sparse && !pb.lp && (m * (int64_t)sizeof(T)) % 16 == 0;
-  if (tH && o->iters > 0) HIP_TRY(nmfk::transpose_rows<T>(w.Ht, n, KP, w.Hk, st));
+  if (tH && o->iters > 0) HIP_TRY(factor_copy<T>(w.Ht, n, KP, w.Hk, st));
   // the updates' Gram shares (w.gsl); qready: Q already holds the current H's
   // Gram
   int nsp_w_v = 1, nsp_h_v = 1;
@@ -672,7 +700,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
   const nmfk::ShareOf upd = o->algo == NMF_MU ? nmfk::ShareOf::MU : nmfk::ShareOf::HALS;
   int* nsp_w = hand && nmfk::takes_slabs(upd, m) ? &nsp_w_v : nullptr;
   int* nsp_h = hand && nmfk::takes_slabs(upd, n) ? &nsp_h_v : nullptr;
-  // MU and HALS at KP <= 64 write the transposed copies the next product
+  // MU and HALS at KP <= 64 write the copies the next product
   // reads from their own output tiles (not HALS's W, which the
   // normalisation rescales after the sweep)
   const bool own_t = (o->algo == NMF_MU || o->algo == NMF_HALS) && KP <= 64;
@@ -720,7 +748,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
       HIP_TRY(nmfk::hals_normalize<T>(w.W, w.W, m, w.Ht, w.Ht, 0, w.S, w.norms, k, KP, st,
                                       Wt_nrm));
     }
-    if (tW && !Wt_upd && !Wt_nrm) HIP_TRY(nmfk::transpose_rows<T>(w.W, m, KP, w.Wt, st));
+    if (tW && !Wt_upd && !Wt_nrm) HIP_TRY(factor_copy<T>(w.W, m, KP, w.Wt, st));
     tm.mark(PH_MM_T);
     RUN(product_AtF<T>(ctx, pb, m, n, w.W, tW ? w.Wt : nullptr, k, KP, w.R, w.part, nsp_h));
     tm.mark(PH_LUC);
@@ -737,7 +765,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
       }
       qready = true;
     }
-    if (next_t && !own_t) HIP_TRY(nmfk::transpose_rows<T>(w.Ht, n, KP, w.Hk, st));
+    if (next_t && !own_t) HIP_TRY(factor_copy<T>(w.Ht, n, KP, w.Hk, st));
     if (pgstop) {
       tm.mark(PH_OBJ);
       RUN(pg_half<T>(ctx, w.Ht, w.R, w.S, n, k, KP, w, 0));
@@ -758,7 +786,8 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
       // the W half at the returned factors, for the final ratio
       tm.mark(PH_OBJ);
       RUN(gram<T>(ctx, w.Ht, n, KP, w.Q, w.part));
-      RUN(product_AF<T>(ctx, pb, m, n, w.Ht, nullptr, k, KP, w.P, w.part));
+      if (tH) HIP_TRY(factor_copy<T>(w.Ht, n, KP, w.Hk, st));
+      RUN(product_AF<T>(ctx, pb, m, n, w.Ht, tH ? w.Hk : nullptr, k, KP, w.P, w.part));
       RUN(pg_half<T>(ctx, w.W, w.P, w.Q, m, k, KP, w, 1));
       double h[2];
       RUN(read_doubles(ctx, w.pg_val, h, 2));
@@ -936,7 +965,10 @@ nmf_status dense_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int lp, co
   pb.lda = lda;
   if (lp) {
     if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo, o->iters > 0)) != NMF_OK) return s;
-  } else if (o->iters > 0 && o->transpose_a == 0) {
+  } else if (sizeof(T) == 8 && o->iters > 0 && o->transpose_a == 0) {
+    // float products read A in either direction at nearly the same rate
+    // (65536^2: 3.2 and 3.3 ms), so a copy (6.5 ms) would pay only after some
+    // fifty iterations
     if ((s = transposed_copy<T>(ctx, A, lda, m, n, m, &pb.At)) != NMF_OK) return s;
   }
   StopInfo si;
@@ -1190,9 +1222,27 @@ nmf_status pad_any(nmf_ctx* ctx, const T* X, int64_t rows, int k, int64_t ldx, T
   return NMF_OK;
 }
 
-template <typename T>
-nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, const T* A,
-                           int64_t lda, int k, const T* F, int64_t ldf, T* Out) {
+nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, const float* A,
+                           int64_t lda, int k, const float* F, int64_t ldf, float* Out) {
+  const int KP = kp_dense(k);
+  const int64_t frows = transA ? m : n, orows = transA ? n : m;
+  const int64_t splits = nmfk::gemm_split_splits(orows, KP, frows);
+  Carve cv;
+  const size_t oFp = cv.take<float>(nmfk::split_floats(frows, KP));
+  const size_t oP = cv.take<float>(splits > 1 ? splits * orows * KP : 1);
+  nmf_status s = ensure_ws(ctx, cv.off);
+  if (s != NMF_OK) return s;
+  float* Fp = at<float>(ctx, oFp);
+  // the planes from the caller's F, the product straight into the caller's P
+  HIP_TRY(nmfk::pack_split(F, frows, ldf, k, KP, Fp, ctx->stream));
+  HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, Out, k, k, orows, KP, frows,
+                           at<float>(ctx, oP), ctx->stream));
+  return NMF_OK;
+}
+
+nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, const double* A,
+                           int64_t lda, int k, const double* F, int64_t ldf, double* Out) {
+  typedef double T;
   const int KP = kp_dense(k);
   const int64_t frows = transA ? m : n, orows = transA ? n : m;
   const int64_t splits = transA ? nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, n, KP, m)
@@ -1413,10 +1463,10 @@ static nmf_status dense_prod(nmf_ctx* ctx, bool transA, nmf_dtype dtype, int64_t
     return dense_prod_lp_impl(ctx, transA, dtype, m, n, A, lda, k, (const float*)F, ldf,
                               (float*)Out);
   if (dtype == NMF_F32)
-    return dense_prod_impl<float>(ctx, transA, m, n, (const float*)A, lda, k, (const float*)F,
+    return dense_prod_impl(ctx, transA, m, n, (const float*)A, lda, k, (const float*)F,
                                   ldf, (float*)Out);
   if (dtype == NMF_F64)
-    return dense_prod_impl<double>(ctx, transA, m, n, (const double*)A, lda, k,
+    return dense_prod_impl(ctx, transA, m, n, (const double*)A, lda, k,
                                    (const double*)F, ldf, (double*)Out);
   return fail(ctx, NMF_EINVAL, "unknown dtype");
 }
@@ -1623,7 +1673,7 @@ size_t mu_plan_common(int64_t m, int64_t n, int KP, Carve& cv, size_t off[8]) {
   off[3] = cv.take<T>(n * KP);
   off[4] = cv.take<T>(KP * KP);
   off[5] = cv.take<T>(KP * KP);
-  off[6] = cv.take<T>(mx * KP);
+  off[6] = cv.take<T>(copy_elems<T>(mx, KP));
   off[7] = cv.take<T>(part);
   return cv.off;
 }
@@ -1635,16 +1685,16 @@ MuWork<T> mu_bind(nmf_ctx* ctx, const size_t off[8]) {
                    at<T>(ctx, off[6]), at<T>(ctx, off[7])};
 }
 
-// Rank-side operands of the dense products are read from a transposed copy
-// (w.Ft) when its rows are 16-byte aligned. ft_ready: the producer of F has
-// already written that copy. With parts set, a split product stays in its
+// Rank-side operands of the dense products are read from the factor's copy
+// (w.Ft): always for float, for double when its rows are 16-byte aligned.
+// ft_ready: the producer of F has already written that copy. With parts set, a split product stays in its
 // slabs (in w.part) for the consumer to sum; otherwise Out receives it.
 template <typename T>
 nmf_status mu_prod_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F, int k,
                       int KP, T* Out, MuWork<T>& w, bool ft_ready = false,
                       nmfk::Split<T>* parts = nullptr) {
-  const bool tf = (n * (int64_t)sizeof(T)) % 16 == 0;
-  if (tf && !ft_ready) HIP_TRY(nmfk::transpose_rows<T>(F, n, KP, w.Ft, ctx->stream));
+  const bool tf = sizeof(T) == 4 || (n * (int64_t)sizeof(T)) % 16 == 0;
+  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, n, KP, w.Ft, ctx->stream));
   int ns = 1;
   nmf_status s = product_AF<T>(ctx, pb, m, n, F, tf ? w.Ft : nullptr, k, KP, Out, w.part,
                                parts ? &ns : nullptr);
@@ -1656,8 +1706,8 @@ template <typename T>
 nmf_status mu_prod_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F, int k,
                        int KP, T* Out, MuWork<T>& w, bool ft_ready = false,
                        nmfk::Split<T>* parts = nullptr) {
-  const bool tf = (m * (int64_t)sizeof(T)) % 16 == 0;
-  if (tf && !ft_ready) HIP_TRY(nmfk::transpose_rows<T>(F, m, KP, w.Ft, ctx->stream));
+  const bool tf = sizeof(T) == 4 || (m * (int64_t)sizeof(T)) % 16 == 0;
+  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, m, KP, w.Ft, ctx->stream));
   int ns = 1;
   nmf_status s = product_AtF<T>(ctx, pb, m, n, F, tf ? w.Ft : nullptr, k, KP, Out, w.part,
                                 parts ? &ns : nullptr);
@@ -1665,18 +1715,18 @@ nmf_status mu_prod_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
   return s;
 }
 
-// Whether a row kernel can hand a rows x KP factor to the next product as the
-// transposed copy directly (the product reads one for these rows).
+// Whether a row kernel can hand a rows x KP factor to the next product as
+// that copy directly (the product reads one for these rows).
 template <typename T>
 bool rows_transposable(int64_t rows, int KP) {
-  return (rows * (int64_t)sizeof(T)) % 16 == 0 && KP <= 64;
+  return (sizeof(T) == 4 || (rows * (int64_t)sizeof(T)) % 16 == 0) && KP <= 64;
 }
 
 // One MU iteration from (W, Ht) into (Wn, Htn) (which may alias W, Ht),
 // leaving Q = H H^T and S = Wn^T Wn in the given buffers (and their
 // transposes in Qt and St where set), and P = A H^T and R = A^T Wn where P
 // and R are set (nullable). The products reach the updates as their split
-// slabs. *ft: on entry, whether w.Ft holds Ht's transposed copy; on return,
+// slabs. *ft: on entry, whether w.Ft holds Ht's copy; on return,
 // whether it holds Htn's (the update writes it for the next iteration's
 // product). With gsl set (room for plan_shares' blocks), the Grams are
 // summed from row-block shares where plan_shares takes them: each update
@@ -1725,6 +1775,7 @@ nmf_status mu_prepare_A(nmf_ctx* ctx, const T* A, int64_t lda, int64_t m, int64_
                         Prob<T>& pb) {
   pb.A = A;
   pb.lda = lda;
+  if (sizeof(T) == 4) return NMF_OK;   // float products read A in either direction
   return transposed_copy<T>(ctx, A, lda, m, n, m, &pb.At);
 }
 
@@ -1901,7 +1952,7 @@ nmf_status mu_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int6
 // sweep. Wp and Hc (nullable) receive W after the sweep and H^T after the
 // rescaling, which the backward pass needs; every step writes its output
 // where the next one reads it, so nothing is copied. *ft: on entry, whether
-// w.Ft holds Ht's transposed copy; on return, whether it holds Htn's. gsl
+// w.Ft holds Ht's copy; on return, whether it holds Htn's. gsl
 // and *qready: the Gram shares, as for mu_iteration (with the sweeps'
 // blocking).
 template <typename T>
@@ -1929,7 +1980,7 @@ nmf_status hals_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n,
   } else if ((s = gram<T>(ctx, Wsw, m, KP, S, w.part)) != NMF_OK) {
     return s;
   }
-  // the normalisation writes Wn's transposed copy for the product (w.Ft, whose
+  // the normalisation writes Wn's copy for the product (w.Ft, whose
   // copy of Ht the product above has read)
   const bool tW = rows_transposable<T>(m, KP);
   HIP_TRY(nmfk::hals_normalize<T>(Wsw, Wn, m, Ht, Hsc, n, S, nrm, k, KP, st,

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void mu_adjoint_rows_kernel(
       }
     }
   }
-  if (gNt) store_rows_transposed<T, KP, ROWS, DLD>(GNs, rb, rows, gNt);
+  if (gNt) store_rows_copy<T, KP, ROWS, DLD>(GNs, rb, rows, gNt);
 }
 
 // Out[r] = (Out[r] + Y[r]) + X[r] M for rows x KP X and KP x KP M, columns
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(256) void hals_adjoint_rows_kernel(
     block_gram_partial<T, KP, ROWS, DLD>(XOs, Ds, Tslab + (gridDim.x + blockIdx.x) * slab);
   }
   // Delta transposed (Dt[i * rows + r]), the layout the next product reads
-  if (Dt) store_rows_transposed<T, KP, ROWS, DLD>(Ds, rb, rows, Dt);
+  if (Dt) store_rows_copy<T, KP, ROWS, DLD>(Ds, rb, rows, Dt);
 }
 
 // M = S + S^T with S[a][b] = -(a <= b ? T1[a][b] : T2[a][b]) (KP x KP): the

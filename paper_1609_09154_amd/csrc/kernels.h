@@ -10,7 +10,8 @@ namespace nmfk {
 
 enum class GemmKind { NN, TN, TN_GRAM };
 
-// D (M x N) = X * Y (NN, X is M x K) or X^T * Y (TN, X is K x M). Y is
+// Double products, and the Grams of both types (TN_GRAM; float takes no other
+// kind): D (M x N) = X * Y (NN, X is M x K) or X^T * Y (TN, X is K x M). Y is
 // K x N, or, with yt set, its transpose N x K (ldy between its N rows; then
 // Y must be 16-byte aligned with ldy a multiple of 16 bytes). N must be a
 // multiple of 16 between 16 and 128.
@@ -20,7 +21,6 @@ template <typename T> struct GemmArgs {
   T* D; int64_t ldd;
   int64_t M, N, K;
   bool yt;
-  int nvalid;  // output columns that matter (0: all N); columns >= nvalid may be 0
   T* Dt;       // nullable: also receives D transposed (Dt[j * M + i]; Grams only)
 };
 
@@ -54,6 +54,22 @@ template <typename T>
 hipError_t reduce_splits(const T* part, int splits, int64_t dsplit, int64_t M, int N,
                          int64_t ldd, T* D, int64_t ldp, hipStream_t st, T* Dt = nullptr);
 
+// Float products at any rank up to 128: D (M x nout, ld ldd) = X F (X M x K)
+// or, tn, X^T F (X K x M) for float X of any pitch ldx and F (K x kv, pitch
+// ldf, given as Fp, its packed planes for KP >= kv columns; F itself is read
+// only where the split does not hold). Columns kv..nout-1 are zero. `part`
+// must hold gemm_split_splits(M, KP, K) * M * KP floats when that count
+// exceeds 1; nsplit as for gemm_run (the slabs then have KP columns).
+hipError_t gemm_split(bool tn, const float* X, int64_t ldx, const float* Fp, const float* F,
+                      int64_t ldf, int kv, float* D, int64_t ldd, int nout, int64_t M, int KP,
+                      int64_t K, float* part, hipStream_t st, int* nsplit = nullptr);
+int64_t gemm_split_splits(int64_t M, int KP, int64_t K);
+// Fp = the packed planes of F (rows x kv, pitch ldf) for KP columns; Fp is
+// 16-byte aligned and holds split_floats(rows, KP) floats.
+hipError_t pack_split(const float* F, int64_t rows, int64_t ldf, int kv, int KP, float* Fp,
+                      hipStream_t st);
+inline int64_t split_floats(int64_t rows, int KP) { return (rows + 31) / 32 * 48 * KP; }
+
 // Reduced-precision products: D (M x N float, ld ldd) = X Y^T for X (M x K)
 // and Y (N x K) stored as bfloat16 bits (uint16_t) or FP8 E4M3 bits
 // (uint8_t), K contiguous in both (rows 16-byte aligned, ldx and ldy whole
@@ -79,8 +95,8 @@ hipError_t pack_fp8_t(const float* F, int64_t rows, int KP, uint8_t* Ft, int64_t
 // Local updates on rows x KP row-major factors (leading dimension KP); k is
 // the true rank, entries k..KP-1 are zero padding and stay zero.
 // mu_rows and hals_rows write the updated rows of X to Xn (Xn == X: in
-// place) and, when Xt is set (KP <= 64), their transpose Xt[i * rows + r] as
-// well; P is summed from its slabs (mu_rows: Pout, nullable, receives the
+// place) and, when Xt is set (KP <= 64), the copy the next product reads as
+// well (double: their transpose Xt[i * rows + r]; float: their packed planes); P is summed from its slabs (mu_rows: Pout, nullable, receives the
 // sum). Gslab (nullable, KP <= 64) receives the row blocks' shares of
 // Xn^T Xn, one KP x KP slab per block of share_rows rows (cdiv(rows,
 // share_rows) of them), for an ordered sum (reduce_splits).
@@ -94,6 +110,10 @@ hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int 
 template <typename T>
 hipError_t hals_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int KP,
                      T* Xt, T* Gslab, hipStream_t st, const T* Xs = nullptr);
+// Lanes per row of the HALS sweep at `rows` rows: many rows fill the chip with
+// small groups, which take fewer permutation steps per column; few rows need
+// larger groups to fill it.
+inline int hals_tpr(int64_t rows) { return rows >= 65536 ? 4 : (rows >= 16384 ? 8 : 16); }
 // Rows per block of an update's Gram shares (0: the update writes none at
 // this KP): mu_rows at any row count, hals_rows at `rows` rows.
 enum class ShareOf { MU, HALS };
@@ -108,9 +128,9 @@ template <typename T>
 hipError_t gram_shares(const T* X, int64_t rows, int KP, int rpb, T* Gslab, hipStream_t st);
 
 // HALS normalisation: s_i = sqrt(S[i][i]); W[:, i] /= s_i, Ht[:, i] *= s_i and
-// S[i][j] /= s_i s_j for s_i > 0. norms receives s. Wt (nullable, KP <= 64,
-// m a multiple of 16 / sizeof(T)) receives the transpose of the rescaled W,
-// Wt[i * m + r].
+// S[i][j] /= s_i s_j for s_i > 0. norms receives s. Wt (nullable, KP <= 64;
+// double: m a multiple of 2) receives the copy of the rescaled W that the next
+// product reads (as mu_rows' Xt).
 template <typename T>
 hipError_t hals_normalize(const T* W, T* Wn, int64_t m, const T* Ht, T* Htn, int64_t n, T* S,
                           T* norms, int k, int KP, hipStream_t st, T* Wt = nullptr);
@@ -198,7 +218,7 @@ hipError_t csr_sumsq(const float* vals, int64_t nnz, double* partial, int64_t np
 // the next half-step's product and Gram pass back): gN = g * X / D,
 // gD = -g * Xn / D, gX = g * N / D + gD G^T (D = X G + eps). Gt and Mt are
 // the transposes of G and M (as the Gram's reduction writes them). gNt
-// (nullable) receives gN transposed, gNt[i * rows + r].
+// (nullable) receives gN as the next product reads it (mu_rows' Xt).
 // Gslab (nullable) receives the Gram gradient dL/dG = X^T gD as one KP x KP
 // slab per row block (mu_adjoint_blocks of them), to be summed in order.
 template <typename T>
@@ -210,7 +230,7 @@ int64_t mu_adjoint_blocks(int64_t rows, int KP);
 // Reverse of the HALS sweep on rows x KP rows (KP in {16, 32, 48, 64}): from
 // the sweep's output Xnew, the Gram G and gXnew = dL/dXnew, writes
 // gXold = dL/dX (input) and Delta = dL/dP (one delta per row and column);
-// Dt (nullable) receives Delta transposed, Dt[i * rows + r]. With Xold (the
+// Dt (nullable) receives Delta as the next product reads it. With Xold (the
 // sweep's input) and Tslab set, the row blocks' shares of Xnew^T Delta and
 // Xold^T Delta go to Tslab: hals_adjoint_blocks slabs of KP x KP each, then as
 // many again, to be summed in order.

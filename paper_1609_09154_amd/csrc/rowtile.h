@@ -1,12 +1,14 @@
-// Transposed store of a block of factor rows, shared by the row kernels that
-// hand their output to a dense product: the products read the rank-side
-// factor as KP x rows (each rank column's rows contiguous, 16-byte loads
-// along the reduction index), and a row kernel that already holds its block
-// of rows in LDS writes that copy directly instead of a separate transpose.
+// Store of a block of factor rows in the layout the dense products read,
+// shared by the row kernels that hand their output to one: double products
+// read the rank-side factor as KP x rows (each rank column's rows contiguous,
+// 16-byte loads along the reduction index), float products its packed
+// bfloat16 planes (split.h). A row kernel that already holds its block of
+// rows in LDS writes that copy directly instead of a separate pass.
 #pragma once
 
 #include "common.h"
 #include "kernels.h"
+#include "split.h"
 
 namespace nmfk {
 
@@ -209,15 +211,35 @@ __device__ __forceinline__ void block_gram_partial(const T* Xs, const T* Ds, T* 
 }
 
 // Writes rows [rb, rb + ROWS) of a rows x KP block held in LDS as
-// tile[q * LD + i] (q = row - rb) to out[i * rows + row]. Column i's rows of
-// the block go out as whole 16-byte runs when rows is a multiple of VEC (out
-// is then 16-byte aligned at every run); rows past the end are skipped. Uses
-// every thread of the block; the caller synchronises before (tile written)
-// and nothing after.
+// tile[q * LD + i] (q = row - rb) as the dense products
+// read them. double: out[i * rows + row], column i's rows of the block as
+// whole 16-byte runs when rows is a multiple of VEC (out is then 16-byte
+// aligned at every run), rows past the end skipped. float: the block's packed
+// chunks, zero past the end; the last block also writes the zero groups up to
+// the padded row count. Uses every thread of the block; the caller synchronises before (tile
+// written) and nothing after.
 template <typename T, int KP, int ROWS, int LD>
-__device__ __forceinline__ void store_rows_transposed(const T* tile, int64_t rb, int64_t rows,
-                                                      T* __restrict__ out) {
+__device__ __forceinline__ void store_rows_copy(const T* tile, int64_t rb, int64_t rows,
+                                                T* __restrict__ out) {
   constexpr int VEC = Tr<T>::VEC;
+  if constexpr (sizeof(T) == 4) {
+    static_assert(ROWS % 8 == 0, "whole groups per block");
+    u32x4* o = reinterpret_cast<u32x4*>(out);
+    for (int e = threadIdx.x; e < KP * (ROWS / 8); e += blockDim.x) {
+      const int i = e % KP, q = e / KP;
+      if (rb / 8 + q >= split_groups(rows)) break;
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        x[u] = rb + 8 * q + u < rows ? tile[(8 * q + u) * LD + i] : 0.f;
+      store_split_chunk(x, rb / 8 + q, KP, i, o);
+    }
+    if (rb + ROWS >= rows) {
+      const int64_t c0 = (rb + ROWS) / 8 * 3 * KP, c1 = split_groups(rows) * 3 * KP;
+      for (int64_t e = c0 + threadIdx.x; e < c1; e += blockDim.x) o[e] = u32x4{0, 0, 0, 0};
+    }
+    return;
+  }
   static_assert(ROWS % VEC == 0, "whole vectors per column");
   constexpr int RV = ROWS / VEC;
   const bool vec = rows % VEC == 0;
@@ -227,13 +249,10 @@ __device__ __forceinline__ void store_rows_transposed(const T* tile, int64_t rb,
     if (r0 >= rows) continue;
     T* dst = out + (int64_t)i * rows + r0;
     if (vec) {
-      if constexpr (sizeof(T) == 4) {
-        *reinterpret_cast<float4*>(dst) =
-            make_float4(tile[q0 * LD + i], tile[(q0 + 1) * LD + i], tile[(q0 + 2) * LD + i],
-                        tile[(q0 + 3) * LD + i]);
-      } else {
-        *reinterpret_cast<double2*>(dst) = make_double2(tile[q0 * LD + i], tile[(q0 + 1) * LD + i]);
-      }
+      V16<T> w;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) w.v[v] = tile[(q0 + v) * LD + i];
+      store16<T>(dst, w);
     } else {
 #pragma unroll
       for (int v = 0; v < VEC; ++v)
