@@ -560,14 +560,21 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
   }
 }
 
-// Relative error of the current (W, Ht) into relerr[slot]. q_current says
-// whether w.Q holds the Gram of the current Ht (the sparse form needs it).
+// Relative error of the current (W, Ht) into relerr[slot]. grams_current: w.S
+// and w.Q hold the Grams of the current factors (the sparse form needs them).
+// first: also form ||A||^2 (w.normA), which the later ones reuse.
 template <typename T>
-nmf_status objective(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int k, int KP,
-                     Work<T>& w, int slot, bool grams_current = false) {
+nmf_status objective(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int KP, Work<T>& w,
+                     int slot, bool first, bool grams_current = false) {
   hipStream_t st = ctx->stream;
   if (pb.sparse) {
     if constexpr (sizeof(T) == 4) {
+      if (first) {
+        const int64_t np = std::min<int64_t>(w.obj_np, 1024);
+        HIP_TRY(nmfk::csr_sumsq(pb.cv, pb.nnz, w.obj_part, np, st));
+        HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nullptr, np, (const T*)nullptr,
+                                       (const T*)nullptr, 0, nullptr, w.normA, st));
+      }
       // <W^T W, H H^T> covers the zeros; both Grams of the current factors
       // (already in S and Q when grams_current).
       if (!grams_current) {
@@ -577,49 +584,27 @@ nmf_status objective(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int 
         if (s != NMF_OK) return s;
       }
       HIP_TRY(nmfk::csr_residual_sq(pb.rp, pb.ci, pb.cv, m, w.W, w.Ht, KP, w.obj_part, st));
-      HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nmfk::csr_residual_partials(m), w.S, w.Q, KP,
-                                     w.normA, w.relerr + slot, st));
+      HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nullptr, nmfk::csr_residual_partials(m), w.S,
+                                     w.Q, KP, w.normA, w.relerr + slot, st));
       return NMF_OK;
     }
     return NMF_EINVAL;
   }
+  const int64_t np = nmfk::residual_partials(m, n);
+  double* nrm = first ? w.obj_part + np : nullptr;
   if (pb.lp == NMF_BF16) {
     if constexpr (sizeof(T) == 4)
       HIP_TRY((nmfk::residual_sq<float, uint16_t>((const uint16_t*)pb.Alp, pb.lda, m, n, w.W,
-                                                  w.Ht, KP, w.obj_part, st)));
+                                                  w.Ht, KP, w.obj_part, nrm, st)));
   } else if (pb.lp == NMF_FP8_E4M3) {
     if constexpr (sizeof(T) == 4)
       HIP_TRY((nmfk::residual_sq<float, uint8_t>((const uint8_t*)pb.Alp, pb.lda, m, n, w.W,
-                                                 w.Ht, KP, w.obj_part, st)));
+                                                 w.Ht, KP, w.obj_part, nrm, st)));
   } else {
-    HIP_TRY((nmfk::residual_sq<T, T>(pb.A, pb.lda, m, n, w.W, w.Ht, KP, w.obj_part, st)));
+    HIP_TRY((nmfk::residual_sq<T, T>(pb.A, pb.lda, m, n, w.W, w.Ht, KP, w.obj_part, nrm, st)));
   }
-  HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nmfk::residual_partials<T>(m, n), (const T*)nullptr,
-                                 (const T*)nullptr, KP, w.normA, w.relerr + slot, st));
-  (void)k;
-  return NMF_OK;
-}
-
-template <typename T>
-nmf_status norm_sq_A(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, Work<T>& w) {
-  hipStream_t st = ctx->stream;
-  if (pb.sparse) {
-    if constexpr (sizeof(T) == 4) {
-      const int64_t np = std::min<int64_t>(w.obj_np, 1024);
-      HIP_TRY(nmfk::csr_sumsq(pb.cv, pb.nnz, w.obj_part, np, st));
-      HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, np, (const T*)nullptr, (const T*)nullptr, 0,
-                                     (const double*)nullptr, w.normA, st));
-      return NMF_OK;
-    }
-    return NMF_EINVAL;
-  }
-  if (pb.lp == NMF_BF16)
-    HIP_TRY(nmfk::sumsq<uint16_t>((const uint16_t*)pb.Alp, pb.lda, m, n, w.obj_part, st));
-  else if (pb.lp == NMF_FP8_E4M3)
-    HIP_TRY(nmfk::sumsq<uint8_t>((const uint8_t*)pb.Alp, pb.lda, m, n, w.obj_part, st));
-  else HIP_TRY(nmfk::sumsq<T>(pb.A, pb.lda, m, n, w.obj_part, st));
-  HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nmfk::sumsq_partials<T>(m, n), (const T*)nullptr,
-                                 (const T*)nullptr, 0, (const double*)nullptr, w.normA, st));
+  HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nrm, np, (const T*)nullptr, (const T*)nullptr, KP,
+                                 w.normA, w.relerr + slot, st));
   return NMF_OK;
 }
 
@@ -629,8 +614,8 @@ template <typename T>
 nmf_status pg_half(nmf_ctx* ctx, const T* X, const T* P, const T* G, int64_t rows, int k,
                    int KP, Work<T>& w, int slot) {
   HIP_TRY(nmfk::pgrad_sq<T>(X, P, G, rows, k, KP, w.pg_part, ctx->stream));
-  HIP_TRY(nmfk::finish_relerr<T>(w.pg_part, nmfk::pgrad_blocks<T>(rows, KP), (const T*)nullptr,
-                                 (const T*)nullptr, 0, (const double*)nullptr, w.pg_val + slot,
+  HIP_TRY(nmfk::finish_relerr<T>(w.pg_part, nullptr, nmfk::pgrad_blocks<T>(rows, KP),
+                                 (const T*)nullptr, (const T*)nullptr, 0, nullptr, w.pg_val + slot,
                                  ctx->stream));
   return NMF_OK;
 }
@@ -660,8 +645,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
   double pg0 = 0.0;
   if (want_obj) {
     tm.mark(PH_OBJ);
-    RUN(norm_sq_A<T>(ctx, pb, m, n, w));
-    RUN(objective<T>(ctx, pb, m, n, k, KP, w, 0));
+    RUN(objective<T>(ctx, pb, m, n, KP, w, 0, true));
   }
   // The factors' copies for the dense products: float products always read
   // them; double ones read 16-byte runs of them, so their rows must stay
@@ -772,7 +756,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
     }
     if (want_obj) {
       tm.mark(PH_OBJ);
-      RUN(objective<T>(ctx, pb, m, n, k, KP, w, t + 1, sh.on()));
+      RUN(objective<T>(ctx, pb, m, n, KP, w, t + 1, false, sh.on()));
     }
     if (errstop) {
       double e[2];
@@ -929,7 +913,7 @@ nmf_status dense_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int lp, co
                       nmf_stats* stats) {
   const int KP = kp_dense(k);
   const bool want_obj = o->objective != NMF_OBJ_NONE;
-  const int64_t obj_np = std::max(nmfk::residual_partials<T>(m, n), nmfk::sumsq_partials<T>(m, n));
+  const int64_t obj_np = 2 * nmfk::residual_partials(m, n);
   const LpPlan bp = lp ? lp_plan(lp, m, n, KP) : LpPlan{0, 0};
   Carve cv;
   size_t off[18];
@@ -1415,8 +1399,7 @@ nmf_status relerr_impl(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, in
                        const T* Ht, double* out) {
   const int KP = pb.sparse ? kp_sparse(k) : kp_dense(k);
   const int64_t obj_np = pb.sparse ? std::max<int64_t>(nmfk::csr_residual_partials(m), 1024)
-                                   : std::max(nmfk::residual_partials<T>(m, n),
-                                              nmfk::sumsq_partials<T>(m, n));
+                                   : 2 * nmfk::residual_partials(m, n);
   Carve cv;
   size_t off[18];
   plan_work<T>(m, n, KP, 0, obj_np, 0, cv, off, pb.sparse);
@@ -1425,8 +1408,7 @@ nmf_status relerr_impl(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, in
   Work<T> w = bind_work<T>(ctx, off, obj_np);
   HIP_TRY(nmfk::pad_rows<T>(W, m, k, w.W, KP, ctx->stream));
   HIP_TRY(nmfk::pad_rows<T>(Ht, n, k, w.Ht, KP, ctx->stream));
-  if ((s = norm_sq_A<T>(ctx, pb, m, n, w)) != NMF_OK) return s;
-  if ((s = objective<T>(ctx, pb, m, n, k, KP, w, 0)) != NMF_OK) return s;
+  if ((s = objective<T>(ctx, pb, m, n, KP, w, 0, true)) != NMF_OK) return s;
   HIP_TRY(hipMemcpyAsync(out, w.relerr, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   HIP_TRY(hipStreamSynchronize(ctx->stream));
   return NMF_OK;
@@ -2262,8 +2244,8 @@ nmf_status pgrad_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, const T* Pm
   HIP_TRY(nmfk::pad_rows<T>(G, k, k, Gp, KP, st));
   if (KP > k) HIP_TRY(hipMemsetAsync(Gp + (size_t)k * KP, 0, sizeof(T) * (KP - k) * KP, st));
   HIP_TRY(nmfk::pgrad_sq<T>(Xp, Pp, Gp, rows, k, KP, at<double>(ctx, oq), st));
-  HIP_TRY(nmfk::finish_relerr<T>(at<double>(ctx, oq), nmfk::pgrad_blocks<T>(rows, KP),
-                                 (const T*)nullptr, (const T*)nullptr, 0, (const double*)nullptr,
+  HIP_TRY(nmfk::finish_relerr<T>(at<double>(ctx, oq), nullptr, nmfk::pgrad_blocks<T>(rows, KP),
+                                 (const T*)nullptr, (const T*)nullptr, 0, nullptr,
                                  at<double>(ctx, ov), st));
   return read_doubles(ctx, at<double>(ctx, ov), out, 1);
 }

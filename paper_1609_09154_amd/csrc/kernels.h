@@ -155,19 +155,14 @@ template <typename T>
 hipError_t transpose_out(const T* Ht, int k, int64_t n, int KP, T* H, hipStream_t st);
 
 // Objective pieces. Each writes one double partial per block into `partial`
-// (capacity given by *_partials) and a final reduce sums them in order.
-template <typename T>
+// and a final reduce sums them in order.
 int64_t residual_partials(int64_t m, int64_t n);
-// residual_sq: A is stored as TA (T, or with float factors uint16_t bfloat16
-// bits or uint8_t FP8 E4M3 bits). sumsq and check_dense take all four.
+// Squared differences of A - W Ht^T (residual_partials of them) and, npartial
+// set, as many partials of ||A||^2 from the same read of A. A is stored as TA
+// (T, or with float factors uint16_t bfloat16 bits or uint8_t FP8 E4M3 bits).
 template <typename T, typename TA = T>
 hipError_t residual_sq(const TA* A, int64_t lda, int64_t m, int64_t n, const T* W, const T* Ht,
-                       int KP, double* partial, hipStream_t st);
-template <typename T>
-int64_t sumsq_partials(int64_t m, int64_t n);
-template <typename T>
-hipError_t sumsq(const T* A, int64_t lda, int64_t m, int64_t n, double* partial,
-                 hipStream_t st);
+                       int KP, double* partial, double* npartial, hipStream_t st);
 // Squares of the projected gradient of 1/2 ||A - W H||^2 in the factor whose
 // rows are X (rows x KP): g = x G - p per row, kept where x > 0, negative part
 // where x = 0; one double per block: pgrad_blocks<T>(rows, KP) of them, at
@@ -178,12 +173,12 @@ int64_t pgrad_blocks(int64_t rows, int KP);
 template <typename T>
 hipError_t pgrad_sq(const T* X, const T* P, const T* G, int64_t rows, int k, int KP,
                     double* partial, hipStream_t st);
-// out[slot] = sqrt(max(0, sum(partial[0..np)) + add) / ref) where add is the
-// <G1, G2> Frobenius product of two KP x KP matrices (nullable) and ref the
-// double at *ref_sq (nullable: out = the sum itself, no sqrt).
+// *out = sqrt(max(0, sum(partial[0..np)) + add) / *ref_sq) where add is the
+// <G1, G2> Frobenius product of two KP x KP matrices (nullable). With npartial
+// set, *ref_sq is first set to its sum; ref_sq null: *out = the sum itself.
 template <typename T>
-hipError_t finish_relerr(const double* partial, int64_t np, const T* G1, const T* G2, int KP,
-                         const double* ref_sq, double* out, hipStream_t st);
+hipError_t finish_relerr(const double* partial, const double* npartial, int64_t np, const T* G1,
+                         const T* G2, int KP, double* ref_sq, double* out, hipStream_t st);
 
 // Sparse (CSR, float32 values).
 // Rows with more than a fixed number of stored entries (csr_long_rows, in

@@ -1,11 +1,14 @@
 // Relative error ||A - W H||_F / ||A||_F (Section 6.2), evaluated directly:
-// a tile of W H^T... i.e. of W (Ht)^T, is formed on the matrix cores, the
-// matching tile of A is read once, and squared differences are summed in
-// double. Each workgroup writes one double; finish_relerr sums them in a
-// fixed order, so the value is reproducible run to run.
+// tiles of W H are formed on the matrix cores, the matching entries of A are
+// read once, and squared differences are summed in double. Each workgroup
+// writes one double; finish_relerr sums them in a fixed order, so the value
+// is reproducible run to run. The pass that needs ||A|| too (the first of a
+// run) sums the squares of A's entries as it reads them.
 #include "common.h"
 #include "rowtile.h"
 #include "kernels.h"
+
+#include "split_mma.h"
 
 namespace nmfk {
 
@@ -28,101 +31,308 @@ __device__ __forceinline__ double block_sum(double v) {
   return s;  // valid in thread 0
 }
 
-// Each wave: 64 rows x 64 columns of the residual; block = 4 waves stacked in
-// columns (64 x 256).
-constexpr int RT = 64;
-template <typename T, typename TA>
-__global__ __launch_bounds__(256) void residual_kernel(const TA* __restrict__ A, int64_t lda,
-                                                       int64_t m, int64_t n,
-                                                       const T* __restrict__ W,
-                                                       const T* __restrict__ Ht, int KP,
-                                                       double* __restrict__ partial) {
-  constexpr int VEC = Tr<T>::VEC;
-  typedef typename Tr<T>::acc4 acc4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  const int64_t r0 = (int64_t)blockIdx.y * RT;
-  const int64_t c0 = ((int64_t)blockIdx.x * 4 + wave) * RT;
-  double local = 0.0;
-  if (c0 < n) {
-    acc4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = zero4<T>();
-    const T* wr[4];
-    const T* hr[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      int64_t row = r0 + 16 * t + c;
-      row = row < m ? row : m - 1;
-      wr[t] = W + row * KP;
-      int64_t col = c0 + 16 * t + c;
-      col = col < n ? col : n - 1;
-      hr[t] = Ht + col * KP;
-    }
-    for (int kk = 0; kk < KP; kk += 4 * VEC) {
-      V16<T> wa[4], hb[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        wa[t] = load16<T>(wr[t] + kk + VEC * g);
-        hb[t] = load16<T>(hr[t] + kk + VEC * g);
-      }
-#pragma unroll
-      for (int v = 0; v < VEC; ++v)
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b) acc[a][b] = mfma16(wa[a].v[v], hb[b].v[v], acc[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = r0 + 16 * a + acc_row<T>(lane, r);
-        if (row < m) {
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const int64_t col = c0 + 16 * b + c;
-            if (col < n) {
-              const double d = to_double(A[row * lda + col]) - (double)acc[a][b][r];
-              local += d * d;
-            }
-          }
-        }
-      }
+// Residual pass. A block takes 64 columns of A and a run of its rows; its four
+// waves take the run's 16-row tiles in turn. The block's 64 rows of Ht stay
+// with the wave for all its tiles, so a tile costs one read of its 16 x 64
+// entries of A (lane (g, c) takes columns 4 c .. 4 c + 3 of four rows, so a
+// load instruction covers 256 bytes of each row; tile j of the product takes
+// columns 4 c + j to match) and of 16 rows of W, both fetched while the tile
+// before is computed. What bounds it is the read of A: 100003 x 5003 at k =
+// 50 took 1781 us (64 x 256 blocks, element loads after the product, and 55
+// us more to sum their partials, and 755 for ||A||) and takes 0.61 ms (3.3 TB/s;
+// rows of an odd length are not 16-byte aligned), 0.66 with ||A||.
+// Four entries of a row of A, widened to what the difference is taken in.
+template <typename TA> struct A4;
+template <> struct A4<float> {
+  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+  V v;
+  __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const V*>(p); }
+  __device__ __forceinline__ double at(int j) const { return (double)v[j]; }
+  __device__ __forceinline__ void set(int j, float x) { v[j] = x; }
+};
+template <> struct A4<double> {
+  typedef double V __attribute__((ext_vector_type(2), aligned(8)));
+  V v[2];
+  __device__ __forceinline__ void load(const double* p) {
+    v[0] = *reinterpret_cast<const V*>(p);
+    v[1] = *reinterpret_cast<const V*>(p + 2);
   }
-  const double s = block_sum(local);
-  if (threadIdx.x == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+  __device__ __forceinline__ double at(int j) const { return v[j >> 1][j & 1]; }
+  __device__ __forceinline__ void set(int j, double x) { v[j >> 1][j & 1] = x; }
+};
+template <> struct A4<uint16_t> {
+  uint2 v;
+  __device__ __forceinline__ void load(const uint16_t* p) { v = *reinterpret_cast<const uint2*>(p); }
+  __device__ __forceinline__ double at(int j) const {
+    const unsigned w = j < 2 ? v.x : v.y;
+    return (double)__uint_as_float((j & 1) ? w & 0xffff0000u : w << 16);
+  }
+  __device__ __forceinline__ void set(int j, uint16_t x) {
+    unsigned& w = j < 2 ? v.x : v.y;
+    w = (j & 1) ? (w & 0xffffu) | (unsigned)x << 16 : (w & 0xffff0000u) | x;
+  }
+};
+template <> struct A4<uint8_t> {
+  unsigned v;
+  __device__ __forceinline__ void load(const uint8_t* p) { v = *reinterpret_cast<const unsigned*>(p); }
+  __device__ __forceinline__ double at(int j) const {
+    return (double)fp8_e4m3_bits_to_float((uint8_t)(v >> (8 * j)));
+  }
+  __device__ __forceinline__ void set(int j, uint8_t x) {
+    v = (v & ~(0xffu << (8 * j))) | (unsigned)x << (8 * j);
+  }
+};
+
+constexpr int RC = 64;       // columns of A per block
+constexpr int RWAVES = 4;    // waves per block
+
+// One tile's entries of A: row row0 + rr(r), columns col .. col + 3. ACC: the
+// type of the product (row order of its accumulator). A block whose columns
+// run past n loads element by element.
+template <typename TACC, typename TA>
+__device__ __forceinline__ void load_a_tile(A4<TA> (&av)[4], const TA* __restrict__ A, int64_t lda,
+                                            int64_t m, int64_t n, int64_t row0, int64_t col,
+                                            bool full, int lane) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    int64_t row = row0 + acc_row<TACC>(lane, r);
+    row = row < m ? row : m - 1;
+    const TA* p = A + row * lda;
+    if (full) {
+      av[r].load(p + col);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) av[r].set(j, p[col + j < n ? col + j : n - 1]);
+    }
+  }
 }
 
-template <typename T>
+// Adds the tile's squared differences to sr and, NORM, A's squares to sa.
+template <bool NORM, typename TACC, typename TA, typename ACC>
+__device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)[4], int64_t m,
+                                         int64_t n, int64_t row0, int64_t col, int lane,
+                                         double& sr, double& sa) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (row0 + acc_row<TACC>(lane, r) >= m) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (col + j >= n) continue;
+      const double a = av[r].at(j), d = a - (double)acc[j][r];
+      sr = fma(d, d, sr);
+      if constexpr (NORM) sa = fma(a, a, sa);
+    }
+  }
+}
+
+// Float factors: the product on the bfloat16 cores from exact splits
+// (split.h), Ht's planes in registers. KS steps of 32 rank entries.
+template <typename TA, int KS, bool NORM>
+__global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_kernel(
+    const TA* __restrict__ A, int64_t lda, int64_t m, int64_t n, const float* __restrict__ W,
+    const float* __restrict__ Ht, int KP, int64_t rows, double* __restrict__ partial,
+    double* __restrict__ npartial) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int64_t c0 = (int64_t)blockIdx.x * RC, col = c0 + 4 * c;
+  const int64_t rbeg = (int64_t)blockIdx.y * rows, rend = rbeg + rows < m ? rbeg + rows : m;
+  const bool full = c0 + RC <= n;
+  // eight entries 32 s + 8 g .. of a factor row (zero past KP), split
+  auto load8 = [&](float (&x)[8], const float* row, int s) {
+    const int k0 = 32 * s + 8 * g;
+    if (k0 < KP) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 v = *reinterpret_cast<const float4*>(row + k0 + 4 * h);
+        x[4 * h] = v.x; x[4 * h + 1] = v.y; x[4 * h + 2] = v.z; x[4 * h + 3] = v.w;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = 0.f;
+    }
+  };
+  Split8 hp[KS][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float* row = Ht + (col + j < n ? col + j : n - 1) * KP;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      float x[8];
+      load8(x, row, s);
+      hp[s][j] = split8(x);
+    }
+  }
+  double sr = 0.0, sa = 0.0;
+  float wv[KS][8];
+  A4<TA> av[4];
+  auto load_w = [&](int64_t row0) {
+    const int64_t row = row0 + c < m ? row0 + c : m - 1;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) load8(wv[s], W + row * KP, s);
+  };
+  int64_t row0 = rbeg + 16 * wave;
+  if (row0 < rend) {
+    load_w(row0);
+    load_a_tile<float>(av, A, lda, m, n, row0, col, full, lane);
+  }
+  for (; row0 < rend; row0 += 16 * RWAVES) {
+    f32x4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
+    Split8 ws[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) ws[s] = split8(wv[s]);
+    A4<TA> cur[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) cur[r] = av[r];
+    const int64_t next = row0 + 16 * RWAVES;
+    if (next < rend) {
+      load_w(next);
+      load_a_tile<float>(av, A, lda, m, n, next, col, full, lane);
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) split_mma(ws[s], hp[s], acc);
+    // products of entries that are not finite: again with the float instruction
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
+    if (__ballot(bad)) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
+      const int64_t row = row0 + c < m ? row0 + c : m - 1;
+      for (int k0 = 0; k0 < KP; k0 += 4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[j] = mfma16(W[row * KP + k0 + g],
+                          Ht[(col + j < n ? col + j : n - 1) * KP + k0 + g], acc[j]);
+    }
+    add_tile<NORM, float>(cur, acc, m, n, row0, col, lane, sr, sa);
+  }
+  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const double s = block_sum(sr);
+  if (threadIdx.x == 0) partial[b] = s;
+  if constexpr (NORM) {
+    __syncthreads();
+    const double t = block_sum(sa);
+    if (threadIdx.x == 0) npartial[b] = t;
+  }
+}
+
+// Double factors: the block's 64 rows of Ht in LDS (row 16 j + c holds column
+// 4 c + j); lane group g takes rank entries k0 + 2 g and k0 + 2 g + 1 of two
+// successive products.
+template <int KP, bool NORM>
+__global__ __launch_bounds__(64 * RWAVES, 2) void residual_f64_kernel(
+    const double* __restrict__ A, int64_t lda, int64_t m, int64_t n, const double* __restrict__ W,
+    const double* __restrict__ Ht, int64_t rows, double* __restrict__ partial,
+    double* __restrict__ npartial) {
+  constexpr int LD = KP + 2;
+  __shared__ __attribute__((aligned(16))) double Hs[RC * LD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int64_t c0 = (int64_t)blockIdx.x * RC, col = c0 + 4 * c;
+  const int64_t rbeg = (int64_t)blockIdx.y * rows, rend = rbeg + rows < m ? rbeg + rows : m;
+  const bool full = c0 + RC <= n;
+  for (int e = threadIdx.x; e < RC * (KP / 2); e += 64 * RWAVES) {
+    const int q = e / (KP / 2), i = 2 * (e % (KP / 2));
+    const int64_t cc = c0 + 4 * (q & 15) + (q >> 4);
+    const V16<double> v = load16<double>(Ht + (cc < n ? cc : n - 1) * KP + i);
+    Hs[q * LD + i] = v.v[0];
+    Hs[q * LD + i + 1] = v.v[1];
+  }
+  __syncthreads();
+  double sr = 0.0, sa = 0.0;
+  A4<double> av[4];
+  int64_t row0 = rbeg + 16 * wave;
+  if (row0 < rend) load_a_tile<double>(av, A, lda, m, n, row0, col, full, lane);
+  for (; row0 < rend; row0 += 16 * RWAVES) {
+    f64x4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = zero4<double>();
+    A4<double> cur[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) cur[r] = av[r];
+    const int64_t next = row0 + 16 * RWAVES;
+    if (next < rend) load_a_tile<double>(av, A, lda, m, n, next, col, full, lane);
+    const double* wr = W + (row0 + c < m ? row0 + c : m - 1) * KP + 2 * g;
+#pragma unroll 2
+    for (int k0 = 0; k0 < KP; k0 += 8) {
+      const V16<double> w = load16<double>(wr + k0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const V16<double> h = load16<double>(&Hs[(16 * j + c) * LD + k0 + 2 * g]);
+        acc[j] = mfma16(w.v[0], h.v[0], acc[j]);
+        acc[j] = mfma16(w.v[1], h.v[1], acc[j]);
+      }
+    }
+    add_tile<NORM, double>(cur, acc, m, n, row0, col, lane, sr, sa);
+  }
+  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const double s = block_sum(sr);
+  if (threadIdx.x == 0) partial[b] = s;
+  if constexpr (NORM) {
+    __syncthreads();
+    const double t = block_sum(sa);
+    if (threadIdx.x == 0) npartial[b] = t;
+  }
+}
+
+// Rows per block: about 2048 blocks (eight per CU: enough to even out the
+// last wave of blocks), at least one tile per wave.
+static int64_t residual_rows(int64_t m, int64_t n) {
+  const int64_t want = cdiv(2048, cdiv(n, RC));
+  return round_up(cdiv(m, want), 16 * RWAVES);
+}
+
 int64_t residual_partials(int64_t m, int64_t n) {
-  return cdiv(n, 4 * RT) * cdiv(m, RT);
+  return cdiv(n, RC) * cdiv(m, residual_rows(m, n));
+}
+
+template <typename TA, int KS>
+static void residual_split_launch(dim3 grid, const TA* A, int64_t lda, int64_t m, int64_t n,
+                                  const float* W, const float* Ht, int KP, int64_t rows,
+                                  double* partial, double* npartial, hipStream_t st) {
+  if (npartial)
+    residual_split_kernel<TA, KS, true><<<grid, 64 * RWAVES, 0, st>>>(A, lda, m, n, W, Ht, KP,
+                                                                       rows, partial, npartial);
+  else
+    residual_split_kernel<TA, KS, false><<<grid, 64 * RWAVES, 0, st>>>(A, lda, m, n, W, Ht, KP,
+                                                                        rows, partial, npartial);
 }
 
 template <typename T, typename TA>
 hipError_t residual_sq(const TA* A, int64_t lda, int64_t m, int64_t n, const T* W, const T* Ht,
-                       int KP, double* partial, hipStream_t st) {
-  dim3 grid((unsigned)cdiv(n, 4 * RT), (unsigned)cdiv(m, RT));
-  residual_kernel<T, TA><<<grid, 256, 0, st>>>(A, lda, m, n, W, Ht, KP, partial);
-  return NMF_LAUNCH_CHECK();
-}
-
-// ||A||^2: one block per 64 rows, double accumulation.
-template <typename T>
-__global__ __launch_bounds__(256) void sumsq_kernel(const T* __restrict__ A, int64_t lda,
-                                                    int64_t m, int64_t n,
-                                                    double* __restrict__ partial) {
-  double local = 0.0;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  for (int64_t r = r0; r < r0 + 64 && r < m; ++r)
-    for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-      const double a = to_double(A[r * lda + j]);
-      local += a * a;
+                       int KP, double* partial, double* npartial, hipStream_t st) {
+  if (KP < 16 || KP > 128 || KP % 16) return hipErrorInvalidValue;
+  const int64_t rows = residual_rows(m, n);
+  const dim3 grid((unsigned)cdiv(n, RC), (unsigned)cdiv(m, rows));
+  if constexpr (sizeof(T) == 8) {
+    switch (KP) {
+#define CASE(K)                                                                                   \
+  case K:                                                                                         \
+    if (npartial)                                                                                 \
+      residual_f64_kernel<K, true><<<grid, 64 * RWAVES, 0, st>>>(A, lda, m, n, W, Ht, rows,       \
+                                                                  partial, npartial);             \
+    else                                                                                          \
+      residual_f64_kernel<K, false><<<grid, 64 * RWAVES, 0, st>>>(A, lda, m, n, W, Ht, rows,      \
+                                                                   partial, npartial);            \
+    break;
+      CASE(16) CASE(32) CASE(48) CASE(64) CASE(80) CASE(96) CASE(112) CASE(128)
+#undef CASE
     }
-  const double s = block_sum(local);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  } else {
+    switch ((KP + 31) / 32) {
+#define CASE(K)                                                                               \
+  case K:                                                                                     \
+    residual_split_launch<TA, K>(grid, A, lda, m, n, W, Ht, KP, rows, partial, npartial, st); \
+    break;
+      CASE(1) CASE(2) CASE(3) CASE(4)
+#undef CASE
+    }
+  }
+  return NMF_LAUNCH_CHECK();
 }
 
 // Projected gradient of 1/2 ||A - W H||_F^2 in one factor (Section 6.2's
@@ -215,34 +425,32 @@ template hipError_t pgrad_sq<float>(const float*, const float*, const float*, in
 template hipError_t pgrad_sq<double>(const double*, const double*, const double*, int64_t, int,
                                      int, double*, hipStream_t);
 
+// One block of 1024 threads; thread t sums partial[t], partial[t+1024], ... in
+// order, then a fixed tree (and the same for npartial, ||A||^2, where given).
 template <typename T>
-int64_t sumsq_partials(int64_t m, int64_t n) {
-  (void)n;
-  return cdiv(m, 64);
-}
-
-template <typename T>
-hipError_t sumsq(const T* A, int64_t lda, int64_t m, int64_t n, double* partial,
-                 hipStream_t st) {
-  sumsq_kernel<T><<<(unsigned)cdiv(m, 64), 256, 0, st>>>(A, lda, m, n, partial);
-  return NMF_LAUNCH_CHECK();
-}
-
-// One block of 256 threads; thread t sums partial[t], partial[t+256], ... in
-// order, then a fixed tree.
-template <typename T>
-__global__ void finish_kernel(const double* __restrict__ partial, int64_t np,
-                              const T* __restrict__ G1, const T* __restrict__ G2, int KP,
-                              const double* __restrict__ ref_sq, double* __restrict__ out) {
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < np; i += blockDim.x) s += partial[i];
+__global__ __launch_bounds__(1024) void finish_kernel(
+    const double* __restrict__ partial, const double* __restrict__ npartial, int64_t np,
+    const T* __restrict__ G1, const T* __restrict__ G2, int KP, double* __restrict__ ref_sq,
+    double* __restrict__ out) {
+  double s = 0.0, q = 0.0;
+  for (int64_t i = threadIdx.x; i < np; i += blockDim.x) {
+    s += partial[i];
+    if (npartial != nullptr) q += npartial[i];
+  }
   if (G1 != nullptr)
     for (int e = threadIdx.x; e < KP * KP; e += blockDim.x) s += (double)G1[e] * (double)G2[e];
   const double tot = block_sum(s);
+  double nrm = 0.0;
+  if (npartial != nullptr) {
+    __syncthreads();
+    nrm = block_sum(q);
+  }
   if (threadIdx.x == 0) {
     if (ref_sq != nullptr) {
+      if (npartial != nullptr) *ref_sq = nrm;
+      else nrm = *ref_sq;
       const double v = tot > 0.0 ? tot : 0.0;
-      *out = sqrt(v / *ref_sq);
+      *out = sqrt(v / nrm);
     } else {
       *out = tot;
     }
@@ -250,9 +458,9 @@ __global__ void finish_kernel(const double* __restrict__ partial, int64_t np,
 }
 
 template <typename T>
-hipError_t finish_relerr(const double* partial, int64_t np, const T* G1, const T* G2, int KP,
-                         const double* ref_sq, double* out, hipStream_t st) {
-  finish_kernel<T><<<1, 256, 0, st>>>(partial, np, G1, G2, KP, ref_sq, out);
+hipError_t finish_relerr(const double* partial, const double* npartial, int64_t np, const T* G1,
+                         const T* G2, int KP, double* ref_sq, double* out, hipStream_t st) {
+  finish_kernel<T><<<1, 1024, 0, st>>>(partial, npartial, np, G1, G2, KP, ref_sq, out);
   return NMF_LAUNCH_CHECK();
 }
 
@@ -278,13 +486,10 @@ hipError_t check_dense(const T* A, int64_t lda, int64_t m, int64_t n, int* flag,
 }
 
 #define INST(T)                                                                               \
-  template int64_t residual_partials<T>(int64_t, int64_t);                                    \
   template hipError_t residual_sq<T, T>(const T*, int64_t, int64_t, int64_t, const T*,        \
-                                        const T*, int, double*, hipStream_t);                 \
-  template int64_t sumsq_partials<T>(int64_t, int64_t);                                       \
-  template hipError_t sumsq<T>(const T*, int64_t, int64_t, int64_t, double*, hipStream_t);    \
-  template hipError_t finish_relerr<T>(const double*, int64_t, const T*, const T*, int,       \
-                                       const double*, double*, hipStream_t);                  \
+                                        const T*, int, double*, double*, hipStream_t);        \
+  template hipError_t finish_relerr<T>(const double*, const double*, int64_t, const T*,       \
+                                       const T*, int, double*, double*, hipStream_t);         \
   template hipError_t check_dense<T>(const T*, int64_t, int64_t, int64_t, int*, hipStream_t);
 INST(float)
 INST(double)
@@ -292,9 +497,7 @@ INST(double)
 #define INST_LP(TA)                                                                         \
   template hipError_t residual_sq<float, TA>(const TA*, int64_t, int64_t, int64_t,          \
                                              const float*, const float*, int, double*,       \
-                                             hipStream_t);                                   \
-  template int64_t sumsq_partials<TA>(int64_t, int64_t);                                    \
-  template hipError_t sumsq<TA>(const TA*, int64_t, int64_t, int64_t, double*, hipStream_t); \
+                                             double*, hipStream_t);                          \
   template hipError_t check_dense<TA>(const TA*, int64_t, int64_t, int64_t, int*, hipStream_t);
 INST_LP(uint16_t)
 INST_LP(uint8_t)
