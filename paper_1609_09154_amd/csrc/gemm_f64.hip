@@ -23,6 +23,8 @@
 // Large reductions can be split (grid.y) into slabs written to a workspace
 // and summed in a fixed order by reduce_splits, so results are bitwise
 // reproducible run to run.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -65,6 +67,19 @@ namespace nmfk {
     }                                                                                     \
   }
 
+// 16 bytes at any element's alignment (rows of A with an odd pitch).
+template <bool STREAM, typename T> __device__ __forceinline__ V16<T> load16u(const T* p) {
+  typedef T VU __attribute__((ext_vector_type(Tr<T>::VEC), aligned(sizeof(T))));
+  const VU* q = reinterpret_cast<const VU*>(p);
+  VU t;
+  if constexpr (STREAM) t = __builtin_nontemporal_load(q);
+  else t = *q;
+  V16<T> r;
+#pragma unroll
+  for (int v = 0; v < Tr<T>::VEC; ++v) r.v[v] = t[v];
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // NN kernel. Y is either K x N (YT = false, ldy between K rows) or its
 // transpose N x K (YT = true, ldy between N rows), which lets each lane fetch
@@ -75,7 +90,7 @@ template <typename T, int NT, int MW> struct FragNN {
   T y[NT][Tr<T>::VEC];
 };
 
-template <typename T, int NT, int MW, bool VX, bool YT, int STAGES, int WPE>
+template <typename T, int NT, int MW, bool YT, int STAGES, int WPE>
 __global__ __launch_bounds__(256, WPE) void gemm_nn_kernel(
     const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t ldy,
     T* __restrict__ D, int64_t ldd, int64_t dsplit, int64_t M, int64_t K,
@@ -110,11 +125,7 @@ __global__ __launch_bounds__(256, WPE) void gemm_nn_kernel(
   {                                                                           \
     const int64_t kk0 = (K0) + VEC * g;                                       \
     _Pragma("unroll") for (int mt = 0; mt < MW; ++mt) {                       \
-      if constexpr (VX) {                                                     \
-        F.x[mt] = load16_stream<T>(xr[mt] + kk0);                             \
-      } else {                                                                \
-        _Pragma("unroll") for (int v = 0; v < VEC; ++v) F.x[mt].v[v] = xr[mt][kk0 + v]; \
-      }                                                                       \
+      F.x[mt] = load16u<false, T>(xr[mt] + kk0);                              \
     }                                                                         \
     _Pragma("unroll") for (int nt = 0; nt < NT; ++nt) {                       \
       if constexpr (YT) {                                                     \
@@ -174,14 +185,24 @@ __global__ __launch_bounds__(256, WPE) void gemm_nn_kernel(
 // rows k0 + 4g + u to MFMA u (u = 0..3). Y is K x N (YT = false) or N x K
 // (YT = true, so the four rows a lane needs are one 16-byte load).
 // ---------------------------------------------------------------------------
-// Column of X that lane column c feeds into M-tile t.  Vector path: tile t
+// Column of X that lane column c feeds into M-tile t. Vector path: tile t
 // takes columns m0 + 16*VEC*(t/VEC) + VEC*c + t%VEC (one 16-byte load per
-// lane covers VEC tiles).  Scalar path: m0 + 16 t + c.
+// lane covers VEC tiles); scalar path: m0 + 16 t + c. Runs past the last
+// column are moved back to end there, so that every wave runs the same
+// pipelined loop; the lanes that then share a column compute and store the
+// same value. (A wave with columns past the end used to take a guarded loop of
+// one memory latency per four rows: 85 of the 93 us of a 3000 x 1700 product
+// at k = 40.)
 template <typename T, bool VX>
-__device__ __forceinline__ int64_t tn_col(int64_t m0, int t, int c) {
+__device__ __forceinline__ int64_t tn_col(int64_t m0, int t, int c, int64_t M) {
   constexpr int VEC = Tr<T>::VEC;
-  if constexpr (VX) return m0 + 16 * VEC * (t / VEC) + VEC * c + (t % VEC);
-  else return m0 + 16 * t + c;
+  if constexpr (VX) {
+    const int64_t b = m0 + 16 * VEC * (t / VEC) + VEC * c;
+    return (b < M - VEC ? b : M - VEC) + t % VEC;
+  } else {
+    const int64_t b = m0 + 16 * t + c;
+    return b < M ? b : M - 1;
+  }
 }
 
 template <typename T, int NT, int MW> struct FragTN {
@@ -189,7 +210,7 @@ template <typename T, int NT, int MW> struct FragTN {
   T y[4][NT];
 };
 
-template <typename T, int NT, int MW, bool VX, bool YT, int STAGES, int WPE>
+template <typename T, int NT, int MW, bool VX, bool YT, int STAGES, int WPE, bool STREAM>
 __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
     const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t ldy,
     T* __restrict__ D, int64_t ldd, int64_t dsplit, int64_t M, int64_t K,
@@ -204,8 +225,9 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
   if (m0 >= M) return;
   const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
   const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
-  // A wave whose columns run past M takes the guarded scalar path.
-  const bool full = m0 + 16 * MW <= M;
+  int64_t xc[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) xc[q] = tn_col<T, VX>(m0, VX ? q * VEC : q, c, M);
 
   acc4 acc[MW][NT];
 #pragma unroll
@@ -223,11 +245,11 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
       const T* xrow = X + kk * ldx;                                           \
       if constexpr (VX) {                                                     \
         _Pragma("unroll") for (int q = 0; q < NQ; ++q) {                      \
-          V16<T> t16 = load16_stream<T>(xrow + m0 + 16 * VEC * q + VEC * c);  \
+          V16<T> t16 = load16u<STREAM, T>(xrow + xc[q]);                      \
           _Pragma("unroll") for (int v = 0; v < VEC; ++v) F.x[u][q * VEC + v] = t16.v[v]; \
         }                                                                     \
       } else {                                                                \
-        _Pragma("unroll") for (int t = 0; t < MW; ++t) F.x[u][t] = xrow[m0 + 16 * t + c]; \
+        _Pragma("unroll") for (int t = 0; t < MW; ++t) F.x[u][t] = xrow[xc[t]];    \
       }                                                                       \
     }                                                                         \
     _Pragma("unroll") for (int nt = 0; nt < NT; ++nt) {                       \
@@ -253,19 +275,18 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
   }
 
   constexpr int KSTEP = 16;
-  int64_t nsteps = (kend - kbeg) / KSTEP;
-  if (!full) nsteps = 0;  // everything through the guarded loop below
+  const int64_t nsteps = (kend - kbeg) / KSTEP;
   NMF_PIPELINE(STAGES, TN_LOAD, TN_COMPUTE, fr, kbeg, nsteps, KSTEP)
 
-  // Guarded remainder, 4 rows at a time (also the whole range for a ragged wave).
+  // Remainder (fewer than 16 rows), 4 at a time.
   for (int64_t k0 = kbeg + nsteps * KSTEP; k0 < kend; k0 += 4) {
     const int64_t kk = k0 + g;
     const bool okk = kk < kend;
     const int64_t kc = okk ? kk : kbeg;
 #pragma unroll
     for (int t = 0; t < MW; ++t) {
-      const int64_t col = tn_col<T, VX>(m0, t, c);
-      fr[0].x[0][t] = (okk && col < M) ? X[kc * ldx + col] : T(0);
+      const T x = X[kc * ldx + tn_col<T, VX>(m0, t, c, M)];
+      fr[0].x[0][t] = okk ? x : T(0);
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -286,11 +307,9 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int rho = acc_row<T>(lane, r);
-      const int64_t row = tn_col<T, VX>(m0, t, rho);
-      if (row < M) {
+      const int64_t row = tn_col<T, VX>(m0, t, rho, M);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) Dp[row * ldd + 16 * nt + c] = acc[t][nt][r];
-      }
+      for (int nt = 0; nt < NT; ++nt) Dp[row * ldd + 16 * nt + c] = acc[t][nt][r];
     }
 }
 
@@ -375,94 +394,112 @@ template hipError_t reduce_splits<double>(const double*, int, int64_t, int64_t, 
 // ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
-// Launch shape of the double products: two waves per SIMD, 64 rows (columns)
-// of A per wave at ranks up to 64, 32 above.
-struct Shape { int mw, stages, wpe; };
-static constexpr Shape prod_shape(int NT) { return Shape{NT <= 4 ? 4 : 2, 2, 2}; }
+// Launch shapes of the double products, two waves per SIMD (TN above rank 80:
+// one, for its registers). A wave takes 64 rows (columns) of A where its two
+// steps in flight fit the registers (NN to rank 64, TN to rank 32: at rank 64
+// the 64-column TN wave spilled and took 2.2 ms for 20000^2, the 32-column one
+// takes 1.17) and the grid still fills the chip; smaller products halve that
+// until it does, down to 16, at low ranks with a deeper pipeline: their time
+// is the latency of a wave's steps (3000 x 1700 at k = 40: 48 workgroups of
+// 64-row waves and 93 us, now 17). 20000^2 at k = 64 runs at 44 TFLOP/s of
+// the 73 that a large matrix product reaches; its register-only pipeline of
+// two steps is what is left.
 constexpr int WAVES = 4;  // waves per workgroup of the product kernels
+constexpr int prod_stages(int NT, int mw) { return mw == 1 && NT <= 2 ? 4 : 2; }
+constexpr int tn_wpe(int NT) { return NT <= 5 ? 2 : 1; }
+static int prod_mw(GemmKind kind, int NT, int64_t M, int64_t K) {
+  const int64_t room = std::max<int64_t>(1, std::min<int64_t>(MAX_PRODUCT_SPLITS, K / 128));
+  int mw = NT <= (kind == GemmKind::NN ? 4 : 2) ? 4 : 2;
+  while (mw > 1 && cdiv(M, 16 * mw * WAVES) * room < 256) mw /= 2;
+  return mw;
+}
 
-// Split the reduction until the grid has about one workgroup per CU, keeping
-// every split at least 256 long. A small product (under 2^26 multiply-adds,
-// such as a 2000 x 1000 matrix at k = 10) may split down to slabs of 64: its
-// few output rows would otherwise leave most of the chip idle while each
-// wavefront walks a long reduction, and at that size the partials cost
-// little. No split is longer than MAX_SPLIT_LEN while the partials stay under
-// 2^28 elements (out_elems per split).
+// Split the reduction until the grid has two workgroups per CU, keeping every
+// split at least 128 long. A small product (under 2^26 multiply-adds, such as
+// a 2000 x 1000 matrix at k = 10) may split down to slabs of 64: at that size
+// the partials cost little. No split is longer than MAX_SPLIT_LEN while the
+// partials stay under 2^28 elements (out_elems per split).
 constexpr int64_t MAX_SPLIT_LEN = 8192;
 static int64_t auto_splits(int64_t wgs, int64_t K, int64_t macs, int64_t out_elems) {
-  const int64_t minlen = macs < ((int64_t)1 << 26) ? 64 : 256;
+  const int64_t minlen = macs < ((int64_t)1 << 26) ? 64 : 128;
   int64_t s = 1;
-  while (wgs * s < 256 && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
+  while (wgs * s < 512 && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
   while (K > s * MAX_SPLIT_LEN && s < MAX_PRODUCT_SPLITS &&
          2 * s * out_elems <= ((int64_t)1 << 28))
     s *= 2;
   return s;
 }
 
-template <typename T, int NT, bool VX, bool YT>
-static void nn_launch(const GemmArgs<T>& a, dim3 grid, int64_t kchunk, T* D, int64_t ldd,
+template <typename T, int NT, int MW>
+static void nn_launch(const GemmArgs<T>& a, int64_t splits, int64_t kchunk, T* D, int64_t ldd,
                       int64_t dsplit, hipStream_t st) {
-  constexpr Shape sh = prod_shape(NT);
-  gemm_nn_kernel<T, NT, sh.mw, VX, YT, sh.stages, sh.wpe><<<grid, 64 * WAVES, 0, st>>>(
+  constexpr int S = prod_stages(NT, MW);
+  const dim3 grid((unsigned)cdiv(a.M, 16 * MW * WAVES), (unsigned)splits);
+  if (a.yt)
+    gemm_nn_kernel<T, NT, MW, true, S, 2><<<grid, 64 * WAVES, 0, st>>>(
+        a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+  else
+    gemm_nn_kernel<T, NT, MW, false, S, 2><<<grid, 64 * WAVES, 0, st>>>(
+        a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+}
+
+template <typename T, int NT, int MW, bool VX, bool STREAM>
+static void tn_launch(const GemmArgs<T>& a, int waves, int64_t splits, int64_t kchunk, T* D,
+                      int64_t ldd, int64_t dsplit, hipStream_t st) {
+  constexpr int S = prod_stages(NT, MW);
+  const dim3 grid((unsigned)cdiv(a.M, 16 * MW * waves), (unsigned)splits);
+  if (a.yt)
+    gemm_tn_kernel<T, NT, MW, VX, true, S, tn_wpe(NT), STREAM><<<grid, 64 * waves, 0, st>>>(
+        a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+  else
+    gemm_tn_kernel<T, NT, MW, VX, false, S, tn_wpe(NT), STREAM><<<grid, 64 * waves, 0, st>>>(
+        a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+}
+
+// Gram: the M side is the padded rank itself, one wave per 16 MW columns; its
+// operands are rows of the workspace, always aligned.
+template <typename T, int NT>
+static void gram_launch(const GemmArgs<T>& a, int64_t splits, int64_t kchunk, T* D, int64_t ldd,
+                        int64_t dsplit, hipStream_t st) {
+  constexpr int MW = sizeof(T) == 8 && NT > 4 ? 2 : NT <= 4 ? NT : 4;
+  const dim3 grid((unsigned)cdiv(a.M, 16 * MW), (unsigned)splits);
+  gemm_tn_kernel<T, NT, MW, MW % Tr<T>::VEC == 0, false, 2, sizeof(T) == 8 ? 1 : 2, true><<<grid, 64, 0, st>>>(
       a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
 }
 
+// TN streams A past the caches (non-temporal loads) where A is larger than the
+// 256 MB last-level cache that would keep it for the next product. NN's load
+// instructions take half a line of a row each, and the other half has to be
+// in the cache when the next asks for it.
 template <typename T, int NT>
-static hipError_t nn_dispatch(const GemmArgs<T>& a, bool vx, int64_t splits, int64_t kchunk,
-                              T* D, int64_t ldd, int64_t dsplit, hipStream_t st) {
-  constexpr Shape sh = prod_shape(NT);
-  dim3 grid((unsigned)cdiv(a.M, 16 * sh.mw * WAVES), (unsigned)splits);
-  if (vx) {
-    if (a.yt) nn_launch<T, NT, true, true>(a, grid, kchunk, D, ldd, dsplit, st);
-    else nn_launch<T, NT, true, false>(a, grid, kchunk, D, ldd, dsplit, st);
-  } else {
-    if (a.yt) nn_launch<T, NT, false, true>(a, grid, kchunk, D, ldd, dsplit, st);
-    else nn_launch<T, NT, false, false>(a, grid, kchunk, D, ldd, dsplit, st);
+static void prod_dispatch(GemmKind kind, const GemmArgs<T>& a, int64_t splits, int64_t kchunk,
+                          T* D, int64_t ldd, int64_t dsplit, hipStream_t st) {
+  const int mw = a.M < 2 ? 1 : prod_mw(kind, NT, a.M, a.K);
+  if (kind == GemmKind::NN) {
+    if constexpr (NT <= 4)
+      if (mw == 4) return nn_launch<T, NT, 4>(a, splits, kchunk, D, ldd, dsplit, st);
+    if (mw == 2) return nn_launch<T, NT, 2>(a, splits, kchunk, D, ldd, dsplit, st);
+    return nn_launch<T, NT, 1>(a, splits, kchunk, D, ldd, dsplit, st);
   }
-  return NMF_LAUNCH_CHECK();
-}
-
-template <typename T, int NT, int MW, int S, int WPE, bool YT>
-static hipError_t tn_launch(const GemmArgs<T>& a, bool vx, int waves, int64_t splits,
-                            int64_t kchunk, T* D, int64_t ldd, int64_t dsplit, hipStream_t st) {
-  dim3 grid((unsigned)cdiv(a.M, 16 * MW * waves), (unsigned)splits);
-  if constexpr (MW % Tr<T>::VEC == 0) {
-    if (vx) {
-      gemm_tn_kernel<T, NT, MW, true, YT, S, WPE><<<grid, 64 * waves, 0, st>>>(
-          a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
-      return NMF_LAUNCH_CHECK();
-    }
+  const bool stream = a.M * a.K * (int64_t)sizeof(T) > ((int64_t)1 << 28);
+  if constexpr (NT <= 2) {
+    if (mw == 4 && stream)
+      return tn_launch<T, NT, 4, true, true>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
+    if (mw == 4)
+      return tn_launch<T, NT, 4, true, false>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
   }
-  gemm_tn_kernel<T, NT, MW, false, YT, S, WPE><<<grid, 64 * waves, 0, st>>>(
-      a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
-  return NMF_LAUNCH_CHECK();
-}
-
-template <typename T, int NT>
-static hipError_t tn_dispatch(const GemmArgs<T>& a, bool vx, bool small_m, int64_t splits,
-                              int64_t kchunk, T* D, int64_t ldd, int64_t dsplit, hipStream_t st) {
-  if (small_m) {
-    // Gram: the M side is the padded rank itself; one wave per 16*MW columns.
-    constexpr int MW = NT <= 4 ? NT : 4;
-    constexpr int MWd = (sizeof(T) == 8 && NT > 4) ? 2 : MW;
-    return tn_launch<T, NT, MWd, 2, 2, false>(a, vx, 1, splits, kchunk, D, ldd, dsplit, st);
-  }
-  if constexpr (sizeof(T) == 8) {
-    constexpr Shape sh = prod_shape(NT);
-    if (a.yt)
-      return tn_launch<T, NT, sh.mw, sh.stages, sh.wpe, true>(a, vx, WAVES, splits, kchunk, D, ldd,
-                                                              dsplit, st);
-    return tn_launch<T, NT, sh.mw, sh.stages, sh.wpe, false>(a, vx, WAVES, splits, kchunk, D, ldd,
-                                                             dsplit, st);
-  }
-  return hipErrorInvalidValue;
+  if (mw == 2 && stream)
+    return tn_launch<T, NT, 2, true, true>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
+  if (mw == 2)
+    return tn_launch<T, NT, 2, true, false>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
+  return tn_launch<T, NT, 1, false, false>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
 }
 
 template <typename T>
 int64_t gemm_auto_splits(GemmKind kind, int64_t M, int64_t N, int64_t K) {
   if (kind == GemmKind::TN_GRAM) return 0;
   if (sizeof(T) == 4) return gemm_split_splits(M, (int)N, K);   // gemm_split's products
-  const int64_t wgs = cdiv(M, 16 * prod_shape((int)(N / 16)).mw * WAVES);
+  const int64_t wgs = cdiv(M, 16 * prod_mw(kind, (int)(N / 16), M, K) * WAVES);
   return auto_splits(wgs, K, M * N * K, M * N);
 }
 
@@ -481,7 +518,6 @@ hipError_t gemm_run(GemmKind kind, const GemmArgs<T>& a_in, int64_t splits, T* p
   int64_t kchunk = round_up(cdiv(a.K, splits), unit);
   splits = cdiv(a.K, kchunk);
   if (splits < 1) splits = 1;
-  const bool vx = aligned16(a.X) && (a.ldx % VEC == 0);
   // A transposed Y is only read with 16-byte loads; otherwise use it as given.
   if (a.yt && !(aligned16(a.Y) && a.ldy % VEC == 0)) return hipErrorInvalidValue;
   const bool small_m = kind == GemmKind::TN_GRAM;
@@ -493,22 +529,19 @@ hipError_t gemm_run(GemmKind kind, const GemmArgs<T>& a_in, int64_t splits, T* p
   T* D = reduce ? part : a.D;
   const int64_t ldd = reduce ? a.N : a.ldd;
   const int64_t dsplit = a.M * a.N;
-  hipError_t e = hipSuccess;
-#define NT_CASE(n)                                                                      \
-  case n:                                                                               \
-    if constexpr (sizeof(T) == 8) {                                                     \
-      if (kind == GemmKind::NN) {                                                       \
-        e = nn_dispatch<T, n>(a, vx, splits, kchunk, D, ldd, dsplit, st);               \
-        break;                                                                          \
-      }                                                                                 \
-    }                                                                                   \
-    e = tn_dispatch<T, n>(a, vx, small_m, splits, kchunk, D, ldd, dsplit, st);          \
-    break;
+  // a Gram reads its padded rows in 16-byte runs
+  if (small_m && (!aligned16(a.X) || a.ldx % Tr<T>::VEC != 0)) return hipErrorInvalidValue;
   switch (NT) {
-    NT_CASE(1) NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8)
-    default: return hipErrorInvalidValue;
+#define CASE(n)                                                                            \
+  case n:                                                                                  \
+    if (small_m) gram_launch<T, n>(a, splits, kchunk, D, ldd, dsplit, st);                 \
+    else if constexpr (sizeof(T) == 8)                                                     \
+      prod_dispatch<T, n>(kind, a, splits, kchunk, D, ldd, dsplit, st);                    \
+    break;
+    CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
+#undef CASE
   }
-#undef NT_CASE
+  const hipError_t e = NMF_LAUNCH_CHECK();
   if (nsplit) *nsplit = (int)splits;
   if (e != hipSuccess || !reduce || nsplit) return e;
   return reduce_splits<T>(part, (int)splits, dsplit, a.M, (int)a.N, a.ldd, a.D, a.N, st, a.Dt);
