@@ -476,18 +476,18 @@ int64_t lp_align(int lp) { return lp == NMF_FP8_E4M3 ? 16 : 8; }
 // Out (M x KP float) = X F^T-style product on the reduced-precision matrix
 // cores: X (M x K, ldx) is A or its transposed copy, F (K x KP float, row
 // layout) the factor, packed (transposed, rounded) into pb.fb first.
-nmf_status lp_product(nmf_ctx* ctx, const Prob<float>& pb, const void* X, int64_t ldx,
+nmf_status lp_product(nmf_ctx* ctx, const Prob<float>& pb, bool tn, const void* X, int64_t ldx,
                       int64_t M, int64_t K, const float* F, int KP, float* Out, float* part) {
   const int64_t ldf = round_up(K, lp_align(pb.lp));
   if (pb.lp == NMF_BF16) {
     HIP_TRY(nmfk::pack_bf16_t(F, K, KP, (uint16_t*)pb.fb, ldf, ctx->stream));
-    HIP_TRY(nmfk::gemm_bf16_nt((const uint16_t*)X, ldx, (const uint16_t*)pb.fb, ldf, Out, KP, M,
-                               KP, K, part, ctx->stream));
+    HIP_TRY(nmfk::gemm_bf16(tn, (const uint16_t*)X, ldx, (const uint16_t*)pb.fb, ldf, Out, KP, M,
+                            KP, K, part, ctx->stream));
     return NMF_OK;
   }
   HIP_TRY(nmfk::pack_fp8_t(F, K, KP, (uint8_t*)pb.fb, ldf, pb.fscale, pb.fmax, ctx->stream));
-  HIP_TRY(nmfk::gemm_fp8_nt((const uint8_t*)X, ldx, (const uint8_t*)pb.fb, ldf, pb.fscale, Out,
-                            KP, M, KP, K, part, ctx->stream));
+  HIP_TRY(nmfk::gemm_fp8(tn, (const uint8_t*)X, ldx, (const uint8_t*)pb.fb, ldf, pb.fscale, Out, KP,
+                         M, KP, K, part, ctx->stream));
   return NMF_OK;
 }
 
@@ -506,7 +506,7 @@ nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, con
   }
   if (pb.lp) {
     // P = A (H^T): H packed as reduced-precision rows (KP x n), K = n contiguous
-    if constexpr (sizeof(T) == 4) return lp_product(ctx, pb, pb.Alp, pb.lda, m, n, F, KP, Pout, part);
+    if constexpr (sizeof(T) == 4) return lp_product(ctx, pb, false, pb.Alp, pb.lda, m, n, F, KP, Pout, part);
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
   if constexpr (sizeof(T) == 4) {
@@ -541,10 +541,11 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
     return fail(ctx, NMF_EINVAL, "sparse path is float32 only");
   }
   if (pb.lp) {
-    // R = A^T W on the transposed copy: W packed as reduced-precision rows (KP x m)
-    if (!pb.Alpt) return fail(ctx, NMF_EINVAL, "reduced-precision A^T W needs the transposed copy");
-    if constexpr (sizeof(T) == 4)
-      return lp_product(ctx, pb, pb.Alpt, pb.ldat, n, m, F, KP, Rout, part);
+    // R = A^T W: W packed as reduced-precision rows (KP x m)
+    if constexpr (sizeof(T) == 4) {
+      if (pb.Alpt) return lp_product(ctx, pb, false, pb.Alpt, pb.ldat, n, m, F, KP, Rout, part);
+      return lp_product(ctx, pb, true, pb.Alp, pb.lda, n, m, F, KP, Rout, part);
+    }
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
   if constexpr (sizeof(T) == 4) {
@@ -948,7 +949,9 @@ nmf_status dense_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int lp, co
   pb.A = A;
   pb.lda = lda;
   if (lp) {
-    if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo, o->iters > 0)) != NMF_OK) return s;
+    if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo,
+                     o->iters > 0 && !nmfk::gemm_lp_reads_a(n, lda))) != NMF_OK)
+      return s;
   } else if (sizeof(T) == 8 && o->iters > 0 && o->transpose_a == 0) {
     // float products read A in either direction at nearly the same rate
     // (65536^2: 3.2 and 3.3 ms), so a copy (6.5 ms) would pay only after some
@@ -1272,7 +1275,9 @@ nmf_status dense_prod_lp_impl(nmf_ctx* ctx, bool transA, int lp, int64_t m, int6
   float* Op = at<float>(ctx, oO);
   if ((s = pad_any<float>(ctx, F, frows, k, ldf, Fp, KP)) != NMF_OK) return s;
   Prob<float> pb;
-  if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo, transA)) != NMF_OK) return s;
+  if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo,
+                   transA && !nmfk::gemm_lp_reads_a(n, lda))) != NMF_OK)
+    return s;
   s = transA ? product_AtF<float>(ctx, pb, m, n, Fp, nullptr, k, KP, Op, at<float>(ctx, oP))
              : product_AF<float>(ctx, pb, m, n, Fp, nullptr, k, KP, Op, at<float>(ctx, oP));
   if (s != NMF_OK) return s;

@@ -7,10 +7,10 @@
 // most 448 (the E4M3 maximum), the power being multiplied back into that
 // output column.
 //
-// Both products are computed as D (M x N, float) = X (M x K) Y (N x K)^T with
-// X and Y in the reduced format and K contiguous in both: X is A (or its
-// transposed copy) and Y is the packed factor. Each K step covers 128 bytes of
-// a row; lane (g = l / 16, c = l % 16) of a wave reads bytes 32 g .. 32 g + 31
+// Both products are computed as D (M x N, float) = X Y^T with X (M x K) A or
+// its transpose, read in A's own layout, and Y (N x K) the packed factor, K
+// contiguous. A H^T (NT) has K contiguous in X too: each K step covers 128
+// bytes of a row; lane (g = l / 16, c = l % 16) of a wave reads bytes 32 g .. 32 g + 31
 // of that step of row c of each of its row tiles, with two 16-byte loads. For
 // FP8 those 32 values are the operand of v_mfma_scale_f32_16x16x128_f8f6f4
 // (lane l: row l % 16, K values 32 (l / 16) .. + 31). For bfloat16 they feed
@@ -18,11 +18,20 @@
 // 8 (l / 16)): values 0..7 the first, 8..15 the second; the factor operand
 // gets the same K permutation, so the sum is unchanged.
 //
+// A^T W (TN) has the output side contiguous: for the same K values lane (g, c)
+// reads four neighbouring columns of each row, one column for each of its
+// tiles, and regroups the values of four columns from along the row to along K
+// in registers (v_perm_b32: one per two bfloat16 values, one per two FP8
+// values). No transposed copy of A is made: at 24000 x 16400 bfloat16 that
+// copy took 360 of the call's 569 us, and it held as much memory again as A.
+//
 // At rank k the product does k (bfloat16) or 2k (FP8) flops per byte of A,
 // far below the ridge of either format, so the kernel is built to keep HBM
 // busy: A is read once with non-temporal loads, several K steps deep; the
 // factor slice of each K step (N rows x 128 bytes) is loaded once per
 // workgroup into LDS and shared by its four waves.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -72,12 +81,54 @@ constexpr int BWAVES = 4;      // waves per workgroup
 
 template <int MT> struct XFrag { u32x4 v[MT][2]; };
 
+// Four neighbouring elements of a row, at any alignment.
+template <typename TE> struct Run4;
+template <> struct Run4<uint16_t> {
+  typedef unsigned V __attribute__((ext_vector_type(2), aligned(2)));
+};
+template <> struct Run4<uint8_t> {
+  typedef unsigned V __attribute__((aligned(1)));
+};
+
+// The operands of four tiles from runs of four columns: r[q] is row q of the
+// lane's K values (16 rows for bfloat16, 32 for FP8); tile t's operand holds
+// column t along K.
+__device__ __forceinline__ void regroup(const Run4<uint16_t>::V (&r)[16], XFrag<4>& f) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned a = r[8 * h + 2 * i][t >> 1], b = r[8 * h + 2 * i + 1][t >> 1];
+        f.v[t][h][i] = __builtin_amdgcn_perm(b, a, (t & 1) ? 0x07060302u : 0x05040100u);
+      }
+}
+__device__ __forceinline__ void regroup(const Run4<uint8_t>::V (&r)[32], XFrag<4>& f) {
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    // bytes (rows 4 q .. 4 q + 3) x (columns 0 .. 3), transposed
+    const unsigned a = r[4 * q], b = r[4 * q + 1], c = r[4 * q + 2], d = r[4 * q + 3];
+    const unsigned ab0 = __builtin_amdgcn_perm(b, a, 0x05010400u);  // a0 b0 a1 b1
+    const unsigned ab1 = __builtin_amdgcn_perm(b, a, 0x07030602u);  // a2 b2 a3 b3
+    const unsigned cd0 = __builtin_amdgcn_perm(d, c, 0x05010400u);
+    const unsigned cd1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    f.v[0][q >> 2][q & 3] = __builtin_amdgcn_perm(cd0, ab0, 0x05040100u);
+    f.v[1][q >> 2][q & 3] = __builtin_amdgcn_perm(cd0, ab0, 0x07060302u);
+    f.v[2][q >> 2][q & 3] = __builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
+    f.v[3][q >> 2][q & 3] = __builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
+  }
+}
+
 // TE: stored element (uint16_t bfloat16 bits or uint8_t FP8 E4M3 bits).
 // NT 16-column tiles (N = 16 NT), MT 16-row tiles per wave, STAGES K steps of
 // X in registers (STAGES - 1 in flight while one is multiplied), WPE waves per
 // SIMD to leave room for. FP8 outputs: column j is multiplied by colscale[j].
-template <typename TE, int NT, int MT, int STAGES, int WPE>
-__global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
+// TR: X is given as its transpose (K x M, ldx between its rows), M >= 4 and
+// ldx < TN_MAX_LD, so that a lane's offset within a step fits 32 bits.
+constexpr int64_t TN_MAX_LD = (int64_t)1 << 24;
+template <typename TE, int NT, bool TR, int MT, int STAGES, int WPE>
+__global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
     const TE* __restrict__ X, int64_t ldx, const TE* __restrict__ Y, int64_t ldy,
     const float* __restrict__ colscale, float* __restrict__ D, int64_t ldd, int64_t dsplit,
     int64_t M, int64_t K, int64_t kchunk) {
@@ -101,12 +152,23 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
   const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
   D += (int64_t)blockIdx.y * dsplit;
 
-  const TE* xr[MT];
+  // TR: columns col0 .. col0 + 3, moved back where they would pass the last
+  // one (two lanes then hold, and store, the same column)
+  static_assert(!TR || MT == 4, "TN lanes take four columns");
+  typedef typename Run4<TE>::V RunV;
+  const TE* xr[TR ? 1 : MT];
+  uint32_t xo = 0;   // TR: the lane's offset from the (uniform) step rows
+  if constexpr (TR) {
+    int64_t col0 = m0 + 4 * c;
+    col0 = col0 < M - 4 ? col0 : M - 4;
+    xo = (uint32_t)((int64_t)(LE * g) * ldx + col0);
+  } else {
 #pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    int64_t row = m0 + 16 * t + c;
-    row = row < M ? row : M - 1;
-    xr[t] = X + row * ldx + LE * g;
+    for (int t = 0; t < MT; ++t) {
+      int64_t row = m0 + 16 * t + c;
+      row = row < M ? row : M - 1;
+      xr[t] = X + row * ldx + LE * g;
+    }
   }
   // factor staging: thread tid copies chunk (tid % YCH) of rows tid / YCH + YRP p
   const int ych = tid % YCH, yrow0 = tid / YCH;
@@ -118,14 +180,24 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
     for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int64_t nfull = (kend - kbeg) / BK;
-  XFrag<MT> xf[STAGES];
+  // a step's X: the operands (NT), or the runs they are regrouped from (TN)
+  struct Runs { RunV r[LE]; };
+  typedef typename std::conditional<TR, Runs, XFrag<MT>>::type XStep;
+  XStep xf[STAGES];
   u32x4 yv[2][YPASS];  // factor slices of the next two steps, in registers
 
-  auto load_x = [&](XFrag<MT>& f, int64_t k0) {
+  auto load_x = [&](XStep& f, int64_t k0) {
+    if constexpr (TR) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      f.v[t][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0));
-      f.v[t][1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0 + VE));
+      for (int u = 0; u < LE; ++u)
+        f.r[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const RunV*>(X + (k0 + u) * ldx + xo));
+    } else {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        f.v[t][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0));
+        f.v[t][1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0 + VE));
+      }
     }
   };
   auto load_y = [&](u32x4 (&v)[YPASS], int64_t k0) {
@@ -143,7 +215,7 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
       *reinterpret_cast<u32x4*>(&Ys[buf][r * YLD + VE * ych]) = v[p];
     }
   };
-  auto compute = [&](const XFrag<MT>& f, int buf) {
+  auto multiply = [&](const XFrag<MT>& f, int buf) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const TE* yp = &Ys[buf][(16 * j + c) * YLD + LE * g];
@@ -162,6 +234,16 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
                                                               as_bf16x8(b1), acc[t][j], 0, 0, 0);
         }
       }
+    }
+  };
+
+  auto compute = [&](const XStep& x, int buf) {
+    if constexpr (TR) {
+      XFrag<MT> f;
+      regroup(x.r, f);
+      multiply(f, buf);
+    } else {
+      multiply(x, buf);
     }
   };
 
@@ -222,8 +304,10 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
       TE e[LE];
 #pragma unroll
       for (int q = 0; q < LE; ++q) {
-        // xr[t] already points at K offset LE g of its row
-        e[q] = kt + LE * g + q < kend ? xr[t][kt + q] : (TE)0;
+        // xr already points at the lane group's K offset LE g
+        const bool in = kt + LE * g + q < kend;
+        if constexpr (TR) e[q] = in ? X[(kt + q) * ldx + xo + t] : (TE)0;
+        else e[q] = in ? xr[t][kt + q] : (TE)0;
       }
       u32x4 w[2];
       __builtin_memcpy(w, e, sizeof(w));
@@ -235,7 +319,7 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
       Ys[0][r * YLD + kk] = (kt + kk < kend) ? Y[(int64_t)r * ldy + kt + kk] : (TE)0;
     }
     __syncthreads();
-    compute(f, 0);
+    multiply(f, 0);
   }
   // store: element r of tile (t, j) is row 4 g + r, column c
   float cs[NT];
@@ -245,8 +329,13 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_nt_kernel(
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = m0 + 16 * t + 4 * g + r;
-      if (row < M) {
+      int64_t row = TR ? m0 + 4 * (4 * g + r) : m0 + 16 * t + 4 * g + r;
+      bool in = row < M;
+      if constexpr (TR) {
+        row = (row < M - 4 ? row : M - 4) + t;
+        in = m0 < M;
+      }
+      if (in) {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
           D[row * ldd + 16 * j + c] = FP8 ? acc[t][j][r] * cs[j] : acc[t][j][r];
@@ -391,14 +480,16 @@ int64_t gemm_lp_splits(int64_t M, int64_t K) {
   return s;
 }
 
+bool gemm_lp_reads_a(int64_t M, int64_t ldx) { return M >= 4 && ldx < TN_MAX_LD; }
+
 template <typename TE>
-static hipError_t gemm_lp_nt(const TE* X, int64_t ldx, const TE* Y, int64_t ldy,
-                             const float* colscale, float* D, int64_t ldd, int64_t M, int N,
-                             int64_t K, float* part, hipStream_t st) {
+static hipError_t gemm_lp(bool tn, const TE* X, int64_t ldx, const TE* Y, int64_t ldy,
+                          const float* colscale, float* D, int64_t ldd, int64_t M, int N,
+                          int64_t K, float* part, hipStream_t st) {
   constexpr int VE = 16 / (int)sizeof(TE);
   constexpr int BK = SB / (int)sizeof(TE);
   if (M <= 0) return hipSuccess;
-  if (N % 16 != 0 || N < 16 || N > 128 || ldx % VE != 0 || ldy % VE != 0)
+  if (N % 16 != 0 || N < 16 || N > 128 || ldx % VE != 0 || ldy % VE != 0 || (tn && !gemm_lp_reads_a(M, ldx)))
     return hipErrorInvalidValue;
   const int64_t splits = gemm_lp_splits(M, K);
   const int64_t kchunk = round_up(cdiv(K, splits), BK);
@@ -410,8 +501,12 @@ static hipError_t gemm_lp_nt(const TE* X, int64_t ldx, const TE* Y, int64_t ldy,
   const int NT = N / 16;
 #define CASE(J)                                                                            \
   case J:                                                                                  \
-    gemm_lp_nt_kernel<TE, J, B_MT, B_STAGES, B_WPE><<<grid, 64 * BWAVES, 0, st>>>(         \
-        X, ldx, Y, ldy, colscale, out, ldo, dsplit, M, K, kchunk);                         \
+    if (tn)                                                                                \
+      gemm_lp_kernel<TE, J, true, B_MT, B_STAGES, B_WPE><<<grid, 64 * BWAVES, 0, st>>>(    \
+          X, ldx, Y, ldy, colscale, out, ldo, dsplit, M, K, kchunk);                       \
+    else                                                                                   \
+      gemm_lp_kernel<TE, J, false, B_MT, B_STAGES, B_WPE><<<grid, 64 * BWAVES, 0, st>>>(   \
+          X, ldx, Y, ldy, colscale, out, ldo, dsplit, M, K, kchunk);                       \
     break;
   switch (NT) {
     CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
@@ -423,16 +518,17 @@ static hipError_t gemm_lp_nt(const TE* X, int64_t ldx, const TE* Y, int64_t ldy,
   return reduce_splits<float>(part, (int)nsplit, dsplit, M, N, ldd, D, N, st);
 }
 
-hipError_t gemm_bf16_nt(const uint16_t* X, int64_t ldx, const uint16_t* Y, int64_t ldy, float* D,
-                        int64_t ldd, int64_t M, int N, int64_t K, float* part, hipStream_t st) {
-  return gemm_lp_nt<uint16_t>(X, ldx, Y, ldy, nullptr, D, ldd, M, N, K, part, st);
+hipError_t gemm_bf16(bool tn, const uint16_t* X, int64_t ldx, const uint16_t* Y, int64_t ldy,
+                     float* D, int64_t ldd, int64_t M, int N, int64_t K, float* part,
+                     hipStream_t st) {
+  return gemm_lp<uint16_t>(tn, X, ldx, Y, ldy, nullptr, D, ldd, M, N, K, part, st);
 }
 
-hipError_t gemm_fp8_nt(const uint8_t* X, int64_t ldx, const uint8_t* Y, int64_t ldy,
-                       const float* colscale, float* D, int64_t ldd, int64_t M, int N, int64_t K,
-                       float* part, hipStream_t st) {
+hipError_t gemm_fp8(bool tn, const uint8_t* X, int64_t ldx, const uint8_t* Y, int64_t ldy,
+                    const float* colscale, float* D, int64_t ldd, int64_t M, int N, int64_t K,
+                    float* part, hipStream_t st) {
   if (!colscale) return hipErrorInvalidValue;
-  return gemm_lp_nt<uint8_t>(X, ldx, Y, ldy, colscale, D, ldd, M, N, K, part, st);
+  return gemm_lp<uint8_t>(tn, X, ldx, Y, ldy, colscale, D, ldd, M, N, K, part, st);
 }
 
 }  // namespace nmfk
