@@ -511,7 +511,7 @@ nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, con
   }
   if constexpr (sizeof(T) == 4) {
     if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
-    HIP_TRY(nmfk::gemm_split(false, pb.A, pb.lda, Ft, F, KP, KP, Pout, KP, KP, m, KP, n, part,
+    HIP_TRY(nmfk::gemm_split(false, pb.A, pb.lda, Ft, F, KP, KP, k, Pout, KP, KP, m, KP, n, part,
                              ctx->stream, nsplit));
     return NMF_OK;
   } else {
@@ -550,7 +550,7 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
   }
   if constexpr (sizeof(T) == 4) {
     if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
-    HIP_TRY(nmfk::gemm_split(true, pb.A, pb.lda, Ft, F, KP, KP, Rout, KP, KP, n, KP, m, part,
+    HIP_TRY(nmfk::gemm_split(true, pb.A, pb.lda, Ft, F, KP, KP, k, Rout, KP, KP, n, KP, m, part,
                              ctx->stream, nsplit));
     return NMF_OK;
   } else {
@@ -1222,7 +1222,7 @@ nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, cons
   float* Fp = at<float>(ctx, oFp);
   // the planes from the caller's F, the product straight into the caller's P
   HIP_TRY(nmfk::pack_split(F, frows, ldf, k, KP, Fp, ctx->stream));
-  HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, Out, k, k, orows, KP, frows,
+  HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, k, Out, k, k, orows, KP, frows,
                            at<float>(ctx, oP), ctx->stream));
   return NMF_OK;
 }

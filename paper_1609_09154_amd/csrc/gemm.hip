@@ -34,7 +34,6 @@
 
 namespace nmfk {
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // loads of rows whose pitch is any number of floats: 4-byte alignment
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
@@ -51,11 +50,17 @@ template <bool STREAM, typename V> __device__ __forceinline__ V load_a(const V* 
 // and tile.
 template <int MT> struct XStep { float v[MT][8]; };
 
-template <int NT, bool TR, int MT, int STAGES, int WPE, int FLUSH, bool STREAM>
+// REM: the last of the NT tiles holds only nrem <= 5 rank columns. Its operand
+// then takes the three planes of those columns side by side (column 16 (NT - 1)
+// + c % nrem, plane c / nrem in lane column c), so that one product with each
+// plane of X gives all of the six terms (and three smaller ones): three
+// instructions instead of six, and the planes' sums are added at the end.
+template <int NT, bool TR, int MT, int STAGES, int WPE, int FLUSH, bool STREAM, bool REM>
 __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
     const float* __restrict__ X, int64_t ldx, const u32x4* __restrict__ Fp,
     const float* __restrict__ F, int64_t ldf, int kv, float* __restrict__ D, int64_t ldd,
-    int64_t dsplit, int nout, int64_t M, int64_t K, int64_t kchunk) {
+    int64_t dsplit, int nout, int nrem, int64_t M, int64_t K, int64_t kchunk) {
+  constexpr int NF = REM ? NT - 1 : NT;    // tiles of six terms
   constexpr int NR = 16 * NT;              // factor columns
   constexpr int CH = 12 * NR;              // 16-byte chunks of a step's factor slice
   constexpr int PASS = (CH + 64 * SPW - 1) / (64 * SPW);
@@ -98,9 +103,13 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
       acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (FLUSH) tot[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-  u16x2 mx[MT];   // largest |h| of each lane's row or column of X, as bits
+  unsigned mx[MT];   // the bits of h of each lane's row or column of X, ored
 #pragma unroll
-  for (int t = 0; t < MT; ++t) mx[t] = u16x2{0, 0};
+  for (int t = 0; t < MT; ++t) mx[t] = 0;
+
+  // REM: the lane's chunk of the last tile within a lane group's chunks
+  int remo = 0;
+  if constexpr (REM) remo = c < 3 * nrem ? (c / nrem) * NR + 16 * NF + c % nrem : 16 * NF;
 
   XStep<MT> xf[STAGES];
   u32x4 yv[PASS];   // factor slice of the next step   // factor slices of the next two steps
@@ -148,25 +157,26 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
     Split8 a[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        unsigned h, m, l;
-        split2(f.v[t][2 * i], f.v[t][2 * i + 1], h, m, l);
-        a[t].h[i] = h;
-        a[t].m[i] = m;
-        a[t].l[i] = l;
-        mx[t] = __builtin_elementwise_max(mx[t], __builtin_bit_cast(u16x2, h));
-      }
+    {
+      a[t] = split8(f.v[t]);
+      mx[t] |= a[t].h[0] | a[t].h[1];
+      mx[t] |= a[t].h[2] | a[t].h[3];
+    }
     const u32x4* fb = &Fs[buf][3 * NR * g + c];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
+    for (int j = 0; j < NF; ++j) {
       const u32x4 bh = fb[16 * j], bm = fb[NR + 16 * j], bl = fb[2 * NR + 16 * j];
 #define TERM(PA, PB)                                             \
   _Pragma("unroll") for (int t = 0; t < MT; ++t)                 \
       acc[t][j] = mfma_bf16(a[t].PA, PB, acc[t][j]);
       TERM(l, bh) TERM(h, bl) TERM(m, bm) TERM(m, bh) TERM(h, bm) TERM(h, bh)
-#undef TERM
     }
+    if constexpr (REM) {
+      constexpr int j = NF;
+      const u32x4 br = Fs[buf][3 * NR * g + remo];
+      TERM(l, br) TERM(m, br) TERM(h, br)
+    }
+#undef TERM
   };
   auto flush = [&]() {
 #pragma unroll
@@ -252,6 +262,17 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
         for (int r = 0; r < 4; ++r) acc[t][j][r] += tot[t][j][r];
   }
 
+  if constexpr (REM) {
+    // lanes c < nrem: the sums with planes l, m and h of column c
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float v = acc[t][NF][r];
+        const float vm = __shfl(v, lane + nrem, 64), vl = __shfl(v, lane + 2 * nrem, 64);
+        acc[t][NF][r] = c < nrem ? (vl + vm) + v : 0.f;
+      }
+  }
   // Where the split does not hold (an entry that is not finite or rounds to
   // infinity as bfloat16, or a row so small that its last bits fall below the
   // smallest bfloat16) the wave computes its tiles again with the float
@@ -259,10 +280,11 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
   bool redo = false;
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
-    unsigned w = max((unsigned)mx[t][0], (unsigned)mx[t][1]);
-    w = max(w, (unsigned)__shfl_xor((int)w, 16, 64));
-    w = max(w, (unsigned)__shfl_xor((int)w, 32, 64));
-    redo = redo || (w > 0 && w < 0x0d80u);   // 2^-100
+    unsigned w = (mx[t] | mx[t] >> 16) & 0x7fffu;
+    w |= (unsigned)__shfl_xor((int)w, 16, 64);
+    w |= (unsigned)__shfl_xor((int)w, 32, 64);
+    // every exponent field below 32: every |h| below 2^-95
+    redo = redo || (w > 0 && w < (32u << 7));
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -392,14 +414,15 @@ int64_t gemm_split_splits(int64_t M, int KP, int64_t K) {
 
 struct SplitCall {
   const float* X; int64_t ldx; const u32x4* Fp; const float* F; int64_t ldf; int kv;
-  float* D; int64_t ldd, dsplit; int nout; int64_t M, K, kchunk, splits;
+  float* D; int64_t ldd, dsplit; int nout, nrem; int64_t M, K, kchunk, splits;
 };
 
-template <int NT, bool TR, int MT, int FLUSH, bool STREAM>
+template <int NT, bool TR, int MT, int FLUSH, bool STREAM, bool REM = false>
 static void split_launch(const SplitCall& a, hipStream_t st) {
   dim3 grid((unsigned)cdiv(a.M, 16 * MT * SPW), (unsigned)a.splits);
-  gemm_split_kernel<NT, TR, MT, 2, 2, FLUSH, STREAM><<<grid, 64 * SPW, 0, st>>>(
-      a.X, a.ldx, a.Fp, a.F, a.ldf, a.kv, a.D, a.ldd, a.dsplit, a.nout, a.M, a.K, a.kchunk);
+  gemm_split_kernel<NT, TR, MT, 2, 2, FLUSH, STREAM, REM><<<grid, 64 * SPW, 0, st>>>(
+      a.X, a.ldx, a.Fp, a.F, a.ldf, a.kv, a.D, a.ldd, a.dsplit, a.nout, a.nrem, a.M, a.K,
+      a.kchunk);
 }
 
 // STREAM (non-temporal loads of A): only where A is larger than the 256 MB
@@ -412,6 +435,13 @@ static void split_dispatch(bool tn, const SplitCall& a, hipStream_t st) {
   const bool stream = a.M * a.K > ((int64_t)1 << 26);
   if constexpr (NT <= 4) {
     if (split_wide(a.M, NT, a.K)) {
+      if constexpr (NT >= 2) {
+        if (a.nrem > 0 && a.nrem <= 5) {
+          if (tn) split_launch<NT, true, 4, 0, true, true>(a, st);
+          else split_launch<NT, false, 4, 0, false, true>(a, st);
+          return;
+        }
+      }
       if (tn) split_launch<NT, true, 4, 0, true>(a, st);
       else split_launch<NT, false, 4, 0, false>(a, st);
       return;
@@ -423,9 +453,9 @@ static void split_dispatch(bool tn, const SplitCall& a, hipStream_t st) {
 }
 
 hipError_t gemm_split(bool tn, const float* X, int64_t ldx, const float* Fp, const float* F,
-                      int64_t ldf, int kv, float* D, int64_t ldd, int nout, int64_t M, int KP,
-                      int64_t K, float* part, hipStream_t st, int* nsplit) {
-  if (KP < 16 || KP > 128 || KP % 16 || kv < 1 || kv > KP || nout < 1 || nout > KP || M < 1 || K < 1)
+                      int64_t ldf, int kv, int k, float* D, int64_t ldd, int nout, int64_t M,
+                      int KP, int64_t K, float* part, hipStream_t st, int* nsplit) {
+  if (KP < 16 || KP > 128 || KP % 16 || kv < 1 || kv > KP || k < 1 || k > kv || nout < 1 || nout > KP || M < 1 || K < 1)
     return hipErrorInvalidValue;
   if (ldx < (tn ? M : K) || ldf < kv || ldd < nout || (uintptr_t)Fp % 16) return hipErrorInvalidValue;
   int64_t splits = gemm_split_splits(M, KP, K);
@@ -433,7 +463,8 @@ hipError_t gemm_split(bool tn, const float* X, int64_t ldx, const float* Fp, con
   splits = cdiv(K, kchunk);
   const bool slabs = splits > 1;
   const SplitCall a{X, ldx, reinterpret_cast<const u32x4*>(Fp), F, ldf, kv, slabs ? part : D,
-                    slabs ? KP : ldd, M * KP, slabs ? KP : nout, M, K, kchunk, splits};
+                    slabs ? KP : ldd, M * KP, slabs ? KP : nout, k > KP - 16 ? k - (KP - 16) : 0, M, K,
+                    kchunk, splits};
   if (tn && M == 1) {
     column_product_kernel<<<dim3(1, (unsigned)splits), 256, 0, st>>>(
         X, ldx, F, ldf, kv, a.D, a.dsplit, KP, a.nout, K, kchunk);

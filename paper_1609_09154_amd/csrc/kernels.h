@@ -57,12 +57,13 @@ hipError_t reduce_splits(const T* part, int splits, int64_t dsplit, int64_t M, i
 // Float products at any rank up to 128: D (M x nout, ld ldd) = X F (X M x K)
 // or, tn, X^T F (X K x M) for float X of any pitch ldx and F (K x kv, pitch
 // ldf, given as Fp, its packed planes for KP >= kv columns; F itself is read
-// only where the split does not hold). Columns kv..nout-1 are zero. `part`
+// only where the split does not hold). Columns k..kv-1 of F are zero, so are
+// columns k..nout-1 of D. `part`
 // must hold gemm_split_splits(M, KP, K) * M * KP floats when that count
 // exceeds 1; nsplit as for gemm_run (the slabs then have KP columns).
 hipError_t gemm_split(bool tn, const float* X, int64_t ldx, const float* Fp, const float* F,
-                      int64_t ldf, int kv, float* D, int64_t ldd, int nout, int64_t M, int KP,
-                      int64_t K, float* part, hipStream_t st, int* nsplit = nullptr);
+                      int64_t ldf, int kv, int k, float* D, int64_t ldd, int nout, int64_t M,
+                      int KP, int64_t K, float* part, hipStream_t st, int* nsplit = nullptr);
 int64_t gemm_split_splits(int64_t M, int KP, int64_t K);
 // Fp = the packed planes of F (rows x kv, pitch ldf) for KP columns; Fp is
 // 16-byte aligned and holds split_floats(rows, KP) floats.
