@@ -1174,38 +1174,59 @@ nmf_status nmf_csr(nmf_ctx* ctx, int64_t m, int64_t n, int64_t nnz, const int64_
 // ---- per-step entry points ------------------------------------------------
 
 namespace {
-template <typename T>
-nmf_status gram_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, int64_t ldx, T* G) {
-  const int KP = kp_dense(k);
-  Carve cv;
-  const size_t oX = cv.take<T>(rows * KP);
-  const size_t oG = cv.take<T>(KP * KP);
-  const size_t oP = cv.take<T>(gram_splits(rows) * KP * KP);
-  nmf_status s = ensure_ws(ctx, cv.off);
-  if (s != NMF_OK) return s;
-  T* Xp = at<T>(ctx, oX);
-  T* Gp = at<T>(ctx, oG);
-  hipStream_t st = ctx->stream;
-  if (ldx == k) HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, st));
-  else {
-    HIP_TRY(hipMemsetAsync(Xp, 0, sizeof(T) * rows * KP, st));
-    HIP_TRY(hipMemcpy2DAsync(Xp, KP * sizeof(T), X, ldx * sizeof(T), k * sizeof(T), rows,
-                             hipMemcpyDeviceToDevice, st));
+// Whether the kernels can read (and update) the caller's rows x k array in
+// place: the rank fills its padding and the rows are 16-byte aligned.
+template <typename T> bool in_place(const T* X, int k, int64_t ldx) {
+  return kp_dense(k) == k && ldx == k && (uintptr_t)X % 16 == 0;
+}
+// One launch's copies of the caller's arrays into the padded layout and back.
+template <typename T> struct Copies {
+  nmfk::CopyJob<T> j[nmfk::MAX_COPY_JOBS];
+  int n = 0;
+  void pad(const T* src, int64_t rows, int k, int64_t ld, T* dst, int KP, int64_t prow) {
+    j[n++] = nmfk::CopyJob<T>{src, dst, rows, prow, k, KP, ld};
   }
-  if ((s = gram<T>(ctx, Xp, rows, KP, Gp, at<T>(ctx, oP))) != NMF_OK) return s;
-  HIP_TRY(nmfk::unpad_rows<T>(Gp, k, k, KP, G, st));
+  void unpad(const T* src, int64_t rows, int k, int KP, T* dst) {
+    j[n++] = nmfk::CopyJob<T>{src, dst, rows, rows, k, KP, k};
+  }
+};
+
+// G (k x k, pitch k) = X^T X for the padded X, the split sums written to G
+// directly.
+template <typename T>
+nmf_status gram_out(nmf_ctx* ctx, const T* X, int64_t rows, int k, int KP, T* G, T* part) {
+  nmfk::GemmArgs<T> a{X, KP, X, KP, part, KP, KP, KP, rows, false, nullptr};
+  int ns = 1;
+  HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN_GRAM, a, gram_splits(rows), part, ctx->stream,
+                            &ns));
+  HIP_TRY(nmfk::reduce_splits<T>(part, ns, (int64_t)KP * KP, k, k, k, G, KP, ctx->stream));
   return NMF_OK;
 }
 
 template <typename T>
-nmf_status pad_any(nmf_ctx* ctx, const T* X, int64_t rows, int k, int64_t ldx, T* Xp, int KP) {
-  hipStream_t st = ctx->stream;
-  if (ldx == k) HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, st));
-  else {
-    HIP_TRY(hipMemsetAsync(Xp, 0, sizeof(T) * rows * KP, st));
-    HIP_TRY(hipMemcpy2DAsync(Xp, KP * sizeof(T), X, ldx * sizeof(T), k * sizeof(T), rows,
-                             hipMemcpyDeviceToDevice, st));
+nmf_status gram_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, int64_t ldx, T* G) {
+  const int KP = kp_dense(k);
+  const bool direct = in_place(X, k, ldx);
+  Carve cv;
+  const size_t oX = cv.take<T>(direct ? 0 : rows * KP);
+  const size_t oP = cv.take<T>(gram_splits(rows) * KP * KP);
+  nmf_status s = ensure_ws(ctx, cv.off);
+  if (s != NMF_OK) return s;
+  const T* Xp = X;
+  if (!direct) {
+    Copies<T> c;
+    c.pad(X, rows, k, ldx, at<T>(ctx, oX), KP, rows);
+    HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
+    Xp = at<T>(ctx, oX);
   }
+  return gram_out<T>(ctx, Xp, rows, k, KP, G, at<T>(ctx, oP));
+}
+
+template <typename T>
+nmf_status pad_any(nmf_ctx* ctx, const T* X, int64_t rows, int k, int64_t ldx, T* Xp, int KP) {
+  Copies<T> c;
+  c.pad(X, rows, k, ldx, Xp, KP, rows);
+  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
   return NMF_OK;
 }
 
@@ -1232,29 +1253,32 @@ nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, cons
   typedef double T;
   const int KP = kp_dense(k);
   const int64_t frows = transA ? m : n, orows = transA ? n : m;
-  const int64_t splits = transA ? nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, n, KP, m)
-                                : nmfk::gemm_auto_splits<T>(nmfk::GemmKind::NN, m, KP, n);
+  const nmfk::GemmKind kind = transA ? nmfk::GemmKind::TN : nmfk::GemmKind::NN;
+  const int64_t splits = nmfk::gemm_auto_splits<T>(kind, orows, KP, frows);
+  const bool direct = in_place(F, k, ldf);
+  // The transposed copy is read with 16-byte loads: rows must stay aligned.
+  // As in the iteration, a small A does not repay its launch.
+  const bool use_t = m * n >= ((int64_t)1 << 22) && (frows * (int64_t)sizeof(T)) % 16 == 0;
   Carve cv;
-  const size_t oF = cv.take<T>(frows * KP);
-  const size_t oFt = cv.take<T>(frows * KP);
-  const size_t oO = cv.take<T>(orows * KP);
-  const size_t oP = cv.take<T>(splits > 1 ? splits * orows * KP : 1);
+  const size_t oF = cv.take<T>(direct ? 0 : frows * KP);
+  const size_t oFt = cv.take<T>(use_t ? frows * KP : 0);
+  const size_t oP = cv.take<T>(splits * orows * KP);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
-  T* Fp = at<T>(ctx, oF);
+  const T* Fp = F;
+  if (!direct) {
+    if ((s = pad_any<T>(ctx, F, frows, k, ldf, at<T>(ctx, oF), KP)) != NMF_OK) return s;
+    Fp = at<T>(ctx, oF);
+  }
   T* Ft = at<T>(ctx, oFt);
-  T* Op = at<T>(ctx, oO);
-  if ((s = pad_any<T>(ctx, F, frows, k, ldf, Fp, KP)) != NMF_OK) return s;
-  // The transposed copy is read with 16-byte loads: rows must stay aligned.
-  const bool use_t = (frows * (int64_t)sizeof(T)) % 16 == 0;
+  T* part = at<T>(ctx, oP);
   if (use_t) HIP_TRY(nmfk::transpose_rows<T>(Fp, frows, KP, Ft, ctx->stream));
-  Prob<T> pb;
-  pb.A = A;
-  pb.lda = lda;
-  s = transA ? product_AtF<T>(ctx, pb, m, n, Fp, use_t ? Ft : nullptr, k, KP, Op, at<T>(ctx, oP))
-             : product_AF<T>(ctx, pb, m, n, Fp, use_t ? Ft : nullptr, k, KP, Op, at<T>(ctx, oP));
-  if (s != NMF_OK) return s;
-  HIP_TRY(nmfk::unpad_rows<T>(Op, orows, k, KP, Out, ctx->stream));
+  nmfk::GemmArgs<T> a{A, lda, use_t ? Ft : Fp, use_t ? frows : (int64_t)KP, part, KP, orows, KP,
+                      frows, use_t};
+  int ns = 1;
+  HIP_TRY(nmfk::gemm_run<T>(kind, a, 0, part, ctx->stream, &ns));
+  // the slabs' sum (of one, a copy) goes to the caller's array
+  HIP_TRY(nmfk::reduce_splits<T>(part, ns, orows * KP, orows, k, k, Out, KP, ctx->stream));
   return NMF_OK;
 }
 
@@ -1289,32 +1313,37 @@ template <typename T>
 nmf_status update_impl(nmf_ctx* ctx, int algo, int64_t rows, int k, const T* G, const T* Pm,
                        T* X, const nmf_opts* o, long long* pivots) {
   const int KP = kp_dense(k);
+  const bool direct = in_place(G, k, k) && in_place(Pm, k, k) && in_place(X, k, k);
   Carve cv;
-  const size_t oG = cv.take<T>(KP * KP);
-  const size_t oP = cv.take<T>(rows * KP);
-  const size_t oX = cv.take<T>(rows * KP);
+  const size_t oG = cv.take<T>(direct ? 0 : KP * KP);
+  const size_t oP = cv.take<T>(direct ? 0 : rows * KP);
+  const size_t oX = cv.take<T>(direct ? 0 : rows * KP);
   const size_t oS = cv.take<int>(4);
   const size_t oV = cv.take<unsigned long long>(nmfk::BPP_TALLIES);
   const size_t oI = cv.take<double>(KP * KP);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
-  T* Gp = at<T>(ctx, oG);
-  T* Pp = at<T>(ctx, oP);
-  T* Xp = at<T>(ctx, oX);
   int* dst = at<int>(ctx, oS);
   unsigned long long* dpv = at<unsigned long long>(ctx, oV);
   hipStream_t st = ctx->stream;
-  HIP_TRY(hipMemsetAsync(dst, 0, 4 * sizeof(int), st));
-  HIP_TRY(hipMemsetAsync(dpv, 0, nmfk::BPP_TALLIES * sizeof(unsigned long long), st));
-  HIP_TRY(nmfk::pad_rows<T>(G, k, k, Gp, KP, st));
-  if (KP > k) HIP_TRY(hipMemsetAsync(Gp + (size_t)k * KP, 0, sizeof(T) * (KP - k) * KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(Pm, rows, k, Pp, KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, st));
+  // status and tallies: the words from one slice to the next
+  if (algo == NMF_ABPP) HIP_TRY(hipMemsetAsync(dst, 0, oI - oS, st));
+  const T *Gp = G, *Pp = Pm;
+  T* Xp = X;
+  if (!direct) {
+    Copies<T> c;
+    c.pad(G, k, k, k, at<T>(ctx, oG), KP, KP);
+    c.pad(Pm, rows, k, k, at<T>(ctx, oP), KP, rows);
+    c.pad(X, rows, k, k, at<T>(ctx, oX), KP, rows);
+    HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, st));
+    Gp = at<T>(ctx, oG);
+    Pp = at<T>(ctx, oP);
+    Xp = at<T>(ctx, oX);
+  }
   if ((s = local_update<T>(ctx, algo, Xp, nmfk::Split<T>{Pp, 1, 0}, Gp, rows, k, KP, o, dst, dpv,
-                          at<double>(ctx, oI))) !=
-      NMF_OK)
+                           at<double>(ctx, oI))) != NMF_OK)
     return s;
-  HIP_TRY(nmfk::unpad_rows<T>(Xp, rows, k, KP, X, st));
+  if (!direct) HIP_TRY(nmfk::unpad_rows<T>(Xp, rows, k, KP, X, st));
   if (algo == NMF_ABPP) return read_status(ctx, dst, dpv, pivots);
   return NMF_OK;
 }
@@ -1354,14 +1383,11 @@ nmf_status update_noalloc_impl(nmf_ctx* ctx, int algo, int64_t rows, int k, cons
   const int64_t nz = (int64_t)(pl.oI - pl.oS) / 4;
   zero_words_kernel<<<(unsigned)cdiv(nz, 256), 256, 0, st>>>((uint32_t*)dst, nz);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(nmfk::pad_rows<T>(G, k, k, Gp, KP, st));
-  if (KP > k) {
-    const int64_t nw = (int64_t)(KP - k) * KP * (int64_t)sizeof(T) / 4;
-    zero_words_kernel<<<(unsigned)cdiv(nw, 256), 256, 0, st>>>((uint32_t*)(Gp + (size_t)k * KP), nw);
-    HIP_TRY(hipGetLastError());
-  }
-  HIP_TRY(nmfk::pad_rows<T>(Pm, rows, k, Pp, KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, st));
+  Copies<T> c;
+  c.pad(G, k, k, k, Gp, KP, KP);
+  c.pad(Pm, rows, k, k, Pp, KP, rows);
+  c.pad(X, rows, k, k, Xp, KP, rows);
+  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, st));
   nmf_status s = local_update<T>(ctx, algo, Xp, nmfk::Split<T>{Pp, 1, 0}, Gp, rows, k, KP, o,
                                  dst, dpv,
                                  (double*)(base + pl.oI));
@@ -1375,27 +1401,37 @@ template <typename T>
 nmf_status normalize_impl(nmf_ctx* ctx, int64_t m, int64_t n, int k, T* W, T* Ht, T* S,
                           T* norms) {
   const int KP = kp_dense(k);
+  const bool direct = in_place(W, k, k) && in_place(Ht, k, k);
   Carve cv;
-  const size_t oW = cv.take<T>(m * KP);
-  const size_t oH = cv.take<T>(n * KP);
+  const size_t oW = cv.take<T>(direct ? 0 : m * KP);
+  const size_t oH = cv.take<T>(direct ? 0 : n * KP);
   const size_t oS = cv.take<T>(KP * KP);
   const size_t oN = cv.take<T>(KP);
   const size_t oP = cv.take<T>(gram_splits(m) * KP * KP);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
-  T* Wp = at<T>(ctx, oW);
-  T* Hp = at<T>(ctx, oH);
+  T *Wp = W, *Hp = Ht;
   T* Sp = at<T>(ctx, oS);
   T* Np = at<T>(ctx, oN);
   hipStream_t st = ctx->stream;
-  HIP_TRY(nmfk::pad_rows<T>(W, m, k, Wp, KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(Ht, n, k, Hp, KP, st));
+  if (!direct) {
+    Wp = at<T>(ctx, oW);
+    Hp = at<T>(ctx, oH);
+    Copies<T> c;
+    c.pad(W, m, k, k, Wp, KP, m);
+    c.pad(Ht, n, k, k, Hp, KP, n);
+    HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, st));
+  }
   if ((s = gram<T>(ctx, Wp, m, KP, Sp, at<T>(ctx, oP))) != NMF_OK) return s;
   HIP_TRY(nmfk::hals_normalize<T>(Wp, Wp, m, Hp, Hp, n, Sp, Np, k, KP, st));
-  HIP_TRY(nmfk::unpad_rows<T>(Wp, m, k, KP, W, st));
-  HIP_TRY(nmfk::unpad_rows<T>(Hp, n, k, KP, Ht, st));
-  if (S) HIP_TRY(nmfk::unpad_rows<T>(Sp, k, k, KP, S, st));
-  if (norms) HIP_TRY(hipMemcpyAsync(norms, Np, sizeof(T) * k, hipMemcpyDeviceToDevice, st));
+  Copies<T> c;
+  if (!direct) {
+    c.unpad(Wp, m, k, KP, W);
+    c.unpad(Hp, n, k, KP, Ht);
+  }
+  if (S) c.unpad(Sp, k, k, KP, S);
+  if (norms) c.unpad(Np, 1, k, KP, norms);
+  if (c.n) HIP_TRY(nmfk::unpad_jobs<T>(c.j, c.n, st));
   return NMF_OK;
 }
 
@@ -1411,8 +1447,10 @@ nmf_status relerr_impl(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, in
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
   Work<T> w = bind_work<T>(ctx, off, obj_np);
-  HIP_TRY(nmfk::pad_rows<T>(W, m, k, w.W, KP, ctx->stream));
-  HIP_TRY(nmfk::pad_rows<T>(Ht, n, k, w.Ht, KP, ctx->stream));
+  Copies<T> c;
+  c.pad(W, m, k, k, w.W, KP, m);
+  c.pad(Ht, n, k, k, w.Ht, KP, n);
+  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
   if ((s = objective<T>(ctx, pb, m, n, KP, w, 0, true)) != NMF_OK) return s;
   HIP_TRY(hipMemcpyAsync(out, w.relerr, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -2244,10 +2282,11 @@ nmf_status pgrad_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, const T* Pm
   T* Xp = at<T>(ctx, oX);
   T* Pp = at<T>(ctx, oP);
   T* Gp = at<T>(ctx, oG);
-  HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(Pm, rows, k, Pp, KP, st));
-  HIP_TRY(nmfk::pad_rows<T>(G, k, k, Gp, KP, st));
-  if (KP > k) HIP_TRY(hipMemsetAsync(Gp + (size_t)k * KP, 0, sizeof(T) * (KP - k) * KP, st));
+  Copies<T> c;
+  c.pad(X, rows, k, k, Xp, KP, rows);
+  c.pad(Pm, rows, k, k, Pp, KP, rows);
+  c.pad(G, k, k, k, Gp, KP, KP);
+  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, st));
   HIP_TRY(nmfk::pgrad_sq<T>(Xp, Pp, Gp, rows, k, KP, at<double>(ctx, oq), st));
   HIP_TRY(nmfk::finish_relerr<T>(at<double>(ctx, oq), nullptr, nmfk::pgrad_blocks<T>(rows, KP),
                                  (const T*)nullptr, (const T*)nullptr, 0, nullptr,

@@ -144,6 +144,22 @@ template <typename T>
 hipError_t pad_rows(const T* src, int64_t rows, int k, T* dst, int KP, hipStream_t st);
 template <typename T>
 hipError_t unpad_rows(const T* src, int64_t rows, int k, int KP, T* dst, hipStream_t st);
+// The same for several matrices in one launch. A job copies a rows x cols
+// matrix of pitch ld into prow x KP (pad_jobs; zero past rows and cols), or
+// the leading rows x cols of a matrix of pitch KP into one of pitch ld
+// (unpad_jobs).
+template <typename T> struct CopyJob {
+  const T* src;
+  T* dst;
+  int64_t rows, prow;
+  int cols, KP;
+  int64_t ld;
+};
+constexpr int MAX_COPY_JOBS = 4;
+template <typename T>
+hipError_t pad_jobs(const CopyJob<T>* jobs, int n, hipStream_t st);
+template <typename T>
+hipError_t unpad_jobs(const CopyJob<T>* jobs, int n, hipStream_t st);
 // At (n x m, row pitch ldt >= m) = A^T for A (m x n, lda). T is float,
 // double, uint16_t (bfloat16 bits) or uint8_t (FP8 bits).
 template <typename T>

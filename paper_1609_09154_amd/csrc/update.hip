@@ -412,6 +412,57 @@ __global__ void unpad_rows_kernel(const T* __restrict__ src, int64_t rows, int k
   }
 }
 
+// Several copies in one launch: a per-step call on a small matrix is the
+// latency of its launches (some 3 us each on the stream).
+template <typename T> struct CopyJobs {
+  CopyJob<T> j[MAX_COPY_JOBS];
+  int64_t end[MAX_COPY_JOBS];   // elements up to and with each job
+  int n;
+};
+template <typename T, bool PAD>
+__global__ void copy_jobs_kernel(const CopyJobs<T> a) {
+  const int64_t total = a.end[a.n - 1], stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
+    int q = 0;
+    while (e >= a.end[q]) ++q;
+    const CopyJob<T>& c = a.j[q];
+    const int64_t x = e - (q ? a.end[q - 1] : 0);
+    if constexpr (PAD) {
+      const int64_t r = x / c.KP;
+      const int i = (int)(x - r * c.KP);
+      c.dst[x] = r < c.rows && i < c.cols ? c.src[r * c.ld + i] : T(0);
+    } else {
+      const int64_t r = x / c.cols;
+      const int i = (int)(x - r * c.cols);
+      c.dst[r * c.ld + i] = c.src[r * c.KP + i];
+    }
+  }
+}
+
+template <typename T, bool PAD>
+static hipError_t copy_jobs(const CopyJob<T>* jobs, int n, hipStream_t st) {
+  if (n < 1 || n > MAX_COPY_JOBS) return hipErrorInvalidValue;
+  CopyJobs<T> a;
+  int64_t at = 0;
+  for (int q = 0; q < n; ++q) {
+    a.j[q] = jobs[q];
+    at += PAD ? jobs[q].prow * jobs[q].KP : jobs[q].rows * jobs[q].cols;
+    a.end[q] = at;
+  }
+  a.n = n;
+  if (at == 0) return hipSuccess;
+  copy_jobs_kernel<T, PAD><<<capped_grid(cdiv(at, 256)), 256, 0, st>>>(a);
+  return NMF_LAUNCH_CHECK();
+}
+template <typename T>
+hipError_t pad_jobs(const CopyJob<T>* jobs, int n, hipStream_t st) {
+  return copy_jobs<T, true>(jobs, n, st);
+}
+template <typename T>
+hipError_t unpad_jobs(const CopyJob<T>* jobs, int n, hipStream_t st) {
+  return copy_jobs<T, false>(jobs, n, st);
+}
+
 // Ht[j][i] = H[i][j] (i < k), 0 for k <= i < KP. Tiled through LDS.
 template <typename T>
 __global__ void transpose_in_kernel(const T* __restrict__ H, int k, int64_t n,
@@ -618,6 +669,8 @@ hipError_t transpose_out(const T* Ht, int k, int64_t n, int KP, T* H, hipStream_
   template hipError_t hals_normalize<T>(const T*, T*, int64_t, const T*, T*, int64_t, T*, T*, \
                                         int, int, hipStream_t, T*);                         \
   template hipError_t pad_rows<T>(const T*, int64_t, int, T*, int, hipStream_t);            \
+  template hipError_t pad_jobs<T>(const CopyJob<T>*, int, hipStream_t);                     \
+  template hipError_t unpad_jobs<T>(const CopyJob<T>*, int, hipStream_t);                   \
   template hipError_t unpad_rows<T>(const T*, int64_t, int, int, T*, hipStream_t);          \
   template hipError_t transpose_in<T>(const T*, int, int64_t, T*, int, hipStream_t);        \
   template hipError_t transpose_out<T>(const T*, int, int64_t, int, T*, hipStream_t);         \
