@@ -163,33 +163,29 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
     }
   }
   double sr = 0.0, sa = 0.0;
-  float wv[KS][8];
-  A4<TA> av[4];
-  auto load_w = [&](int64_t row0) {
+  // PF tiles in flight (one wave per SIMD has the registers for two)
+  constexpr int PF = KS <= 2 ? 1 : 2;
+  float wv[PF][KS][8];
+  A4<TA> av[PF][4];
+  auto load_tile = [&](int p, int64_t row0) {
+    if (row0 >= rend) return;
     const int64_t row = row0 + c < m ? row0 + c : m - 1;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) load8(wv[s], W + row * KP, s);
+    for (int s = 0; s < KS; ++s) load8(wv[p][s], W + row * KP, s);
+    load_a_tile<float>(av[p], A, lda, m, n, row0, col, full, lane);
   };
-  int64_t row0 = rbeg + 16 * wave;
-  if (row0 < rend) {
-    load_w(row0);
-    load_a_tile<float>(av, A, lda, m, n, row0, col, full, lane);
-  }
-  for (; row0 < rend; row0 += 16 * RWAVES) {
+  auto tile = [&](int p, int64_t row0) {
+    if (row0 >= rend) return;
     f32x4 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
     Split8 ws[KS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ws[s] = split8(wv[s]);
+    for (int s = 0; s < KS; ++s) ws[s] = split8(wv[p][s]);
     A4<TA> cur[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) cur[r] = av[r];
-    const int64_t next = row0 + 16 * RWAVES;
-    if (next < rend) {
-      load_w(next);
-      load_a_tile<float>(av, A, lda, m, n, next, col, full, lane);
-    }
+    for (int r = 0; r < 4; ++r) cur[r] = av[p][r];
+    load_tile(p, row0 + PF * 16 * RWAVES);
 #pragma unroll
     for (int s = 0; s < KS; ++s) split_mma(ws[s], hp[s], acc);
     // products of entries that are not finite: again with the float instruction
@@ -209,6 +205,13 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
                           Ht[(col + j < n ? col + j : n - 1) * KP + k0 + g], acc[j]);
     }
     add_tile<NORM, float>(cur, acc, m, n, row0, col, lane, sr, sa);
+  };
+  const int64_t first = rbeg + 16 * wave;
+#pragma unroll
+  for (int p = 0; p < PF; ++p) load_tile(p, first + p * 16 * RWAVES);
+  for (int64_t row0 = first; row0 < rend; row0 += PF * 16 * RWAVES) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) tile(p, row0 + p * 16 * RWAVES);
   }
   const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   const double s = block_sum(sr);
@@ -279,10 +282,11 @@ __global__ __launch_bounds__(64 * RWAVES, 2) void residual_f64_kernel(
   }
 }
 
-// Rows per block: about 2048 blocks (eight per CU: enough to even out the
-// last wave of blocks), at least one tile per wave.
+// Rows per block: about 1024 blocks (512 and 2048 measured within 5% up to
+// 8192^2; fewer cost 25% at 100003 x 5003), at least one tile per wave.
+constexpr int RBLOCKS = 1024;
 static int64_t residual_rows(int64_t m, int64_t n) {
-  const int64_t want = cdiv(2048, cdiv(n, RC));
+  const int64_t want = cdiv(RBLOCKS, cdiv(n, RC));
   return round_up(cdiv(m, want), 16 * RWAVES);
 }
 
