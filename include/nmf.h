@@ -145,7 +145,7 @@ typedef struct {
    * Each passive-set solve eliminates the smaller of two equivalent systems
    * (ns unknowns, ns <= 32); four right-hand sides share a wavefront and
    * eliminate together at the size of the largest of them, rounded up to a
-   * size class (8, 12, 16, 18, 20, ..., 30 or 32). */
+   * size class (8, 12, 16, 20, 24, 28 or 32). */
   long long bpp_solves;       /* eliminations performed                    */
   double bpp_flops;           /* their algorithmic flops: ns^3 - ns (Gauss- */
                               /* Jordan, one right-hand side) + 2 k ns (the */

@@ -36,10 +36,21 @@
 // incoming X (warm start); the solution is unique, so the start only changes
 // how many exchanges are needed. The four right-hand sides of a wavefront
 // eliminate together at the size of the largest of their systems.
+//
+// The elimination is a serial chain at two waves per SIMD (the registers of
+// two rows of 32 doubles per lane), so what counts is how many eliminations a
+// wavefront runs. Above k = 32 both matrices are in LDS with the same layout
+// and rows of either form share one elimination; with G^-1 in memory and one
+// elimination per form, a wavefront whose rows were of both forms ran two.
+// 200,000 rows at half-full supports, a sweep: k = 40 580 -> 460 us, k = 48
+// 750 -> 513, k = 64 1507 -> 748; 1,048,576 rows at k = 50 with few rows in
+// the active form 5.05 -> 4.86 ms.
 // ===========================================================================
 namespace nmfk {
 
-constexpr int BPP_WAVES = 4;   // wavefronts per workgroup
+// Wavefronts per workgroup: eight (all that the registers let run on a CU)
+// where G and G^-1 share the CU's LDS with them, four at ranks up to 32.
+constexpr int bpp_waves(int KP) { return KP > 32 ? 8 : 4; }
 constexpr int BPP_RPW = 4;     // right-hand sides per wavefront (one per 16-lane row)
 constexpr int CNF = 32;        // largest eliminated set
 
@@ -125,42 +136,38 @@ __device__ __forceinline__ void gj_steps(std::integer_sequence<int, Q...>, doubl
 }
 
 // acc[s] += M[16 s + i][f] * x_T for the solution entry x_T of position T
-// (held by lane T % 16, slot T / 16) at index f. M is G (LDS, leading
-// dimension KP + 1) or G^-1 (ACTIVE, leading dimension KP).
-template <int T, bool ACTIVE, int KP>
-__device__ __forceinline__ void product_step(const double* __restrict__ Gs,
-                                             const double* __restrict__ Ginv, const int (&fi)[CNF],
+// (held by lane T % 16, slot T / 16) at index f.
+template <int T, int KP>
+__device__ __forceinline__ void product_step(const double* __restrict__ M, const int (&fi)[CNF],
                                              const double (&xs)[2], int nsm, int i,
                                              double (&acc)[KP / 16]) {
-  constexpr int LD = ACTIVE ? KP : KP + 1;
+  constexpr int LD = KP + 1;
   if (T >= nsm) return;
   const double v = row_bcast<T & 15>(xs[T >> 4]);
-  const double* m = (ACTIVE ? Ginv : Gs) + i * LD + fi[T];
+  const double* m = M + i * LD + fi[T];
 #pragma unroll
   for (int s = 0; s < KP / 16; ++s) acc[s] = fma(m[16 * s * LD], v, acc[s]);
 }
 
-template <bool ACTIVE, int KP, int... T>
+template <int KP, int... T>
 __device__ __forceinline__ void product_steps(std::integer_sequence<int, T...>,
-                                              const double* __restrict__ Gs,
-                                              const double* __restrict__ Ginv,
-                                              const int (&fi)[CNF], const double (&xs)[2], int nsm,
-                                              int i, double (&acc)[KP / 16]) {
-  (product_step<T, ACTIVE, KP>(Gs, Ginv, fi, xs, nsm, i, acc), ...);
+                                              const double* __restrict__ M, const int (&fi)[CNF],
+                                              const double (&xs)[2], int nsm, int i,
+                                              double (&acc)[KP / 16]) {
+  (product_step<T, KP>(M, fi, xs, nsm, i, acc), ...);
 }
 
 // Loads each row's system on its solved set (listed in il, right-hand side
 // in rl by index), eliminates, stores the solution by index in sl, and adds
 // the product of the same matrix's columns on the solved set with the
-// solution to acc (one entry per index of the row). The matrix comes from G
-// in LDS (passive form) or from G^-1 (ACTIVE); a row with ns = 0 takes no
-// part. Positions of il past a row's ns hold the index KP, whose row and
-// column of the LDS copy of G are zero, so the passive loads need no
-// masking; every load address is in range, so the loads are branch-free. A
-// non-positive pivot of a row's own system sets bad.
-template <int NS, bool ACTIVE, int KP>
-__device__ __forceinline__ void solve_rows(const double* __restrict__ Gs,
-                                           const double* __restrict__ Ginv, const int* il,
+// solution to acc (one entry per index of the row). M is the row's own matrix
+// in LDS, G (passive form) or G^-1 (active form): both have a zero row and
+// column at index KP, which the positions of il past a row's ns hold, so the
+// loads need no masking, and rows of either form eliminate together. A row
+// with ns = 0 takes no part. A non-positive pivot of a row's own system sets
+// bad.
+template <int NS, int KP>
+__device__ __forceinline__ void solve_rows(const double* __restrict__ M, const int* il,
                                            const double* rl, double* sl, double* pvl, int ns,
                                            int nsm, int i, bool& bad, double (&acc)[KP / 16]) {
   constexpr int RS = NS > 16 ? 2 : 1;
@@ -174,29 +181,11 @@ __device__ __forceinline__ void solve_rows(const double* __restrict__ Gs,
     ri[rs] = il[li + 16 * rs];
     b[rs] = rl[ri[rs]];   // rl[KP] is zero
   }
-  if (ACTIVE) {
-    bool rv[RS];
 #pragma unroll
-    for (int rs = 0; rs < RS; ++rs) {
-      rv[rs] = ri[rs] < KP;
-      ri[rs] = min(ri[rs], KP - 1);
-    }
+  for (int c = 0; c < NS; ++c) {
+    const int cc = il[c];
 #pragma unroll
-    for (int c = 0; c < NS; ++c) {
-      const int cc = il[c];
-#pragma unroll
-      for (int rs = 0; rs < RS; ++rs) {
-        const double v = Ginv[ri[rs] * KP + min(cc, KP - 1)];
-        a[rs][c] = (rv[rs] && cc < KP) ? v : 0.0;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < NS; ++c) {
-      const int cc = il[c];
-#pragma unroll
-      for (int rs = 0; rs < RS; ++rs) a[rs][c] = Gs[ri[rs] * LD + cc];
-    }
+    for (int rs = 0; rs < RS; ++rs) a[rs][c] = M[ri[rs] * LD + cc];
   }
   gj_steps<NS>(std::make_integer_sequence<int, NS>{}, a, b, pvl, nsm, li);
   double xs[2] = {0.0, 0.0};
@@ -215,43 +204,37 @@ __device__ __forceinline__ void solve_rows(const double* __restrict__ Gs,
   // positions past ns hold the index KP; their x_T is 0
   int fi[CNF];
 #pragma unroll
-  for (int t = 0; t < NS; ++t) fi[t] = ACTIVE ? min(il[t], KP - 1) : il[t];
-  product_steps<ACTIVE, KP>(std::make_integer_sequence<int, NS>{}, Gs, Ginv, fi, xs, nsm, li, acc);
+  for (int t = 0; t < NS; ++t) fi[t] = il[t];
+  product_steps<KP>(std::make_integer_sequence<int, NS>{}, M, fi, xs, nsm, li, acc);
 }
 
-// The size an elimination of at most nsm unknowns runs at (solve_pass).
+// The size an elimination of at most nsm unknowns runs at (solve_pass). Few
+// classes: each is some 1000 instructions, and the kernel's code has to fit
+// the instruction cache.
 __device__ __forceinline__ int bpp_size_class(int nsm, int KP) {
   if (nsm <= 8) return 8;
   if (nsm <= 12) return 12;
   if (nsm <= 16 || KP <= 16) return 16;
-  return (nsm + 1) & ~1;   // 18, 20, ..., 32
+  return (nsm + 3) & ~3;   // 20, 24, 28, 32
 }
 
-// One elimination pass over the rows with ns > 0 at the size class of the
+// One elimination pass over the rows with ns > 0 at the size class of nsm, the
 // largest of them.
-template <bool ACTIVE, int KP>
-__device__ __forceinline__ void solve_pass(const double* __restrict__ Gs,
-                                           const double* __restrict__ Ginv, const int* il,
+template <int KP>
+__device__ __forceinline__ void solve_pass(const double* __restrict__ M, const int* il,
                                            const double* rl, double* sl, double* pvl, int ns,
-                                           int i, bool& bad, double (&acc)[KP / 16]) {
-  const int nsm = max(max(__builtin_amdgcn_readlane(ns, 0), __builtin_amdgcn_readlane(ns, 16)),
-                      max(__builtin_amdgcn_readlane(ns, 32), __builtin_amdgcn_readlane(ns, 48)));
+                                           int nsm, int i, bool& bad, double (&acc)[KP / 16]) {
   if (nsm == 0) return;
-#define NMF_BPP_CLASS(C) solve_rows<C, ACTIVE, KP>(Gs, Ginv, il, rl, sl, pvl, ns, nsm, i, bad, acc)
+#define NMF_BPP_CLASS(C) solve_rows<C, KP>(M, il, rl, sl, pvl, ns, nsm, i, bad, acc)
   if (nsm <= 8) NMF_BPP_CLASS(8);
   else if (nsm <= 12) NMF_BPP_CLASS(12);
   else if (nsm <= 16 || KP <= 16) NMF_BPP_CLASS(16);
-  else if (nsm <= 18) NMF_BPP_CLASS(18);
   else if (nsm <= 20) NMF_BPP_CLASS(20);
-  else if (nsm <= 22) NMF_BPP_CLASS(22);
   else if (nsm <= 24) NMF_BPP_CLASS(24);
-  else if (nsm <= 26) NMF_BPP_CLASS(26);
   else if (nsm <= 28) NMF_BPP_CLASS(28);
-  else if (nsm <= 30) NMF_BPP_CLASS(30);
   else NMF_BPP_CLASS(32);
 #undef NMF_BPP_CLASS
 }
-
 
 // Ginv (KP x KP, double) = inverse of G restricted to the indices i < k with
 // G_ii > 0 (zero rows and columns elsewhere); *ok = 0 when a pivot of that
@@ -313,15 +296,19 @@ __global__ __launch_bounds__(64) void gram_inverse_kernel(const TS* __restrict__
 }
 
 template <typename TS, int KP>
-__global__ __launch_bounds__(64 * BPP_WAVES, 2) void bpp_quad_kernel(
+__global__ __launch_bounds__(64 * bpp_waves(KP), 2) void bpp_quad_kernel(
     TS* __restrict__ X, const TS* __restrict__ P, const TS* __restrict__ G,
     const double* __restrict__ Ginv, const int* __restrict__ ginv_ok, int64_t rows, int k,
     int max_pivots, int warm, int* __restrict__ status, unsigned long long* __restrict__ pivots) {
   static_assert(KP % 16 == 0 && KP <= 64, "16-lane rows over at most 64 indices");
   constexpr int JS = KP / 16;   // index slots per lane
   constexpr int LD = KP + 1;
-  // G in double with a zero row and column at index KP (the padding index)
+  constexpr int BPP_WAVES = bpp_waves(KP);
+  constexpr bool INV = KP > CNF;   // the active form occurs
+  // G (and G^-1) in double with a zero row and column at index KP (the
+  // padding index)
   __shared__ double Gs[(KP + 1) * LD];
+  __shared__ double Gis[INV ? (KP + 1) * LD : 1];
   __shared__ double rhs_l[BPP_WAVES][BPP_RPW][KP + 1];   // right-hand side of the solved system
   __shared__ double sol_l[BPP_WAVES][BPP_RPW][KP];   // its solution, by index
   __shared__ double p_l[BPP_WAVES][BPP_RPW][KP];     // the right-hand side p
@@ -348,6 +335,21 @@ __global__ __launch_bounds__(64 * BPP_WAVES, 2) void bpp_quad_kernel(
       const int e = u * 64 * BPP_WAVES + (int)threadIdx.x;
       const int r = e / LD, c = e % LD;
       if (e < NG) Gs[e] = (r < KP && c < KP) ? (double)gv[u] : 0.0;
+    }
+    if constexpr (INV) {
+      double iv[PER];
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int e = u * 64 * BPP_WAVES + (int)threadIdx.x;
+        const int r = e / LD, c = e % LD;
+        iv[u] = Ginv[(e < NG && r < KP && c < KP) ? r * KP + c : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int e = u * 64 * BPP_WAVES + (int)threadIdx.x;
+        const int r = e / LD, c = e % LD;
+        if (e < NG) Gis[e] = (r < KP && c < KP) ? iv[u] : 0.0;
+      }
     }
   }
   for (int e = threadIdx.x; e < BPP_WAVES * BPP_RPW * CNF; e += blockDim.x)
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(64 * BPP_WAVES, 2) void bpp_quad_kernel(
       for (int s = 0; s < JS; ++s) {
         const int jr = act[s] ? 16 * s + i : 0;
         double acc = 0.0;
-        for (int l = 0; l < k; ++l) acc = fma(Ginv[jr * KP + l], pl[l], acc);
+        for (int l = 0; l < k; ++l) acc = fma(Gis[INV ? jr * LD + l : 0], pl[l], acc);
         cpl[16 * s + i] = act[s] ? acc : 0.0;
       }
       have_cp = true;
@@ -507,24 +509,17 @@ __global__ __launch_bounds__(64 * BPP_WAVES, 2) void bpp_quad_kernel(
     const uint64_t S = passive ? F : (all & ~F);
     const int ns = solve ? __popcll(S) : 0;   // 0 in the active form when F holds every index
     if (__ballot(solve) == 0) continue;
-    if (solve && ns > 0) {
-      // the system size this row's elimination runs at: the largest of its
-      // form in the wavefront, then that size's class
-      const int nf_p = passive ? ns : 0, nf_a = passive ? 0 : ns;
-      const int mp = max(max(__builtin_amdgcn_readlane(nf_p, 0), __builtin_amdgcn_readlane(nf_p, 16)),
-                         max(__builtin_amdgcn_readlane(nf_p, 32), __builtin_amdgcn_readlane(nf_p, 48)));
-      const int ma = max(max(__builtin_amdgcn_readlane(nf_a, 0), __builtin_amdgcn_readlane(nf_a, 16)),
-                         max(__builtin_amdgcn_readlane(nf_a, 32), __builtin_amdgcn_readlane(nf_a, 48)));
-      if (i == 0) {
-        const unsigned long long n3 = (unsigned long long)ns;
-        const int mx = passive ? mp : ma;
-        unsigned long long* t = tally_l[wv][g];
-        t[BPP_T_SOLVES] += 1ull;
-        t[BPP_T_FLOPS] += n3 * n3 * n3 - n3 + 2ull * k * n3;
-        t[BPP_T_SIZE] += n3;
-        t[BPP_T_SIZE_MAX] += (unsigned long long)mx;
-        t[BPP_T_SIZE_CLASS] += (unsigned long long)bpp_size_class(mx, KP);
-      }
+    // the four rows eliminate together at the size of the largest system
+    const int nsm = max(max(__builtin_amdgcn_readlane(ns, 0), __builtin_amdgcn_readlane(ns, 16)),
+                        max(__builtin_amdgcn_readlane(ns, 32), __builtin_amdgcn_readlane(ns, 48)));
+    if (solve && ns > 0 && i == 0) {
+      const unsigned long long n3 = (unsigned long long)ns;
+      unsigned long long* t = tally_l[wv][g];
+      t[BPP_T_SOLVES] += 1ull;
+      t[BPP_T_FLOPS] += n3 * n3 * n3 - n3 + 2ull * k * n3;
+      t[BPP_T_SIZE] += n3;
+      t[BPP_T_SIZE_MAX] += (unsigned long long)nsm;
+      t[BPP_T_SIZE_CLASS] += (unsigned long long)bpp_size_class(nsm, KP);
     }
     if (solve) {
       // the solved set in increasing order, then the padding index KP
@@ -544,8 +539,7 @@ __global__ __launch_bounds__(64 * BPP_WAVES, 2) void bpp_quad_kernel(
     double acc[JS];
 #pragma unroll
     for (int s = 0; s < JS; ++s) acc[s] = 0.0;
-    solve_pass<false, KP>(Gs, Ginv, il, rl, sl, pvl, passive ? ns : 0, i, sbad, acc);
-    if (KP > CNF) solve_pass<true, KP>(Gs, Ginv, il, rl, sl, pvl, passive ? 0 : ns, i, sbad, acc);
+    solve_pass<KP>(passive ? Gs : Gis, il, rl, sl, pvl, ns, nsm, i, sbad, acc);
     wave_lds_order();
     if (!solve) continue;
     if (sbad) {
@@ -592,12 +586,15 @@ hipError_t bpp_rows_compact(T* X, const T* P, const T* G, int64_t rows, int k, i
                             int max_pivots, int warm, double* Ginv, int* ginv_ok, int* status,
                             unsigned long long* pivots, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  const int64_t maxb = 256 * 16;
-  const unsigned blocks = (unsigned)std::min<int64_t>(maxb, cdiv(rows, BPP_WAVES * BPP_RPW));
+  // each row of lanes works through its right-hand sides; 16 times as many
+  // workgroups as a CU runs of them even out the ends
+  const int waves = bpp_waves(KP);
+  const int64_t maxb = 256 * 64 / waves;
+  const unsigned blocks = (unsigned)std::min<int64_t>(maxb, cdiv(rows, waves * BPP_RPW));
 #define CASE(K)                                                                          \
   case K:                                                                                \
     if (k > CNF) gram_inverse_kernel<T, K><<<1, 64, 0, st>>>(G, k, Ginv, ginv_ok);            \
-    bpp_quad_kernel<T, K><<<blocks, 64 * BPP_WAVES, 0, st>>>(                         \
+    bpp_quad_kernel<T, K><<<blocks, 64 * bpp_waves(K), 0, st>>>(                         \
         X, P, G, Ginv, ginv_ok, rows, k, max_pivots, warm, status, pivots);              \
     break;
   switch (KP) {
