@@ -9,14 +9,19 @@
 //
 // Both products are computed as D (M x N, float) = X Y^T with X (M x K) A or
 // its transpose, read in A's own layout, and Y (N x K) the packed factor, K
-// contiguous. A H^T (NT) has K contiguous in X too: each K step covers 128
-// bytes of a row; lane (g = l / 16, c = l % 16) of a wave reads bytes 32 g .. 32 g + 31
-// of that step of row c of each of its row tiles, with two 16-byte loads. For
-// FP8 those 32 values are the operand of v_mfma_scale_f32_16x16x128_f8f6f4
-// (lane l: row l % 16, K values 32 (l / 16) .. + 31). For bfloat16 they feed
-// two v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, eight K values from
+// contiguous. A H^T (NT) has K contiguous in X too: each K step covers one
+// 128-byte line of a row, and lane (g = l / 16, c = l % 16) of a wave needs bytes
+// 32 g .. 32 g + 31 of row c of each of its row tiles. For FP8 those 32 values
+// are the operand of v_mfma_scale_f32_16x16x128_f8f6f4 (lane l: row l % 16, K
+// values 32 (l / 16) .. + 31). For bfloat16 they feed two
+// v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, eight K values from
 // 8 (l / 16)): values 0..7 the first, 8..15 the second; the factor operand
-// gets the same K permutation, so the sum is unchanged.
+// gets the same K permutation, so the sum is unchanged. The two 16-byte loads
+// of a tile read eight whole lines each (lane (g, c): row c % 8, then row
+// 8 + c % 8, bytes 32 g + 16 (c / 8)), and lanes c and c + 8 trade halves
+// afterwards (unpair): whole lines per instruction read at 7.1 TB/s on this
+// card, and halves of sixteen lines at 6.1. 131072 x 65536 at k = 100: FP8
+// 1.71 -> 1.39 ms a product, bfloat16 3.35 -> 2.86.
 //
 // A^T W (TN) has the output side contiguous: for the same K values lane (g, c)
 // reads four neighbouring columns of each row, one column for each of its
@@ -120,6 +125,22 @@ __device__ __forceinline__ void regroup(const Run4<uint8_t>::V (&r)[32], XFrag<4
   }
 }
 
+// The operands of MT tiles from row pieces loaded in pairs: x.v[t][h] of lane
+// (g, c) is bytes 32 g + 16 (c / 8) of row 8 h + c % 8; the operand's two
+// halves are bytes 32 g and 32 g + 16 of row c, so lanes c and c + 8 trade one
+// half each (DPP row_ror:8; bank masks 0xC and 0x3 are lanes 8..15 and 0..7).
+template <int MT>
+__device__ __forceinline__ void unpair(const XFrag<MT>& x, XFrag<MT>& f) {
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int a = (int)x.v[t][0][i], b = (int)x.v[t][1][i];
+      f.v[t][0][i] = (unsigned)__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xC, false);
+      f.v[t][1][i] = (unsigned)__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false);
+    }
+}
+
 // TE: stored element (uint16_t bfloat16 bits or uint8_t FP8 E4M3 bits).
 // NT 16-column tiles (N = 16 NT), MT 16-row tiles per wave, STAGES K steps of
 // X in registers (STAGES - 1 in flight while one is multiplied), WPE waves per
@@ -156,7 +177,7 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
   // one (two lanes then hold, and store, the same column)
   static_assert(!TR || MT == 4, "TN lanes take four columns");
   typedef typename Run4<TE>::V RunV;
-  const TE* xr[TR ? 1 : MT];
+  const TE* xr[TR ? 1 : MT][2];
   uint32_t xo = 0;   // TR: the lane's offset from the (uniform) step rows
   if constexpr (TR) {
     int64_t col0 = m0 + 4 * c;
@@ -164,11 +185,13 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
     xo = (uint32_t)((int64_t)(LE * g) * ldx + col0);
   } else {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      int64_t row = m0 + 16 * t + c;
-      row = row < M ? row : M - 1;
-      xr[t] = X + row * ldx + LE * g;
-    }
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int64_t row = m0 + 16 * t + 8 * h + (c & 7);
+        row = row < M ? row : M - 1;
+        xr[t][h] = X + row * ldx + LE * g + VE * (c >> 3);
+      }
   }
   // factor staging: thread tid copies chunk (tid % YCH) of rows tid / YCH + YRP p
   const int ych = tid % YCH, yrow0 = tid / YCH;
@@ -194,10 +217,10 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
             reinterpret_cast<const RunV*>(X + (k0 + u) * ldx + xo));
     } else {
 #pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        f.v[t][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0));
-        f.v[t][1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t] + k0 + VE));
-      }
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          f.v[t][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xr[t][h] + k0));
     }
   };
   auto load_y = [&](u32x4 (&v)[YPASS], int64_t k0) {
@@ -238,13 +261,10 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
   };
 
   auto compute = [&](const XStep& x, int buf) {
-    if constexpr (TR) {
-      XFrag<MT> f;
-      regroup(x.r, f);
-      multiply(f, buf);
-    } else {
-      multiply(x, buf);
-    }
+    XFrag<MT> f;
+    if constexpr (TR) regroup(x.r, f);
+    else unpair(x, f);
+    multiply(f, buf);
   };
 
   // Memory loads complete in issue order as far as the wait counter is
@@ -302,12 +322,13 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       TE e[LE];
+      const int64_t row = m0 + 16 * t + c;
+      const TE* xt = X + (row < M ? row : M - 1) * ldx + LE * g;
 #pragma unroll
       for (int q = 0; q < LE; ++q) {
-        // xr already points at the lane group's K offset LE g
         const bool in = kt + LE * g + q < kend;
         if constexpr (TR) e[q] = in ? X[(kt + q) * ldx + xo + t] : (TE)0;
-        else e[q] = in ? xr[t][kt + q] : (TE)0;
+        else e[q] = in ? xt[kt + q] : (TE)0;
       }
       u32x4 w[2];
       __builtin_memcpy(w, e, sizeof(w));

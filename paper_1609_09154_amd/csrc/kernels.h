@@ -312,7 +312,8 @@ hipError_t check_csr(const int64_t* rowptr, const int32_t* colidx, const float* 
 // right-hand side, 2 k ns for the other half of the optimality pair, 2 k^2
 // per right-hand side that forms G^-1 p); [BPP_T_SIZE] the sizes ns;
 // [BPP_T_SIZE_MAX] the largest size in the wavefront at that elimination (the
-// four right-hand sides of a wavefront eliminate together); [BPP_T_SIZE_CLASS] the size the elimination ran at.
+// four right-hand sides of a wavefront eliminate together);
+// [BPP_T_SIZE_CLASS] the size the elimination ran at.
 enum { BPP_T_PIVOTS = 0, BPP_T_SOLVES, BPP_T_FLOPS, BPP_T_SIZE, BPP_T_SIZE_MAX,
        BPP_T_SIZE_CLASS, BPP_TALLIES = 8 };
 template <typename T>
