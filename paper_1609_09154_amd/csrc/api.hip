@@ -161,7 +161,7 @@ int64_t gram_splits(int64_t rows) {
 // the unrolled layers, so their Grams agree bit for bit.
 constexpr int64_t SHARE_CAP = 4096;
 // Where the shares of a factor's Gram hold at most GSUM_MAX elements (a
-// 2000-row factor at k = 10: 16 shares of 16 x 16), the MU update that needs
+// 2000-row factor at k = 10: 63 shares of 16 x 16), the MU update that needs
 // the Gram adds them itself as it stages G, so the Grams take no launches of
 // their own; each update then keeps its shares in its own buffer.
 constexpr int64_t GSUM_MAX = 1 << 14;
@@ -188,10 +188,10 @@ Shares plan_shares(int algo, int64_t m, int64_t n, int KP) {
 }
 
 // Whether the MU updates add these shares themselves as they stage G (few
-// enough: at most 16, which reduce_splits also adds one after another, so
+// enough: at most 64 at KP = 16, 16 above; in the order of reduce_splits, so
 // either way gives the same bits).
 bool gsum_fits(const Shares& sh, int KP) {
-  return sh.on() && sh.blocks() * KP * KP <= GSUM_MAX && sh.blocks() <= 16;
+  return sh.on() && sh.blocks() * KP * KP <= GSUM_MAX && sh.blocks() <= (KP == 16 ? 64 : 16);
 }
 
 // Elements of the updates' share workspace for an m x n problem: room for

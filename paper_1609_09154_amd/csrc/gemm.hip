@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
   if constexpr (REM) remo = c < 3 * nrem ? (c / nrem) * NR + 16 * NF + c % nrem : 16 * NF;
 
   XStep<MT> xf[STAGES];
-  u32x4 yv[PASS];   // factor slice of the next step   // factor slices of the next two steps
+  u32x4 yv[PASS];   // factor slice of the next step
 
   auto load_x = [&](XStep<MT>& f, int64_t k0) {
     if constexpr (TR) {

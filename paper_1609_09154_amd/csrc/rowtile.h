@@ -122,11 +122,11 @@ __device__ __forceinline__ void stage_rows(T* dst, const T* __restrict__ X, int6
 // acc[e] += the RPT entries at p[e] of each slab q < n at p + q stride,
 // added in slab order in double (16-byte runs when RPT is a multiple of VEC
 // and p is 16-byte aligned, else element by element). The slabs are fetched
-// eight at a time so that their loads are in flight together rather than one
+// G at a time so that their loads are in flight together rather than one
 // memory latency per slab.
-template <typename T, int RPT>
+template <typename T, int RPT, int G = 8>
 __device__ __forceinline__ void slab_sum(const T* p, int n, int64_t stride, double (&acc)[RPT]) {
-  constexpr int VEC = Tr<T>::VEC, G = 8;
+  constexpr int VEC = Tr<T>::VEC;
   if constexpr (RPT % VEC == 0) {
     constexpr int NV = RPT / VEC;
     int q = 0;

@@ -30,23 +30,72 @@ namespace nmfk {
 // rows. P arrives as the product's slabs, summed here in slab order in double
 // (Pout, nullable, receives the sum), so that a split product needs no pass
 // of its own to add them.
-template <int KP> struct RowSplit {
-  static constexpr int TPR = KP == 48 ? 4 : KP / 8;
+//
+// Two row splits. A product over few rows arrives in many slabs (16 at 2000 x
+// 1000), so a block of 128 rows at KP = 16 reads 256 KB of them through one
+// CU, and the update of a 2000-row factor keeps 16 CUs at that for 11 us.
+// FINE takes blocks of 32 (KP = 16) or 16 rows, up to FINE_ROWS rows, where
+// the larger blocks are at most 64; past that they fill the chip well enough,
+// and the Gram shares, one per block, would cost more than they save. An MU
+// iteration, double: 300 x 200 at k = 10 29 -> 19 us, 2000 x 1000 at k = 10
+// 34 -> 27, at k = 48 62 -> 46, at k = 64 58 -> 54; float at k = 10 32 -> 27.
+template <int KP, bool FINE> struct RowSplit {
+  static constexpr int TPR = FINE ? (KP == 16 ? 8 : 16) : KP == 48 ? 4 : KP / 8;
   static constexpr int RPT = KP / TPR;
   static constexpr int ROWS = 256 / TPR;
 };
+constexpr int64_t FINE_ROWS = 2048;
+constexpr bool fine_rows(int64_t rows, int KP) { return rows <= FINE_ROWS; }
 
-// GSUM: G arrives as gn KP x KP shares, summed while staged (in slab order
-// in double, as the separate ordered sum would).
-template <typename T, int KP, bool SLABS, bool GSUM>
+// One element of the sum of n <= 64 shares, in double and in the order of
+// reduce_splits: slabs q, q + 16, ... into sum q, then the 16 sums in turn
+// (up to 16 slabs that is slab after slab). All loads of a batch are issued
+// before the first is added.
+template <typename T>
+__device__ __forceinline__ T share_sum(const T* __restrict__ p, int n, int64_t stride) {
+  double t = 0.0;
+  if (n <= 16) {
+    T v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = p[(q < n ? q : 0) * stride];
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (q < n) t += (double)v[q];
+    return (T)t;
+  }
+#pragma unroll
+  for (int b = 0; b < 16; b += 8) {
+    T v[8][4];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = b + q + 16 * u;
+        v[q][u] = p[(e < n ? e : 0) * stride];
+      }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      double s = 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (b + q + 16 * u < n) s += (double)v[q][u];
+      t += s;
+    }
+  }
+  return (T)t;
+}
+
+// GSUM: G arrives as gn KP x KP shares, summed while staged, in double and in
+// the order of the separate sum (reduce_splits).
+template <typename T, int KP, bool SLABS, bool GSUM, bool FINE>
 __global__ __launch_bounds__(256) void mu_rows_tpr_kernel(const T* X, T* Xn, Split<T> P,
                                                           const T* __restrict__ G, int64_t rows,
                                                           int k, T eps, T* __restrict__ Xt,
                                                           T* __restrict__ Pout,
                                                           T* __restrict__ Gslab, int gn) {
-  constexpr int TPR = RowSplit<KP>::TPR, RPT = RowSplit<KP>::RPT, ROWS = RowSplit<KP>::ROWS;
+  typedef RowSplit<KP, FINE> RS;
+  constexpr int TPR = RS::TPR, RPT = RS::RPT, ROWS = RS::ROWS;
   constexpr int VEC = Tr<T>::VEC;
-  static_assert(RPT % VEC == 0, "16-byte reads of G");
   constexpr int XLD = KP + VEC;
   __shared__ __attribute__((aligned(16))) T Gs[KP * KP];
   __shared__ __attribute__((aligned(16))) T Xs[ROWS * XLD];
@@ -59,7 +108,9 @@ __global__ __launch_bounds__(256) void mu_rows_tpr_kernel(const T* X, T* Xn, Spl
   // all in flight together
   SquareStage<T, KP, 256> gst;
   RowStage<T, KP, ROWS, XLD, 256> xst;
-  if constexpr (GSUM) gst.load_sum(G, gn, (int64_t)KP * KP);
+  T gs = T(0);
+  if constexpr (GSUM && KP == 16) gs = share_sum(G + threadIdx.x, gn, (int64_t)KP * KP);
+  else if constexpr (GSUM) gst.load_sum(G, gn, (int64_t)KP * KP);
   else gst.load(G, nullptr);
   xst.load(X, rb, rows);
   double ps[RPT];
@@ -67,14 +118,15 @@ __global__ __launch_bounds__(256) void mu_rows_tpr_kernel(const T* X, T* Xn, Spl
   for (int ii = 0; ii < RPT; ++ii) ps[ii] = 0.0;
   if (live) {
     if constexpr (SLABS) {
-      slab_sum<T, RPT>(P.p + r * KP + i0, P.n, P.stride, ps);
+      slab_sum<T, RPT, (RPT <= 4 ? 16 : 8)>(P.p + r * KP + i0, P.n, P.stride, ps);
     } else {
       // one slab: the product itself (a sum of one term rounds to itself)
 #pragma unroll
       for (int ii = 0; ii < RPT; ++ii) ps[ii] = (double)P.p[r * KP + i0 + ii];
     }
   }
-  gst.store(Gs);
+  if constexpr (GSUM && KP == 16) Gs[threadIdx.x] = gs;
+  else gst.store(Gs);
   xst.store(Xs, rb, rows);
   __syncthreads();
   const T* xs = &Xs[lr * XLD];
@@ -84,11 +136,16 @@ __global__ __launch_bounds__(256) void mu_rows_tpr_kernel(const T* X, T* Xn, Spl
 #pragma unroll 8
   for (int j = 0; j < KP; ++j) {
     const T xj = xs[j];
+    if constexpr (RPT % VEC == 0) {
 #pragma unroll
-    for (int q = 0; q < RPT / VEC; ++q) {
-      const V16<T> v = load16<T>(&Gs[j * KP + i0 + q * VEC]);
+      for (int q = 0; q < RPT / VEC; ++q) {
+        const V16<T> v = load16<T>(&Gs[j * KP + i0 + q * VEC]);
 #pragma unroll
-      for (int w = 0; w < VEC; ++w) d[q * VEC + w] = fma(xj, v.v[w], d[q * VEC + w]);
+        for (int w = 0; w < VEC; ++w) d[q * VEC + w] = fma(xj, v.v[w], d[q * VEC + w]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < RPT; ++e) d[e] = fma(xj, Gs[j * KP + i0 + e], d[e]);
     }
   }
   T out[RPT];
@@ -172,23 +229,31 @@ __global__ __launch_bounds__(LDS_ROWS) void mu_rows_lds_kernel(const T* X, T* Xn
 
 // One slab (the product as it came) needs no double accumulation: that form
 // keeps fewer registers live.
-template <typename T, int KP, bool GSUM>
+template <typename T, int KP, bool GSUM, bool FINE>
 void launch_mu_rows_tpr_g(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, T eps,
                           T* Xt, T* Pout, T* Gslab, int gn, hipStream_t st) {
-  const unsigned nb = (unsigned)cdiv(rows, RowSplit<KP>::ROWS);
+  const unsigned nb = (unsigned)cdiv(rows, RowSplit<KP, FINE>::ROWS);
   if (P.n > 1)
-    mu_rows_tpr_kernel<T, KP, true, GSUM><<<nb, 256, 0, st>>>(X, Xn, P, G, rows, k, eps, Xt,
-                                                                Pout, Gslab, gn);
+    mu_rows_tpr_kernel<T, KP, true, GSUM, FINE><<<nb, 256, 0, st>>>(X, Xn, P, G, rows, k, eps, Xt,
+                                                                    Pout, Gslab, gn);
   else
-    mu_rows_tpr_kernel<T, KP, false, GSUM><<<nb, 256, 0, st>>>(X, Xn, P, G, rows, k, eps, Xt,
-                                                                 Pout, Gslab, gn);
+    mu_rows_tpr_kernel<T, KP, false, GSUM, FINE><<<nb, 256, 0, st>>>(X, Xn, P, G, rows, k, eps,
+                                                                     Xt, Pout, Gslab, gn);
 }
 
 template <typename T, int KP>
 void launch_mu_rows_tpr(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, T eps,
                         T* Xt, T* Pout, T* Gslab, int gn, hipStream_t st) {
-  if (gn > 1) launch_mu_rows_tpr_g<T, KP, true>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, st);
-  else launch_mu_rows_tpr_g<T, KP, false>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, 1, st);
+#define CALL(GS, FI) \
+  launch_mu_rows_tpr_g<T, KP, GS, FI>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, st)
+  if (fine_rows(rows, KP)) {
+    if (gn > 1) CALL(true, true);
+    else CALL(false, true);
+  } else {
+    if (gn > 1) CALL(true, false);
+    else CALL(false, false);
+  }
+#undef CALL
 }
 
 template <typename T>
@@ -197,6 +262,7 @@ hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int 
   if (rows <= 0) return hipSuccess;
   if (((Xt || Gslab || gn > 1) && KP > 64) || !P.p || P.n < 1 || gn < 1)
     return hipErrorInvalidValue;
+  if (gn > (KP == 16 ? 64 : 16)) return hipErrorInvalidValue;
   KP_SWITCH(KP, (launch_mu_rows_tpr<T, KPc>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, st)),
             (mu_rows_lds_kernel<T><<<(unsigned)cdiv(rows, LDS_ROWS), LDS_ROWS, 0, st>>>(
                 X, Xn, P, G, rows, k, KP, eps, Pout)));
@@ -208,11 +274,12 @@ bool takes_slabs(ShareOf u, int64_t rows) { return u == ShareOf::MU || hals_tpr(
 int share_rows(ShareOf u, int64_t rows, int KP) {
   if (KP > 64 || KP % 16 || KP < 16) return 0;
   if (u == ShareOf::HALS) return 256 / hals_tpr(rows);
+  if (fine_rows(rows, KP)) return KP == 16 ? RowSplit<16, true>::ROWS : RowSplit<64, true>::ROWS;
   switch (KP) {
-    case 16: return RowSplit<16>::ROWS;
-    case 32: return RowSplit<32>::ROWS;
-    case 48: return RowSplit<48>::ROWS;
-    default: return RowSplit<64>::ROWS;
+    case 16: return RowSplit<16, false>::ROWS;
+    case 32: return RowSplit<32, false>::ROWS;
+    case 48: return RowSplit<48, false>::ROWS;
+    default: return RowSplit<64, false>::ROWS;
   }
 }
 
