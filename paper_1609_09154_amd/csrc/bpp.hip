@@ -243,56 +243,84 @@ __device__ __forceinline__ void solve_pass(const double* __restrict__ M, const i
 // right-hand side entry is exactly 0 too, so it stays active with
 // x_i = y_i = 0.
 //
-// One wavefront, in-place Gauss-Jordan in double: lane r holds row r of M
-// (G on the live indices, the identity elsewhere) and ends with row r of
-// M^-1. The step on pivot q subtracts f_r times the raw pivot row from every
-// row r, with f_r = M_rq / M_qq off the pivot row and 1 - 1 / M_qq on it
-// (which scales the pivot row by 1 / M_qq), then sets column q to the
-// inverse's column (-f_r, and 1 / M_qq on the pivot row). Pivot rows are
-// read with readlane; steps of indices outside the live set are identity
-// steps and are skipped.
+// One workgroup, in-place Gauss-Jordan in double: lane r of every wavefront
+// holds row r of M (G on the live indices, the identity elsewhere), each
+// wavefront KP / GINV_WAVES of its columns, and ends with row r of M^-1. The
+// step on pivot q subtracts f_r times the raw pivot row from every row r, with
+// f_r = M_rq / M_qq off the pivot row and 1 - 1 / M_qq on it (which scales the
+// pivot row by 1 / M_qq), then sets column q to the inverse's column (-f_r,
+// and 1 / M_qq on the pivot row). The wavefront that holds column q passes
+// f to the others through LDS, in two buffers in turn, so a step takes one
+// barrier: its writer two steps on has passed the next step's barrier, which
+// every reader reaches after its read. Pivot rows are read with readlane;
+// steps of indices outside the live set are identity steps and are skipped.
+// A step is a chain (a quotient, the exchange, the update); what the
+// wavefronts share is the update of KP columns, most of the 62 us (KP = 64,
+// k = 50) that a single wavefront took; 26 us now.
+constexpr int GINV_WAVES = 8;
+
 template <int Q, int KP>
-__device__ __forceinline__ void ginv_step(double (&a)[KP], int lane, uint64_t live, int k,
-                                          bool& good) {
+__device__ __forceinline__ void ginv_step(double (&a)[KP / GINV_WAVES], int lane, int wave,
+                                          uint64_t live, int k, bool& good, double* fs) {
+  constexpr int CW = KP / GINV_WAVES, QW = Q / CW, QC = Q % CW;
   if (Q >= k || !((live >> Q) & 1ull)) return;
-  const double pv = rdl(a[Q], Q);
-  if (!(pv > 0.0)) good = false;
-  const double s = pv > 0.0 ? 1.0 / pv : 1.0;
   const bool me = lane == Q;
-  const double f = me ? 1.0 - s : a[Q] * s;
+  double f = 0.0, s = 0.0;
+  if (wave == QW) {
+    const double pv = rdl(a[QC], Q);
+    if (!(pv > 0.0)) good = false;
+    s = pv > 0.0 ? 1.0 / pv : 1.0;
+    f = me ? 1.0 - s : a[QC] * s;
+    fs[(Q & 1) * 64 + lane] = f;
+  }
+  __syncthreads();
+  if (wave != QW) f = fs[(Q & 1) * 64 + lane];
 #pragma unroll
-  for (int c = 0; c < KP; ++c)
-    if (c != Q) a[c] = fma(-f, rdl(a[c], Q), a[c]);
-  a[Q] = me ? s : -f;
+  for (int c = 0; c < CW; ++c)
+    if (c != QC || wave != QW) a[c] = fma(-f, rdl(a[c], Q), a[c]);
+  if (wave == QW) a[QC] = me ? s : -f;
 }
 
 template <int KP, int... Q>
-__device__ __forceinline__ void ginv_steps(std::integer_sequence<int, Q...>, double (&a)[KP],
-                                           int lane, uint64_t live, int k, bool& good) {
-  (ginv_step<Q, KP>(a, lane, live, k, good), ...);
+__device__ __forceinline__ void ginv_steps(std::integer_sequence<int, Q...>,
+                                           double (&a)[KP / GINV_WAVES], int lane, int wave,
+                                           uint64_t live, int k, bool& good, double* fs) {
+  (ginv_step<Q, KP>(a, lane, wave, live, k, good, fs), ...);
 }
 
 template <typename TS, int KP>
-__global__ __launch_bounds__(64) void gram_inverse_kernel(const TS* __restrict__ G, int k,
-                                                          double* __restrict__ Ginv,
-                                                          int* __restrict__ ok) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * GINV_WAVES) void gram_inverse_kernel(const TS* __restrict__ G,
+                                                                       int k,
+                                                                       double* __restrict__ Ginv,
+                                                                       int* __restrict__ ok) {
+  constexpr int CW = KP / GINV_WAVES;
+  __shared__ double fs[2 * 64];
+  __shared__ int bad_sh;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (threadIdx.x == 0) bad_sh = 0;
   const bool mine = lane < k && G[lane * KP + lane] > TS(0);
-  const uint64_t live = __ballot(mine);
-  double a[KP];
+  const uint64_t live = __ballot(mine);   // the same in every wavefront
+  double a[CW];
 #pragma unroll
-  for (int c = 0; c < KP; ++c) {
-    const bool lc = (live >> c) & 1ull;
-    a[c] = (mine && lc) ? (double)G[lane * KP + c] : (lane == c ? 1.0 : 0.0);
+  for (int c = 0; c < CW; ++c) {
+    const int cg = wave * CW + c;
+    const bool lc = (live >> cg) & 1ull;
+    a[c] = (mine && lc) ? (double)G[lane * KP + cg] : (lane == cg ? 1.0 : 0.0);
   }
   bool good = true;
-  ginv_steps<KP>(std::make_integer_sequence<int, KP>{}, a, lane, live, k, good);
+  ginv_steps<KP>(std::make_integer_sequence<int, KP>{}, a, lane, wave, live, k, good, fs);
+  __syncthreads();
+  if (!good && lane == 0) bad_sh = 1;
   if (lane < KP) {
 #pragma unroll
-    for (int c = 0; c < KP; ++c)
-      Ginv[lane * KP + c] = (mine && ((live >> c) & 1ull)) ? a[c] : 0.0;
+    for (int c = 0; c < CW; ++c) {
+      const int cg = wave * CW + c;
+      Ginv[lane * KP + cg] = (mine && ((live >> cg) & 1ull)) ? a[c] : 0.0;
+    }
   }
-  if (lane == 0) *ok = good ? 1 : 0;
+  __syncthreads();
+  if (threadIdx.x == 0) *ok = bad_sh ? 0 : 1;
 }
 
 template <typename TS, int KP>
@@ -593,7 +621,10 @@ hipError_t bpp_rows_compact(T* X, const T* P, const T* G, int64_t rows, int k, i
   const unsigned blocks = (unsigned)std::min<int64_t>(maxb, cdiv(rows, waves * BPP_RPW));
 #define CASE(K)                                                                          \
   case K:                                                                                \
-    if (k > CNF) gram_inverse_kernel<T, K><<<1, 64, 0, st>>>(G, k, Ginv, ginv_ok);            \
+    if constexpr (K > CNF) {                                                             \
+      if (k > CNF)                                                                       \
+        gram_inverse_kernel<T, K><<<1, 64 * GINV_WAVES, 0, st>>>(G, k, Ginv, ginv_ok);   \
+    }                                                                                    \
     bpp_quad_kernel<T, K><<<blocks, 64 * bpp_waves(K), 0, st>>>(                         \
         X, P, G, Ginv, ginv_ok, rows, k, max_pivots, warm, status, pivots);              \
     break;
