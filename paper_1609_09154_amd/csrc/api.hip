@@ -591,7 +591,7 @@ nmf_status objective(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int 
     }
     return NMF_EINVAL;
   }
-  const int64_t np = nmfk::residual_partials(m, n);
+  const int64_t np = nmfk::residual_partials<T>(m, n);
   double* nrm = first ? w.obj_part + np : nullptr;
   if (pb.lp == NMF_BF16) {
     if constexpr (sizeof(T) == 4)
@@ -914,7 +914,7 @@ nmf_status dense_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int lp, co
                       nmf_stats* stats) {
   const int KP = kp_dense(k);
   const bool want_obj = o->objective != NMF_OBJ_NONE;
-  const int64_t obj_np = 2 * nmfk::residual_partials(m, n);
+  const int64_t obj_np = 2 * nmfk::residual_partials<T>(m, n);
   const LpPlan bp = lp ? lp_plan(lp, m, n, KP) : LpPlan{0, 0};
   Carve cv;
   size_t off[18];
@@ -1440,7 +1440,7 @@ nmf_status relerr_impl(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, in
                        const T* Ht, double* out) {
   const int KP = pb.sparse ? kp_sparse(k) : kp_dense(k);
   const int64_t obj_np = pb.sparse ? std::max<int64_t>(nmfk::csr_residual_partials(m), 1024)
-                                   : 2 * nmfk::residual_partials(m, n);
+                                   : 2 * nmfk::residual_partials<T>(m, n);
   Carve cv;
   size_t off[18];
   plan_work<T>(m, n, KP, 0, obj_np, 0, cv, off, pb.sparse);

@@ -176,7 +176,7 @@ hipError_t transpose_out(const T* Ht, int k, int64_t n, int KP, T* H, hipStream_
 
 // Objective pieces. Each writes one double partial per block into `partial`
 // and a final reduce sums them in order.
-int64_t residual_partials(int64_t m, int64_t n);
+template <typename T> int64_t residual_partials(int64_t m, int64_t n);
 // Squared differences of A - W Ht^T (residual_partials of them) and, npartial
 // set, as many partials of ||A||^2 from the same read of A. A is stored as TA
 // (T, or with float factors uint16_t bfloat16 bits or uint8_t FP8 E4M3 bits).

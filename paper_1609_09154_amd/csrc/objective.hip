@@ -10,6 +10,8 @@
 
 #include "split_mma.h"
 
+#include <type_traits>
+
 namespace nmfk {
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -31,16 +33,23 @@ __device__ __forceinline__ double block_sum(double v) {
   return s;  // valid in thread 0
 }
 
-// Residual pass. A block takes 64 columns of A and a run of its rows; its four
-// waves take the run's 16-row tiles in turn. The block's 64 rows of Ht stay
-// with the wave for all its tiles, so a tile costs one read of its 16 x 64
-// entries of A (lane (g, c) takes columns 4 c .. 4 c + 3 of four rows, so a
-// load instruction covers 256 bytes of each row; tile j of the product takes
-// columns 4 c + j to match) and of 16 rows of W, both fetched while the tile
-// before is computed. What bounds it is the read of A: 100003 x 5003 at k =
-// 50 took 1781 us (64 x 256 blocks, element loads after the product, and 55
-// us more to sum their partials, and 755 for ||A||) and takes 0.61 ms (3.3 TB/s;
-// rows of an odd length are not 16-byte aligned), 0.66 with ||A||.
+// Residual pass. A wave takes 64 columns of A and a run of its 16-row tiles.
+// The 64 rows of Ht stay with the wave for all its tiles, so a tile costs one
+// read of its 16 x 64 entries of A (lane (g, c) takes columns 4 c .. 4 c + 3 of
+// four rows, so a load instruction covers 256 bytes of each row; tile j of the
+// product takes columns 4 c + j to match) and of 16 rows of W, both fetched
+// while the tile before is computed. Float: the block's four waves take
+// neighbouring columns and the same tiles, so that W's rows come once per
+// block (the other waves find them in the L1 cache); double: the same columns,
+// whose rows of Ht are in LDS, and the run's tiles in turn.
+//
+// What bounds it is the read of A, at the occupancy that Ht's planes leave:
+// 100003 x 5003 at k = 50 took 1781 us (64 x 256 blocks, element loads after
+// the product, and 55 us more to sum their partials, and 755 for ||A||) and
+// takes 0.56 ms with ||A|| (3.6 TB/s; rows of an odd length are not 16-byte
+// aligned). Of that, loads that no branch surrounds gave 830 -> 633 us, and
+// the waves side by side 633 -> 561 (4096 x 2048 at k = 32: 14.8 -> 13.8 ->
+// 11.5; 30000^2 at k = 64: 1304 -> 985 -> 1009).
 // Four entries of a row of A, widened to what the difference is taken in.
 template <typename TA> struct A4;
 template <> struct A4<float> {
@@ -83,22 +92,22 @@ template <> struct A4<uint8_t> {
   }
 };
 
-constexpr int RC = 64;       // columns of A per block
+constexpr int RC = 64;       // columns of A per wave
 constexpr int RWAVES = 4;    // waves per block
 
 // One tile's entries of A: row row0 + rr(r), columns col .. col + 3. ACC: the
 // type of the product (row order of its accumulator). A block whose columns
-// run past n loads element by element.
-template <typename TACC, typename TA>
+// run past n (not FULL) loads element by element.
+template <bool FULL, typename TACC, typename TA>
 __device__ __forceinline__ void load_a_tile(A4<TA> (&av)[4], const TA* __restrict__ A, int64_t lda,
                                             int64_t m, int64_t n, int64_t row0, int64_t col,
-                                            bool full, int lane) {
+                                            int lane) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     int64_t row = row0 + acc_row<TACC>(lane, r);
     row = row < m ? row : m - 1;
     const TA* p = A + row * lda;
-    if (full) {
+    if constexpr (FULL) {
       av[r].load(p + col);
     } else {
 #pragma unroll
@@ -108,7 +117,7 @@ __device__ __forceinline__ void load_a_tile(A4<TA> (&av)[4], const TA* __restric
 }
 
 // Adds the tile's squared differences to sr and, NORM, A's squares to sa.
-template <bool NORM, typename TACC, typename TA, typename ACC>
+template <bool FULL, bool NORM, typename TACC, typename TA, typename ACC>
 __device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)[4], int64_t m,
                                          int64_t n, int64_t row0, int64_t col, int lane,
                                          double& sr, double& sa) {
@@ -117,7 +126,7 @@ __device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)
     if (row0 + acc_row<TACC>(lane, r) >= m) continue;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (col + j >= n) continue;
+      if (!FULL && col + j >= n) continue;
       const double a = av[r].at(j), d = a - (double)acc[j][r];
       sr = fma(d, d, sr);
       if constexpr (NORM) sa = fma(a, a, sa);
@@ -134,22 +143,24 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
     double* __restrict__ npartial) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, c = lane & 15;
-  const int64_t c0 = (int64_t)blockIdx.x * RC, col = c0 + 4 * c;
-  const int64_t rbeg = (int64_t)blockIdx.y * rows, rend = rbeg + rows < m ? rbeg + rows : m;
+  const int64_t c0 = ((int64_t)blockIdx.x * RWAVES + wave) * RC, col = c0 + 4 * c;
+  const int64_t rbeg = (int64_t)blockIdx.y * rows;
+  // a wave past the last column takes no tile
+  const int64_t rend = c0 >= n ? 0 : rbeg + rows < m ? rbeg + rows : m;
   const bool full = c0 + RC <= n;
-  // eight entries 32 s + 8 g .. of a factor row (zero past KP), split
+  // eight entries 32 s + 8 g .. of a factor row; clear8: zero past KP
   auto load8 = [&](float (&x)[8], const float* row, int s) {
-    const int k0 = 32 * s + 8 * g;
-    if (k0 < KP) {
+    const int k0 = 32 * s + 8 * g < KP ? 32 * s + 8 * g : 0;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float4 v = *reinterpret_cast<const float4*>(row + k0 + 4 * h);
-        x[4 * h] = v.x; x[4 * h + 1] = v.y; x[4 * h + 2] = v.z; x[4 * h + 3] = v.w;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = 0.f;
+    for (int h = 0; h < 2; ++h) {
+      const float4 v = *reinterpret_cast<const float4*>(row + k0 + 4 * h);
+      x[4 * h] = v.x; x[4 * h + 1] = v.y; x[4 * h + 2] = v.z; x[4 * h + 3] = v.w;
     }
+  };
+  auto clear8 = [&](float (&x)[8], int s) {
+    if (s < KS - 1) return;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = 32 * s + 8 * g < KP ? x[u] : 0.f;
   };
   Split8 hp[KS][4];
 #pragma unroll
@@ -159,60 +170,72 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
     for (int s = 0; s < KS; ++s) {
       float x[8];
       load8(x, row, s);
+      clear8(x, s);
       hp[s][j] = split8(x);
     }
   }
   double sr = 0.0, sa = 0.0;
-  // PF tiles in flight (one wave per SIMD has the registers for two)
+  // PF tiles in flight (one wave per SIMD has the registers for two). Loads of
+  // tiles past the run's end are clamped, not skipped: with a branch around a
+  // load the compiler cannot count what was issued after it, and waits for
+  // all of it.
   constexpr int PF = KS <= 2 ? 1 : 2;
-  float wv[PF][KS][8];
-  A4<TA> av[PF][4];
-  auto load_tile = [&](int p, int64_t row0) {
-    if (row0 >= rend) return;
-    const int64_t row = row0 + c < m ? row0 + c : m - 1;
+  auto run = [&](auto fullc) {
+    constexpr bool FULL = decltype(fullc)::value;
+    float wv[PF][KS][8];
+    A4<TA> av[PF][4];
+    auto load_w = [&](int p, int64_t row0) {
+      const int64_t row = row0 + c < m ? row0 + c : m - 1;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) load8(wv[p][s], W + row * KP, s);
-    load_a_tile<float>(av[p], A, lda, m, n, row0, col, full, lane);
-  };
-  auto tile = [&](int p, int64_t row0) {
-    if (row0 >= rend) return;
-    f32x4 acc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
-    Split8 ws[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) ws[s] = split8(wv[p][s]);
-    A4<TA> cur[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) cur[r] = av[p][r];
-    load_tile(p, row0 + PF * 16 * RWAVES);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) split_mma(ws[s], hp[s], acc);
-    // products of entries that are not finite: again with the float instruction
-    bool bad = false;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
-    if (__ballot(bad)) {
+      for (int s = 0; s < KS; ++s) load8(wv[p][s], W + row * KP, s);
+    };
+    auto load_a = [&](int p, int64_t row0) {
+      load_a_tile<FULL, float>(av[p], A, lda, m, n, row0, col, lane);
+    };
+    auto tile = [&](int p, int64_t row0) {
+      f32x4 acc[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
-      const int64_t row = row0 + c < m ? row0 + c : m - 1;
-      for (int k0 = 0; k0 < KP; k0 += 4)
+      Split8 ws[KS];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[j] = mfma16(W[row * KP + k0 + g],
-                          Ht[(col + j < n ? col + j : n - 1) * KP + k0 + g], acc[j]);
+      for (int s = 0; s < KS; ++s) {
+        clear8(wv[p][s], s);
+        ws[s] = split8(wv[p][s]);
+      }
+      load_w(p, row0 + PF * 16);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) split_mma(ws[s], hp[s], acc);
+      // products of entries that are not finite: again with the float instruction
+      bool bad = false;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
+      if (__ballot(bad)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
+        const int64_t row = row0 + c < m ? row0 + c : m - 1;
+        for (int k0 = 0; k0 < KP; k0 += 4)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[j] = mfma16(W[row * KP + k0 + g],
+                            Ht[(col + j < n ? col + j : n - 1) * KP + k0 + g], acc[j]);
+      }
+      add_tile<FULL, NORM, float>(av[p], acc, row0 < rend ? m : 0, n, row0, col, lane, sr, sa);
+      load_a(p, row0 + PF * 16);
+    };
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      load_w(p, rbeg + p * 16);
+      load_a(p, rbeg + p * 16);
     }
-    add_tile<NORM, float>(cur, acc, m, n, row0, col, lane, sr, sa);
+    for (int64_t row0 = rbeg; row0 < rend; row0 += PF * 16) {
+#pragma unroll
+      for (int p = 0; p < PF; ++p) tile(p, row0 + p * 16);
+    }
   };
-  const int64_t first = rbeg + 16 * wave;
-#pragma unroll
-  for (int p = 0; p < PF; ++p) load_tile(p, first + p * 16 * RWAVES);
-  for (int64_t row0 = first; row0 < rend; row0 += PF * 16 * RWAVES) {
-#pragma unroll
-    for (int p = 0; p < PF; ++p) tile(p, row0 + p * 16 * RWAVES);
-  }
+  if (full) run(std::true_type{});
+  else run(std::false_type{});
   const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   const double s = block_sum(sr);
   if (threadIdx.x == 0) partial[b] = s;
@@ -247,31 +270,35 @@ __global__ __launch_bounds__(64 * RWAVES, 2) void residual_f64_kernel(
   }
   __syncthreads();
   double sr = 0.0, sa = 0.0;
-  A4<double> av[4];
-  int64_t row0 = rbeg + 16 * wave;
-  if (row0 < rend) load_a_tile<double>(av, A, lda, m, n, row0, col, full, lane);
-  for (; row0 < rend; row0 += 16 * RWAVES) {
-    f64x4 acc[4];
+  auto run = [&](auto fullc) {
+    constexpr bool FULL = decltype(fullc)::value;
+    A4<double> av[4];
+    int64_t row0 = rbeg + 16 * wave;
+    load_a_tile<FULL, double>(av, A, lda, m, n, row0, col, lane);
+    for (; row0 < rend; row0 += 16 * RWAVES) {
+      f64x4 acc[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = zero4<double>();
-    A4<double> cur[4];
+      for (int j = 0; j < 4; ++j) acc[j] = zero4<double>();
+      A4<double> cur[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) cur[r] = av[r];
-    const int64_t next = row0 + 16 * RWAVES;
-    if (next < rend) load_a_tile<double>(av, A, lda, m, n, next, col, full, lane);
-    const double* wr = W + (row0 + c < m ? row0 + c : m - 1) * KP + 2 * g;
+      for (int r = 0; r < 4; ++r) cur[r] = av[r];
+      load_a_tile<FULL, double>(av, A, lda, m, n, row0 + 16 * RWAVES, col, lane);
+      const double* wr = W + (row0 + c < m ? row0 + c : m - 1) * KP + 2 * g;
 #pragma unroll 2
-    for (int k0 = 0; k0 < KP; k0 += 8) {
-      const V16<double> w = load16<double>(wr + k0);
+      for (int k0 = 0; k0 < KP; k0 += 8) {
+        const V16<double> w = load16<double>(wr + k0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const V16<double> h = load16<double>(&Hs[(16 * j + c) * LD + k0 + 2 * g]);
-        acc[j] = mfma16(w.v[0], h.v[0], acc[j]);
-        acc[j] = mfma16(w.v[1], h.v[1], acc[j]);
+        for (int j = 0; j < 4; ++j) {
+          const V16<double> h = load16<double>(&Hs[(16 * j + c) * LD + k0 + 2 * g]);
+          acc[j] = mfma16(w.v[0], h.v[0], acc[j]);
+          acc[j] = mfma16(w.v[1], h.v[1], acc[j]);
+        }
       }
+      add_tile<FULL, NORM, double>(cur, acc, m, n, row0, col, lane, sr, sa);
     }
-    add_tile<NORM, double>(cur, acc, m, n, row0, col, lane, sr, sa);
-  }
+  };
+  if (full) run(std::true_type{});
+  else run(std::false_type{});
   const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   const double s = block_sum(sr);
   if (threadIdx.x == 0) partial[b] = s;
@@ -282,17 +309,20 @@ __global__ __launch_bounds__(64 * RWAVES, 2) void residual_f64_kernel(
   }
 }
 
-// Rows per block: about 1024 blocks (512 and 2048 measured within 5% up to
-// 8192^2; fewer cost 25% at 100003 x 5003), at least one tile per wave.
+// Columns and rows per block: about 1024 blocks (512 and 2048 measured within
+// 5% up to 8192^2; fewer cost 25% at 100003 x 5003), at least 64 rows.
 constexpr int RBLOCKS = 1024;
-static int64_t residual_rows(int64_t m, int64_t n) {
-  const int64_t want = cdiv(RBLOCKS, cdiv(n, RC));
+template <typename T> constexpr int residual_cols() { return sizeof(T) == 8 ? RC : RC * RWAVES; }
+template <typename T> static int64_t residual_rows(int64_t m, int64_t n) {
+  const int64_t want = cdiv(RBLOCKS, cdiv(n, residual_cols<T>()));
   return round_up(cdiv(m, want), 16 * RWAVES);
 }
 
-int64_t residual_partials(int64_t m, int64_t n) {
-  return cdiv(n, RC) * cdiv(m, residual_rows(m, n));
+template <typename T> int64_t residual_partials(int64_t m, int64_t n) {
+  return cdiv(n, residual_cols<T>()) * cdiv(m, residual_rows<T>(m, n));
 }
+template int64_t residual_partials<float>(int64_t, int64_t);
+template int64_t residual_partials<double>(int64_t, int64_t);
 
 template <typename TA, int KS>
 static void residual_split_launch(dim3 grid, const TA* A, int64_t lda, int64_t m, int64_t n,
@@ -310,8 +340,8 @@ template <typename T, typename TA>
 hipError_t residual_sq(const TA* A, int64_t lda, int64_t m, int64_t n, const T* W, const T* Ht,
                        int KP, double* partial, double* npartial, hipStream_t st) {
   if (KP < 16 || KP > 128 || KP % 16) return hipErrorInvalidValue;
-  const int64_t rows = residual_rows(m, n);
-  const dim3 grid((unsigned)cdiv(n, RC), (unsigned)cdiv(m, rows));
+  const int64_t rows = residual_rows<T>(m, n);
+  const dim3 grid((unsigned)cdiv(n, residual_cols<T>()), (unsigned)cdiv(m, rows));
   if constexpr (sizeof(T) == 8) {
     switch (KP) {
 #define CASE(K)                                                                                   \
