@@ -206,12 +206,16 @@ __global__ __launch_bounds__(256) void mu_adjoint_rows_kernel(
 
 // Out[r] = (Out[r] + Y[r]) + X[r] M for rows x KP X and KP x KP M, columns
 // < k; Y (nullable) arrives as a product's slabs, summed in slab order in
-// double.
-template <typename T, int KP>
+// double. Bound by the read of those slabs; TPR threads a row, RPT outputs
+// each. FINE: 16 threads a row, up to ROWMM_FINE rows, where the blocks of
+// AdjSplit are too few to pull a product's slabs from memory (double, 3000 x
+// 1700 at k = 40: 18.7 us with 47 and 27 blocks, 5.8 with 188 and 107).
+constexpr int64_t ROWMM_FINE = 8192;
+template <typename T, int KP, bool FINE>
 __global__ __launch_bounds__(256) void rowmm_add_kernel(const T* __restrict__ X,
                                                         const T* __restrict__ M, Split<T> Y,
                                                         int64_t rows, int k, T* __restrict__ Out) {
-  constexpr int TPR = AdjSplit<KP>::TPR, RPT = AdjSplit<KP>::RPT, ROWS = AdjSplit<KP>::ROWS;
+  constexpr int TPR = FINE ? 16 : AdjSplit<KP>::TPR, RPT = KP / TPR, ROWS = 256 / TPR;
   constexpr int VEC = Tr<T>::VEC;
   constexpr int XLD = KP + VEC;
   __shared__ __attribute__((aligned(16))) T Ms[KP * KP];
@@ -225,10 +229,13 @@ __global__ __launch_bounds__(256) void rowmm_add_kernel(const T* __restrict__ X,
   RowStage<T, KP, ROWS, XLD, 256> xst;
   mst.load(M, nullptr);
   xst.load(X, rb, rows);
+  T o[RPT];
+#pragma unroll
+  for (int ii = 0; ii < RPT; ++ii) o[ii] = Out[(live ? r : rows - 1) * KP + i0 + ii];
   double ys[RPT];
 #pragma unroll
   for (int ii = 0; ii < RPT; ++ii) ys[ii] = 0.0;
-  if (live && Y.p) slab_sum<T, RPT>(Y.p + r * KP + i0, Y.n, Y.stride, ys);
+  if (live && Y.p) slab_sum<T, RPT, (RPT <= 4 ? 16 : 8)>(Y.p + r * KP + i0, Y.n, Y.stride, ys);
   mst.store(Ms);
   xst.store(Xs, rb, rows);
   __syncthreads();
@@ -240,19 +247,23 @@ __global__ __launch_bounds__(256) void rowmm_add_kernel(const T* __restrict__ X,
 #pragma unroll 8
   for (int j = 0; j < KP; ++j) {
     const T xj = xs[j];
+    if constexpr (RPT % VEC == 0) {
 #pragma unroll
-    for (int q = 0; q < RPT / VEC; ++q) {
-      const V16<T> v = load16<T>(&Ms[j * KP + i0 + q * VEC]);
+      for (int q = 0; q < RPT / VEC; ++q) {
+        const V16<T> v = load16<T>(&Ms[j * KP + i0 + q * VEC]);
 #pragma unroll
-      for (int w = 0; w < VEC; ++w) s[q * VEC + w] = fma(xj, v.v[w], s[q * VEC + w]);
+        for (int w = 0; w < VEC; ++w) s[q * VEC + w] = fma(xj, v.v[w], s[q * VEC + w]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < RPT; ++e) s[e] = fma(xj, Ms[j * KP + i0 + e], s[e]);
     }
   }
 #pragma unroll
   for (int ii = 0; ii < RPT; ++ii)
     if (i0 + ii < k) {
-      T o = Out[r * KP + i0 + ii];
-      if (Y.p) o += (T)ys[ii];
-      Out[r * KP + i0 + ii] = o + s[ii];
+      if (Y.p) o[ii] += (T)ys[ii];
+      Out[r * KP + i0 + ii] = o[ii] + s[ii];
     }
 }
 
@@ -838,9 +849,12 @@ hipError_t rowmm_add(const T* X, const T* M, int64_t rows, int k, int KP, T* Out
   switch (KP) {
 #define CASE(K)                                                                              \
   case K:                                                                                    \
-    rowmm_add_kernel<T, K><<<(unsigned)cdiv(rows, AdjSplit<K>::ROWS), 256, 0, st>>>(X, M, Y,  \
-                                                                                  rows, k,   \
-                                                                                  Out);      \
+    if (rows <= ROWMM_FINE)                                                                  \
+      rowmm_add_kernel<T, K, true><<<(unsigned)cdiv(rows, 16), 256, 0, st>>>(X, M, Y, rows,  \
+                                                                             k, Out);        \
+    else                                                                                     \
+      rowmm_add_kernel<T, K, false><<<(unsigned)cdiv(rows, AdjSplit<K>::ROWS), 256, 0, st>>>( \
+          X, M, Y, rows, k, Out);                                                            \
     break;
     CASE(16) CASE(32) CASE(48) CASE(64)
 #undef CASE
