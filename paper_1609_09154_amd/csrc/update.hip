@@ -34,18 +34,21 @@ namespace nmfk {
 // Two row splits. A product over few rows arrives in many slabs (16 at 2000 x
 // 1000), so a block of 128 rows at KP = 16 reads 256 KB of them through one
 // CU, and the update of a 2000-row factor keeps 16 CUs at that for 11 us.
-// FINE takes blocks of 32 (KP = 16) or 16 rows, up to FINE_ROWS rows, where
-// the larger blocks are at most 64; past that they fill the chip well enough,
-// and the Gram shares, one per block, would cost more than they save. An MU
-// iteration, double: 300 x 200 at k = 10 29 -> 19 us, 2000 x 1000 at k = 10
-// 34 -> 27, at k = 48 62 -> 46, at k = 64 58 -> 54; float at k = 10 32 -> 27.
+// FINE takes blocks of 32 (KP up to 32) or 16 rows, up to fine_rows; past that
+// the larger blocks fill the chip well enough, and the Gram shares, one per
+// block, would cost more than they save. An MU iteration, double: 300 x 200 at
+// k = 10 29 -> 19 us, 2000 x 1000 at k = 10 34 -> 27, 3000 x 2500 at k = 32 70 ->
+// 59, 8000 x 1000 at k = 40 73 -> 66, 2000 x 1000 at k = 64 58 -> 54; float at
+// k = 10 32 -> 27, at k = 32 47 -> 46, at k = 40 57 -> 53 (and 4000 x 1000 at
+// k = 30 38.5 -> 40.2, 8000 x 1000 at k = 64 57.2 -> 58.7: past the line).
 template <int KP, bool FINE> struct RowSplit {
-  static constexpr int TPR = FINE ? (KP == 16 ? 8 : 16) : KP == 48 ? 4 : KP / 8;
+  static constexpr int TPR = FINE ? (KP <= 32 ? 8 : 16) : KP == 48 ? 4 : KP / 8;
   static constexpr int RPT = KP / TPR;
   static constexpr int ROWS = 256 / TPR;
 };
-constexpr int64_t FINE_ROWS = 2048;
-constexpr bool fine_rows(int64_t rows, int KP) { return rows <= FINE_ROWS; }
+constexpr bool fine_rows(int64_t rows, int KP) {
+  return rows <= (KP == 48 ? 8192 : KP == 32 ? 3072 : 2048);
+}
 
 // One element of the sum of n <= 64 shares, in double and in the order of
 // reduce_splits: slabs q, q + 16, ... into sum q, then the 16 sums in turn
@@ -274,7 +277,7 @@ bool takes_slabs(ShareOf u, int64_t rows) { return u == ShareOf::MU || hals_tpr(
 int share_rows(ShareOf u, int64_t rows, int KP) {
   if (KP > 64 || KP % 16 || KP < 16) return 0;
   if (u == ShareOf::HALS) return 256 / hals_tpr(rows);
-  if (fine_rows(rows, KP)) return KP == 16 ? RowSplit<16, true>::ROWS : RowSplit<64, true>::ROWS;
+  if (fine_rows(rows, KP)) return KP <= 32 ? RowSplit<32, true>::ROWS : RowSplit<64, true>::ROWS;
   switch (KP) {
     case 16: return RowSplit<16, false>::ROWS;
     case 32: return RowSplit<32, false>::ROWS;

@@ -1,7 +1,7 @@
-"""The MU row update's two splits of a factor into blocks (up to 2048 rows and
-above), at the edges of their blocks and of the rule between them, and the
-Gram shares that small problems' updates add themselves (up to 64 at the
-smallest padded rank), in the order of the separate sum."""
+"""The MU row update's two splits of a factor into blocks (up to 2048, 3072 or
+8192 rows by rank, and above), at the edges of their blocks and of the rule
+between them, and the Gram shares that small problems' updates add themselves
+(up to 64 at the smallest padded rank), in the order of the separate sum."""
 import numpy as np
 import pytest
 
@@ -21,7 +21,7 @@ def test_update_mu_blocks(dt, k):
     npdt, u = DT[dt]
     H = uniform((k, 3 * k + 5), seed=k)
     G = (H @ H.T).astype(npdt)
-    for rows in (1, 16, 17, 33, 2048, 2049):
+    for rows in (1, 16, 17, 33, 2048, 2049, 3072, 3073, 8192, 8193):
         P = (uniform((rows, 3 * k + 5), seed=rows + k) @ H.T).astype(npdt)
         X = uniform((rows, k), seed=rows + 2 * k).astype(npdt)
         Xd = to_dev(X, npdt)
