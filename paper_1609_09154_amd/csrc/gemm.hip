@@ -402,14 +402,24 @@ static bool split_wide(int64_t M, int NT, int64_t K) {
   return NT <= 4 && M >= 64 && M * K >= ((int64_t)1 << 27);
 }
 
+// Slabs: doubled from one until the grid holds SPLIT_WGS workgroups and no
+// slab is longer than the shape allows; then full_rounds. 20000^2 at k = 128:
+// 3 slabs for 4 (471 workgroups for 628 on 512 places), 591 -> 501 us; 9000 x
+// 7000 at k = 64: 76 -> 59 us; A^T W of 24000 x 16400 at k = 50: 15 for 8, 366 ->
+// 304 us (A H^T, 5 for 8: 355 -> 367); 100003 x 5003 at k = 50: 588 -> 533 us (5 for
+// 2) and 490 -> 460 us (25 for 32).
 int64_t gemm_split_splits(int64_t M, int KP, int64_t K) {
   const bool wide = split_wide(M, KP / 16, K);
   const int64_t wgs = cdiv(M, (wide ? 64 : 32) * SPW), maxlen = wide ? 8192 : 16384;
   const int64_t minlen = M * K < ((int64_t)1 << 23) ? 64 : 128;
+  auto room = [&](int64_t s) { return s * M * KP <= ((int64_t)1 << 28); };
   int64_t s = 1;
   while (wgs * s < SPLIT_WGS && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
-  while (K > s * maxlen && s < MAX_PRODUCT_SPLITS && 2 * s * M * KP <= ((int64_t)1 << 28)) s *= 2;
-  return s;
+  while (K > s * maxlen && s < MAX_PRODUCT_SPLITS && room(2 * s)) s *= 2;
+  return full_rounds(wgs, s, SPLIT_WGS, 2.0 * KP / (double)K, [&](int64_t t) {
+    return t <= MAX_PRODUCT_SPLITS && (t == 1 || K / t >= minlen) && (t <= s || room(t)) &&
+           (K <= t * maxlen || K > s * maxlen);
+  });
 }
 
 struct SplitCall {

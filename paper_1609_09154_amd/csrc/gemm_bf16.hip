@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "grid.h"
 #include "kernels.h"
 
 namespace nmfk {
@@ -494,11 +495,18 @@ hipError_t pack_fp8_t(const float* F, int64_t rows, int KP, uint8_t* Ft, int64_t
 constexpr int B_MT = 4, B_STAGES = 4, B_WPE = 1;  // launch shape (timing sweep at 131072 x 65536, k = 100)
 constexpr int BROWS = 16 * B_MT * BWAVES;
 
+// One workgroup per CU and round, slabs of at least 1024, at most 2^21 rows of
+// them (1 GB at the largest rank). A slab's cost is taken at rank 64 and
+// bfloat16. bfloat16, 24000 x 16400 at k = 50, A^T W: 7 slabs for 4, 240 -> 199 us;
+// 100000 x 4800 249 -> 180; 20000^2 at k = 100 274 -> 200 and A H^T 295 -> 220 (FP8
+// 222 -> 168 and 205 -> 162).
 int64_t gemm_lp_splits(int64_t M, int64_t K) {
   const int64_t blocks = cdiv(M, BROWS);
   int64_t s = 1;
   while (blocks * s < 256 && K / (2 * s) >= 1024 && s < 16) s *= 2;
-  return s;
+  return full_rounds(blocks, s, 256, 256.0 / (double)K, [&](int64_t t) {
+    return t == 1 || (K / t >= 1024 && t <= 32 && (t <= s || t * M <= ((int64_t)1 << 21)));
+  });
 }
 
 bool gemm_lp_reads_a(int64_t M, int64_t ldx) { return M >= 4 && ldx < TN_MAX_LD; }
