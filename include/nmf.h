@@ -118,9 +118,10 @@ typedef struct {
                      /* large products then stream A row by row); -1 never   */
                      /* does. NMF_F32 products read A itself in both         */
                      /* directions and take either value.                    */
-                     /* NMF_BF16 and NMF_FP8_E4M3 A always need the copy: */
-                     /* -1 is rejected and                                  */
-                     /* a copy that does not fit returns NMF_ENOMEM          */
+                     /* NMF_BF16 and NMF_FP8_E4M3 take 0 only; their products*/
+                     /* read A itself too, except that one of fewer than 4   */
+                     /* columns or a row pitch of 2^24 or more is copied     */
+                     /* (NMF_ENOMEM where the copy does not fit)             */
   double tol;        /* tolerance of the stopping test (>= 0)                */
   int stop;          /* nmf_stop. Section 6.2: the iteration count together  */
                      /* with a tolerance on a quality metric. With a metric, */
@@ -145,7 +146,7 @@ typedef struct {
    * Each passive-set solve eliminates the smaller of two equivalent systems
    * (ns unknowns, ns <= 32); four right-hand sides share a wavefront and
    * eliminate together at the size of the largest of them, rounded up to a
-   * size class (8, 12, 16, 20, 24, 28 or 32). */
+   * size class (8, 12, 16, 18, 20, ..., 30 or 32). */
   long long bpp_solves;       /* eliminations performed                    */
   double bpp_flops;           /* their algorithmic flops: ns^3 - ns (Gauss- */
                               /* Jordan, one right-hand side) + 2 k ns (the */
@@ -232,8 +233,8 @@ nmf_status nmf_dense_AF(nmf_ctx* ctx, nmf_dtype dtype, int64_t m, int64_t n,
 
 /* R = A^T F for dense A (m x n, lda) and F (m x k, ldf): with F = W this is
  * (W^T A)^T of the H update. Output R is n x k (leading dimension k).
- * NMF_BF16 and NMF_FP8_E4M3 as for nmf_dense_AF (the call makes a
- * transposed copy of A). */
+ * NMF_BF16 and NMF_FP8_E4M3 as for nmf_dense_AF (A of fewer than 4 columns
+ * or a row pitch of 2^24 or more is copied transposed for the call). */
 nmf_status nmf_dense_AtF(nmf_ctx* ctx, nmf_dtype dtype, int64_t m, int64_t n,
                          const void* A, int64_t lda, int k, const void* F,
                          int64_t ldf, void* R);

@@ -44,7 +44,7 @@
 // elimination per form, a wavefront whose rows were of both forms ran two.
 // 200,000 rows at half-full supports, a sweep: k = 40 580 -> 460 us, k = 48
 // 750 -> 513, k = 64 1507 -> 748; 1,048,576 rows at k = 50 with few rows in
-// the active form 5.05 -> 4.86 ms.
+// the active form, both factors: 6.62 -> 6.48 ms.
 // ===========================================================================
 namespace nmfk {
 
@@ -208,14 +208,14 @@ __device__ __forceinline__ void solve_rows(const double* __restrict__ M, const i
   product_steps<KP>(std::make_integer_sequence<int, NS>{}, M, fi, xs, nsm, li, acc);
 }
 
-// The size an elimination of at most nsm unknowns runs at (solve_pass). Few
-// classes: each is some 1000 instructions, and the kernel's code has to fit
-// the instruction cache.
+// The size an elimination of at most nsm unknowns runs at (solve_pass): every
+// second size above 16. Steps of four there pad more than the smaller code
+// saves (1,048,576 rows at k = 50, both factors: 6.65 against 6.48 ms).
 __device__ __forceinline__ int bpp_size_class(int nsm, int KP) {
   if (nsm <= 8) return 8;
   if (nsm <= 12) return 12;
   if (nsm <= 16 || KP <= 16) return 16;
-  return (nsm + 3) & ~3;   // 20, 24, 28, 32
+  return (nsm + 1) & ~1;   // 18, 20, ..., 32
 }
 
 // One elimination pass over the rows with ns > 0 at the size class of nsm, the
@@ -229,9 +229,13 @@ __device__ __forceinline__ void solve_pass(const double* __restrict__ M, const i
   if (nsm <= 8) NMF_BPP_CLASS(8);
   else if (nsm <= 12) NMF_BPP_CLASS(12);
   else if (nsm <= 16 || KP <= 16) NMF_BPP_CLASS(16);
+  else if (nsm <= 18) NMF_BPP_CLASS(18);
   else if (nsm <= 20) NMF_BPP_CLASS(20);
+  else if (nsm <= 22) NMF_BPP_CLASS(22);
   else if (nsm <= 24) NMF_BPP_CLASS(24);
+  else if (nsm <= 26) NMF_BPP_CLASS(26);
   else if (nsm <= 28) NMF_BPP_CLASS(28);
+  else if (nsm <= 30) NMF_BPP_CLASS(30);
   else NMF_BPP_CLASS(32);
 #undef NMF_BPP_CLASS
 }
