@@ -9,13 +9,13 @@ with A resident in HBM. Prints one JSON line.
   python bench.py [--steps K] [--warmup W] [--gpus 1] [--workload NAME]
                   [--no-cpu-baseline] [--sample-rows R]
 
-roofline: the dominant kernels are the two large products (A H^T and W^T A,
-2 m n k algorithmic flops per launch, k unpadded). Their average launch time
-comes from the library's hipEvents on the stream the kernels run on;
-achieved = 2 m n k / that time, against the FP32 matrix peak. traffic is the
-HBM byte count per launch from the committed rocprofv3 counter summary,
-reported only while the product kernel source is unchanged since the counters
-were taken.
+roofline: the dominant kernels are the two large products (A H^T and W^T A).
+Their average launch time comes from the library's hipEvents on the stream the
+kernels run on; achieved = the bytes of A / that time, against the HBM peak
+(the float products run on the bfloat16 matrix cores, whose peak is far above
+that); tflops is 2 m n k / that time. traffic is the HBM byte count per launch
+from the committed rocprofv3 counter summary, reported only while the product
+kernel source is unchanged since the counters were taken.
 
 cpu_baseline: the FP64 oracle (tests only, never the product path) timed on
 the host for three iterations of the same algorithm on the workload's own
@@ -399,9 +399,9 @@ def run_lowp(args, wl):
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": traffic,
-                     "kernel": ("gemm_lp_nt_kernel<uint16_t> (A H^T and A^T W, BF16 MFMA "
+                     "kernel": ("gemm_lp_kernel<uint16_t> (A H^T and A^T W, BF16 MFMA "
                                 "16x16x32)" if lp == "bf16" else
-                                "gemm_lp_nt_kernel<uint8_t> (A H^T and A^T W, FP8 MFMA "
+                                "gemm_lp_kernel<uint8_t> (A H^T and A^T W, FP8 MFMA "
                                 "16x16x128)"),
                      "ms_per_launch": round(ms_launch, 4),
                      "algorithmic_bytes_per_launch": bytes_launch,

@@ -12,7 +12,7 @@ import sqlite3
 import sys
 
 
-def summarize(db, out, title, command, top=14, patterns=("gemm_tn_kernel", "gemm_nn_kernel")):
+def summarize(db, out, title, command, top=14, patterns=("gemm_split_kernel", "gemm_tn_kernel")):
     con = sqlite3.connect(db)
     cur = con.cursor()
     rows = list(cur.execute("select name, total_calls, total_duration, average, percentage "
@@ -81,6 +81,6 @@ if __name__ == "__main__":
         print(traffic(sys.argv[2], sys.argv[3], sys.argv[4], sys.argv[5], sys.argv[6],
                       int(sys.argv[7]), sys.argv[8]))
     else:
-        pats = tuple(sys.argv[5].split(",")) if len(sys.argv) > 5 else ("gemm_tn_kernel",
-                                                                         "gemm_nn_kernel")
+        pats = tuple(sys.argv[5].split(",")) if len(sys.argv) > 5 else ("gemm_split_kernel",
+                                                                         "gemm_tn_kernel")
         summarize(*sys.argv[1:5], patterns=pats)
