@@ -859,7 +859,10 @@ LpPlan lp_plan(int lp, int64_t m, int64_t n, int KP) {
   LpPlan p;
   const int64_t esize = lp == NMF_FP8_E4M3 ? 1 : 2;
   p.fb_bytes = (int64_t)KP * round_up(std::max(m, n), lp_align(lp)) * esize;
-  const int64_t sp = nmfk::gemm_lp_splits(m, n), sr = nmfk::gemm_lp_splits(n, m);
+  // A^T W may take either form (the copied A runs as A H^T does)
+  const int64_t sp = nmfk::gemm_lp_splits(false, (int)esize, m, KP, n);
+  const int64_t sr = std::max(nmfk::gemm_lp_splits(false, (int)esize, n, KP, m),
+                              nmfk::gemm_lp_splits(true, (int)esize, n, KP, m));
   p.part_elems = std::max<int64_t>(sp > 1 ? sp * m * KP : 0, sr > 1 ? sr * n * KP : 0);
   return p;
 }

@@ -24,8 +24,8 @@
 // 1.71 -> 1.39 ms a product, bfloat16 3.35 -> 2.86.
 //
 // A^T W (TN) has the output side contiguous: for the same K values lane (g, c)
-// reads four neighbouring columns of each row, one column for each of its
-// tiles, and regroups the values of four columns from along the row to along K
+// reads four (or eight, lp_wide) neighbouring columns of each row, one column
+// for each of its tiles, and regroups the values of four columns from along the row to along K
 // in registers (v_perm_b32: one per two bfloat16 values, one per two FP8
 // values). No transposed copy of A is made: at 24000 x 16400 bfloat16 that
 // copy took 360 of the call's 569 us, and it held as much memory again as A.
@@ -87,19 +87,22 @@ constexpr int BWAVES = 4;      // waves per workgroup
 
 template <int MT> struct XFrag { u32x4 v[MT][2]; };
 
-// Four neighbouring elements of a row, at any alignment.
-template <typename TE> struct Run4;
-template <> struct Run4<uint16_t> {
+// MT neighbouring elements of a row, at any alignment.
+template <typename TE, int MT> struct Run;
+template <> struct Run<uint16_t, 4> {
   typedef unsigned V __attribute__((ext_vector_type(2), aligned(2)));
 };
-template <> struct Run4<uint8_t> {
-  typedef unsigned V __attribute__((aligned(1)));
+template <> struct Run<uint8_t, 4> {
+  typedef unsigned V __attribute__((ext_vector_type(1), aligned(1)));
+};
+template <> struct Run<uint8_t, 8> {
+  typedef unsigned V __attribute__((ext_vector_type(2), aligned(1)));
 };
 
 // The operands of four tiles from runs of four columns: r[q] is row q of the
 // lane's K values (16 rows for bfloat16, 32 for FP8); tile t's operand holds
 // column t along K.
-__device__ __forceinline__ void regroup(const Run4<uint16_t>::V (&r)[16], XFrag<4>& f) {
+__device__ __forceinline__ void regroup(const Run<uint16_t, 4>::V (&r)[16], XFrag<4>& f) {
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -110,11 +113,13 @@ __device__ __forceinline__ void regroup(const Run4<uint16_t>::V (&r)[16], XFrag<
         f.v[t][h][i] = __builtin_amdgcn_perm(b, a, (t & 1) ? 0x07060302u : 0x05040100u);
       }
 }
-__device__ __forceinline__ void regroup(const Run4<uint8_t>::V (&r)[32], XFrag<4>& f) {
+// FP8: the operands of tiles 4 H .. 4 H + 3.
+template <int H, typename V>
+__device__ __forceinline__ void regroup(const V (&r)[32], XFrag<4>& f) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    // bytes (rows 4 q .. 4 q + 3) x (columns 0 .. 3), transposed
-    const unsigned a = r[4 * q], b = r[4 * q + 1], c = r[4 * q + 2], d = r[4 * q + 3];
+    // bytes (rows 4 q .. 4 q + 3) x (columns 4 H .. 4 H + 3), transposed
+    const unsigned a = r[4 * q][H], b = r[4 * q + 1][H], c = r[4 * q + 2][H], d = r[4 * q + 3][H];
     const unsigned ab0 = __builtin_amdgcn_perm(b, a, 0x05010400u);  // a0 b0 a1 b1
     const unsigned ab1 = __builtin_amdgcn_perm(b, a, 0x07030602u);  // a2 b2 a3 b3
     const unsigned cd0 = __builtin_amdgcn_perm(d, c, 0x05010400u);
@@ -146,7 +151,7 @@ __device__ __forceinline__ void unpair(const XFrag<MT>& x, XFrag<MT>& f) {
 // NT 16-column tiles (N = 16 NT), MT 16-row tiles per wave, STAGES K steps of
 // X in registers (STAGES - 1 in flight while one is multiplied), WPE waves per
 // SIMD to leave room for. FP8 outputs: column j is multiplied by colscale[j].
-// TR: X is given as its transpose (K x M, ldx between its rows), M >= 4 and
+// TR: X is given as its transpose (K x M, ldx between its rows), M >= MT and
 // ldx < TN_MAX_LD, so that a lane's offset within a step fits 32 bits.
 constexpr int64_t TN_MAX_LD = (int64_t)1 << 24;
 template <typename TE, int NT, bool TR, int MT, int STAGES, int WPE>
@@ -174,15 +179,14 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
   const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
   D += (int64_t)blockIdx.y * dsplit;
 
-  // TR: columns col0 .. col0 + 3, moved back where they would pass the last
-  // one (two lanes then hold, and store, the same column)
-  static_assert(!TR || MT == 4, "TN lanes take four columns");
-  typedef typename Run4<TE>::V RunV;
+  // TR: columns col0 .. col0 + MT - 1, moved back where they would pass the
+  // last one (two lanes then hold, and store, the same column)
+  typedef typename Run<TE, TR ? MT : 4>::V RunV;
   const TE* xr[TR ? 1 : MT][2];
   uint32_t xo = 0;   // TR: the lane's offset from the (uniform) step rows
   if constexpr (TR) {
-    int64_t col0 = m0 + 4 * c;
-    col0 = col0 < M - 4 ? col0 : M - 4;
+    int64_t col0 = m0 + MT * c;
+    col0 = col0 < M - MT ? col0 : M - MT;
     xo = (uint32_t)((int64_t)(LE * g) * ldx + col0);
   } else {
 #pragma unroll
@@ -239,33 +243,47 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
       *reinterpret_cast<u32x4*>(&Ys[buf][r * YLD + VE * ych]) = v[p];
     }
   };
-  auto multiply = [&](const XFrag<MT>& f, int buf) {
+  // tiles t0 .. of the wave times the slice in buf
+  auto multiply = [&](const auto& f, int buf, auto t0) {
+    constexpr int T0 = decltype(t0)::value, N = sizeof(f.v) / sizeof(f.v[0]);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const TE* yp = &Ys[buf][(16 * j + c) * YLD + LE * g];
       const u32x4 b0 = *reinterpret_cast<const u32x4*>(yp);
       const u32x4 b1 = *reinterpret_cast<const u32x4*>(yp + VE);
 #pragma unroll
-      for (int t = 0; t < MT; ++t) {
+      for (int t = 0; t < N; ++t) {
         if constexpr (FP8) {
           // operand formats 0 (E4M3) and no block scales: a plain FP8 product
-          acc[t][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-              join32(f.v[t][0], f.v[t][1]), join32(b0, b1), acc[t][j], 0, 0, 0, 0, 0, 0);
+          acc[T0 + t][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+              join32(f.v[t][0], f.v[t][1]), join32(b0, b1), acc[T0 + t][j], 0, 0, 0, 0, 0, 0);
         } else {
-          acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.v[t][0]),
-                                                              as_bf16x8(b0), acc[t][j], 0, 0, 0);
-          acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.v[t][1]),
-                                                              as_bf16x8(b1), acc[t][j], 0, 0, 0);
+          acc[T0 + t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.v[t][0]),
+                                                              as_bf16x8(b0), acc[T0 + t][j], 0, 0, 0);
+          acc[T0 + t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.v[t][1]),
+                                                              as_bf16x8(b1), acc[T0 + t][j], 0, 0, 0);
         }
       }
     }
   };
 
+  typedef std::integral_constant<int, 0> First;
+  typedef std::integral_constant<int, 4> Second;
   auto compute = [&](const XStep& x, int buf) {
-    XFrag<MT> f;
-    if constexpr (TR) regroup(x.r, f);
-    else unpair(x, f);
-    multiply(f, buf);
+    if constexpr (TR) {
+      XFrag<4> f;
+      if constexpr (FP8) regroup<0>(x.r, f);
+      else regroup(x.r, f);
+      multiply(f, buf, First{});
+      if constexpr (MT == 8) {
+        regroup<1>(x.r, f);
+        multiply(f, buf, Second{});
+      }
+    } else {
+      XFrag<MT> f;
+      unpair(x, f);
+      multiply(f, buf, First{});
+    }
   };
 
   // Memory loads complete in issue order as far as the wait counter is
@@ -341,7 +359,7 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
       Ys[0][r * YLD + kk] = (kt + kk < kend) ? Y[(int64_t)r * ldy + kt + kk] : (TE)0;
     }
     __syncthreads();
-    multiply(f, 0);
+    multiply(f, 0, First{});
   }
   // store: element r of tile (t, j) is row 4 g + r, column c
   float cs[NT];
@@ -351,10 +369,10 @@ __global__ __launch_bounds__(64 * BWAVES, WPE) void gemm_lp_kernel(
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      int64_t row = TR ? m0 + 4 * (4 * g + r) : m0 + 16 * t + 4 * g + r;
+      int64_t row = TR ? m0 + MT * (4 * g + r) : m0 + 16 * t + 4 * g + r;
       bool in = row < M;
       if constexpr (TR) {
-        row = (row < M - 4 ? row : M - 4) + t;
+        row = (row < M - MT ? row : M - MT) + t;
         in = m0 < M;
       }
       if (in) {
@@ -493,17 +511,26 @@ hipError_t pack_fp8_t(const float* F, int64_t rows, int KP, uint8_t* Ft, int64_t
 }
 
 constexpr int B_MT = 4, B_STAGES = 4, B_WPE = 1;  // launch shape (timing sweep at 131072 x 65536, k = 100)
-constexpr int BROWS = 16 * B_MT * BWAVES;
+// FP8 A^T W: eight columns a lane, so that a load takes whole lines of A (a
+// wave of four columns a lane reads 64 bytes of a row), and two stages (a
+// stage holds twice the bytes). 131072 x 65536 at k = 50: 1807 -> 1320 us, 24000 x
+// 16400 176 -> 131. The accumulators are twice as many too: from 96 columns on
+// they spill (k = 100: 1990 us with four columns a lane, 2228 with eight), and
+// a small A has too few workgroups of 512 columns.
+static bool lp_wide(bool tn, int esize, int64_t M, int N, int64_t K) {
+  return tn && esize == 1 && N <= 80 && M >= 512 && M * K >= ((int64_t)1 << 28);
+}
 
 // One workgroup per CU and round, slabs of at least 1024, at most 2^21 rows of
 // them (1 GB at the largest rank). A slab's cost is taken at rank 64 and
 // bfloat16. bfloat16, 24000 x 16400 at k = 50, A^T W: 7 slabs for 4, 240 -> 199 us;
 // 100000 x 4800 249 -> 180; 20000^2 at k = 100 274 -> 200 and A H^T 295 -> 220 (FP8
 // 222 -> 168 and 205 -> 162).
-int64_t gemm_lp_splits(int64_t M, int64_t K) {
-  const int64_t blocks = cdiv(M, BROWS);
+int64_t gemm_lp_splits(bool tn, int esize, int64_t M, int N, int64_t K) {
+  const bool wide = lp_wide(tn, esize, M, N, K);
+  const int64_t blocks = cdiv(M, 16 * (wide ? 8 : B_MT) * BWAVES);
   int64_t s = 1;
-  while (blocks * s < 256 && K / (2 * s) >= 1024 && s < 16) s *= 2;
+  while (blocks * s < 256 && K / (2 * s) >= 1024 && s < (wide ? 32 : 16)) s *= 2;
   return full_rounds(blocks, s, 256, 256.0 / (double)K, [&](int64_t t) {
     return t == 1 || (K / t >= 1024 && t <= 32 && (t <= s || t * M <= ((int64_t)1 << 21)));
   });
@@ -520,16 +547,23 @@ static hipError_t gemm_lp(bool tn, const TE* X, int64_t ldx, const TE* Y, int64_
   if (M <= 0) return hipSuccess;
   if (N % 16 != 0 || N < 16 || N > 128 || ldx % VE != 0 || ldy % VE != 0 || (tn && !gemm_lp_reads_a(M, ldx)))
     return hipErrorInvalidValue;
-  const int64_t splits = gemm_lp_splits(M, K);
+  const bool wide = lp_wide(tn, sizeof(TE), M, N, K);
+  const int64_t splits = gemm_lp_splits(tn, sizeof(TE), M, N, K);
   const int64_t kchunk = round_up(cdiv(K, splits), BK);
   const int64_t nsplit = cdiv(K, kchunk);
   float* out = nsplit > 1 ? part : D;
   const int64_t ldo = nsplit > 1 ? N : ldd;
   const int64_t dsplit = (int64_t)M * N;
-  dim3 grid((unsigned)cdiv(M, BROWS), (unsigned)nsplit);
+  dim3 grid((unsigned)cdiv(M, 16 * (wide ? 8 : B_MT) * BWAVES), (unsigned)nsplit);
   const int NT = N / 16;
 #define CASE(J)                                                                            \
   case J:                                                                                  \
+    if constexpr (sizeof(TE) == 1 && J <= 5)                                               \
+      if (wide) {                                                                          \
+        gemm_lp_kernel<TE, J, true, 8, 2, B_WPE><<<grid, 64 * BWAVES, 0, st>>>(            \
+            X, ldx, Y, ldy, colscale, out, ldo, dsplit, M, K, kchunk);                     \
+        break;                                                                             \
+      }                                                                                    \
     if (tn)                                                                                \
       gemm_lp_kernel<TE, J, true, B_MT, B_STAGES, B_WPE><<<grid, 64 * BWAVES, 0, st>>>(    \
           X, ldx, Y, ldy, colscale, out, ldo, dsplit, M, K, kchunk);                       \

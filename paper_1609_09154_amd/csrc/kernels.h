@@ -76,14 +76,14 @@ inline int64_t split_floats(int64_t rows, int KP) { return (rows + 31) / 32 * 48
 // bfloat16 bits (uint16_t) or FP8 E4M3 bits (uint8_t), rows 16-byte aligned,
 // ldx and ldy whole multiples of 16 bytes, N a multiple of 16 up to 128, float
 // accumulation. The FP8 form multiplies output column j by colscale[j]. `part`
-// must hold gemm_lp_splits(M, K) * M * N floats when that count exceeds 1.
+// must hold gemm_lp_splits(...) * M * N floats when that count exceeds 1.
 hipError_t gemm_bf16(bool tn, const uint16_t* X, int64_t ldx, const uint16_t* Y, int64_t ldy,
                      float* D, int64_t ldd, int64_t M, int N, int64_t K, float* part,
                      hipStream_t st);
 hipError_t gemm_fp8(bool tn, const uint8_t* X, int64_t ldx, const uint8_t* Y, int64_t ldy,
                     const float* colscale, float* D, int64_t ldd, int64_t M, int N, int64_t K,
                     float* part, hipStream_t st);
-int64_t gemm_lp_splits(int64_t M, int64_t K);
+int64_t gemm_lp_splits(bool tn, int esize, int64_t M, int N, int64_t K);
 // Whether the tn form takes these sizes (else the caller transposes A).
 bool gemm_lp_reads_a(int64_t M, int64_t ldx);
 // Ft (KP x rows, row pitch ldt) = F^T rounded to bfloat16 (nearest even), for

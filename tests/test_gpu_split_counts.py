@@ -1,5 +1,6 @@
 """Products whose slab count is chosen to fill the last round of workgroups
-(counts that are no power of two), each format and direction, against a double
+(counts that are no power of two), and FP8 A^T W with eight columns a lane (from
+2^28 entries of A and 512 columns on), each format and direction, against a double
 product of the same stored entries."""
 import numpy as np
 import pytest
@@ -13,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dt,m,n,k", [("f32", 8191, 6007, 100), ("f32", 16700, 9001, 50),
                                       ("f64", 9000, 7000, 20), ("f64", 6007, 8191, 100),
-                                      ("bf16", 16400, 9000, 50), ("fp8", 16400, 9008, 20)])
+                                      ("bf16", 16400, 9000, 50), ("fp8", 16400, 9008, 20),
+                                      ("fp8", 16400, 16416, 20), ("fp8", 32783, 8208, 80),
+                                      ("fp8", 524301, 512, 33)])
 def test_balanced_slab_counts(dt, m, n, k):
     gen = torch.Generator(device="cuda").manual_seed(m + n + k)
     fd = torch.float64 if dt == "f64" else torch.float32
