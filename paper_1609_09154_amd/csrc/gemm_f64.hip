@@ -211,14 +211,14 @@ template <typename T, int NT, int MW> struct FragTN {
   T y[4][NT];
 };
 
-// SYM (Grams of up to 64 columns): Y is X and one wave takes all columns, so
+// SYM 1 (Grams of up to 64 columns): Y is X and one wave takes all columns, so
 // the fragment of X serves as Y too, in the same order of columns on either
 // side of the output (the Y side read every row again, a float per lane and
-// load), and only the tiles on and above the diagonal are computed (the sums
+// load). SYM 2: only the tiles on and above the diagonal are computed (the sums
 // of the others are the same term by term). 11,708,841 rows at KP = 64: float
 // 1.10 ms before, 0.99 with the shared fragment, 0.70 with those tiles only;
 // double 1.68, 1.54, 1.14.
-template <typename T, int NT, int MW, bool VX, bool YT, int STAGES, int WPE, bool STREAM, bool SYM>
+template <typename T, int NT, int MW, bool VX, bool YT, int STAGES, int WPE, bool STREAM, int SYM>
 __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
     const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t ldy,
     T* __restrict__ D, int64_t ldd, int64_t dsplit, int64_t M, int64_t K,
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
   {                                                                           \
     _Pragma("unroll") for (int u = 0; u < 4; ++u)                             \
       _Pragma("unroll") for (int t = 0; t < MW; ++t) {                        \
-        _Pragma("unroll") for (int nt = SYM ? t : 0; nt < NT; ++nt)           \
+        _Pragma("unroll") for (int nt = SYM == 2 ? t : 0; nt < NT; ++nt)      \
           acc[t][nt] = mfma16(F.x[u][t], SYM ? F.x[u][nt % MW] : F.y[u][nt],  \
                               acc[t][nt]);                                    \
       }                                                                       \
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
 #pragma unroll
     for (int t = 0; t < MW; ++t) {
 #pragma unroll
-      for (int nt = SYM ? t : 0; nt < NT; ++nt)
+      for (int nt = SYM == 2 ? t : 0; nt < NT; ++nt)
         acc[t][nt] = mfma16(fr[0].x[0][t], SYM ? fr[0].x[0][nt % MW] : fr[0].y[0][nt], acc[t][nt]);
     }
   }
@@ -320,10 +320,10 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
       const int rho = acc_row<T>(lane, r);
       const int64_t row = tn_col<T, VX>(m0, t, rho, M);
 #pragma unroll
-      for (int nt = SYM ? t : 0; nt < NT; ++nt) {
+      for (int nt = SYM == 2 ? t : 0; nt < NT; ++nt) {
         const int64_t col = SYM ? tn_col<T, VX>(0, nt, c, M) : 16 * nt + c;
         Dp[row * ldd + col] = acc[t][nt][r];
-        if (SYM && nt > t) Dp[col * ldd + row] = acc[t][nt][r];
+        if (SYM == 2 && nt > t) Dp[col * ldd + row] = acc[t][nt][r];
       }
     }
 }
@@ -471,13 +471,18 @@ static void tn_launch(const GemmArgs<T>& a, int waves, int64_t splits, int64_t k
   constexpr int S = prod_stages(NT, MW);
   const dim3 grid((unsigned)cdiv(a.M, 16 * MW * waves), (unsigned)splits);
   if (a.yt)
-    gemm_tn_kernel<T, NT, MW, VX, true, S, tn_wpe(NT), STREAM, false><<<grid, 64 * waves, 0, st>>>(
+    gemm_tn_kernel<T, NT, MW, VX, true, S, tn_wpe(NT), STREAM, 0><<<grid, 64 * waves, 0, st>>>(
         a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
   else
-    gemm_tn_kernel<T, NT, MW, VX, false, S, tn_wpe(NT), STREAM, false><<<grid, 64 * waves, 0, st>>>(
+    gemm_tn_kernel<T, NT, MW, VX, false, S, tn_wpe(NT), STREAM, 0><<<grid, 64 * waves, 0, st>>>(
         a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
 }
 
+// Gram slabs compute half the tiles (SYM 2), float ones from GRAM_HALF rows on:
+// shorter ones do not repay the scattered stores of the other half (200,000 rows at
+// KP = 64, 196 a slab: float 27 us with all tiles, 31 with half, double 45 and 36;
+// 1,048,576 rows, 1024 a slab: float 79 and 67).
+constexpr int64_t GRAM_HALF = 512;
 // Gram: the M side is the padded rank itself, one wave per 16 MW columns; its
 // operands are rows of the workspace, always aligned.
 template <typename T, int NT>
@@ -485,9 +490,13 @@ static void gram_launch(const GemmArgs<T>& a, int64_t splits, int64_t kchunk, T*
                         int64_t dsplit, hipStream_t st) {
   constexpr int MW = sizeof(T) == 8 && NT > 4 ? 2 : NT <= 4 ? NT : 4;
   const dim3 grid((unsigned)cdiv(a.M, 16 * MW), (unsigned)splits);
-  gemm_tn_kernel<T, NT, MW, MW % Tr<T>::VEC == 0, false, 2, sizeof(T) == 8 ? 1 : 2, false, MW == NT>
-      <<<grid, 64, 0, st>>>(
-      a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+  constexpr int WPE = sizeof(T) == 8 ? 1 : 2;
+  if (MW == NT && (sizeof(T) == 8 || kchunk >= GRAM_HALF))
+    gemm_tn_kernel<T, NT, MW, MW % Tr<T>::VEC == 0, false, 2, WPE, false, MW == NT ? 2 : 0>
+        <<<grid, 64, 0, st>>>(a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
+  else
+    gemm_tn_kernel<T, NT, MW, MW % Tr<T>::VEC == 0, false, 2, WPE, false, MW == NT ? 1 : 0>
+        <<<grid, 64, 0, st>>>(a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
 }
 
 // TN streams A past the caches (non-temporal loads) where A is larger than the
