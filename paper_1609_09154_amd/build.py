@@ -11,7 +11,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["hals_f32.hip", "hals_f64.hip", "bpp.hip", "gemm.hip", "update.hip", "gemm_f64.hip", "autograd.hip",
+SOURCES = ["hals_f32.hip", "hals_f64.hip", "bpp.hip", "gemm.hip", "update.hip", "gemm_f64.hip", "gemm_f32.hip", "autograd.hip",
            "gemm_bf16.hip", "objective.hip", "sparse.hip", "api.hip"]
 LIB_NAME = "libnmf_mi355x.so"
 ARCH = "gfx950"

@@ -348,15 +348,37 @@ nmf_status local_update(nmf_ctx* ctx, int algo, T* X, nmfk::Split<T> P, const T*
 }
 
 // The copy of a rows x KP factor that a dense product reads: its packed
-// bfloat16 planes for float (every float product needs them), its transpose
-// for double.
+// bfloat16 planes for float (every float product but gemm_f32's needs them),
+// its transpose for double and gemm_f32.
 template <typename T> int64_t copy_elems(int64_t rows, int KP) {
   return sizeof(T) == 4 ? nmfk::split_floats(rows, KP) : rows * KP;
 }
 template <typename T>
-hipError_t factor_copy(const T* X, int64_t rows, int KP, T* dst, hipStream_t st) {
-  if constexpr (sizeof(T) == 4) return nmfk::pack_split(X, rows, KP, KP, KP, dst, st);
-  else return nmfk::transpose_rows<T>(X, rows, KP, dst, st);
+hipError_t factor_copy(const T* X, int64_t rows, int KP, T* dst, hipStream_t st,
+                       nmfk::FactorCopy copy = nmfk::FactorCopy::PLANES) {
+  if constexpr (sizeof(T) == 4)
+    if (copy == nmfk::FactorCopy::PLANES) return nmfk::pack_split(X, rows, KP, KP, KP, dst, st);
+  return nmfk::transpose_rows<T>(X, rows, KP, dst, st);
+}
+
+// Slabs of a rows x KP product of A or A^T with `red` terms: of the general
+// kernels and, f32, of gemm_f32's.
+template <typename T>
+int64_t product_splits(nmfk::GemmKind kind, int64_t rows, int KP, int64_t red, bool f32) {
+  const int64_t s = nmfk::gemm_auto_splits<T>(kind, rows, KP, red);
+  if (sizeof(T) == 8 || !f32) return s;
+  return std::max(s, nmfk::gemm_f32_splits(kind, rows, KP, red));
+}
+
+// Whether nmf_dense forms the products of a float HALS iteration with the float
+// instruction, as the unrolled layer does at every size (gemm_f32.hip says why).
+// Up to 2^16 entries of A both then give the same factors bit for bit, which a
+// program that checks one against the other on a small case relies on, for a run
+// of ten iterations on 300 x 200 at k = 10 in 513 us instead of 430; past it the
+// bfloat16 splits are worth more than the last bits (2000 x 1000 at k = 50: 2180
+// us a run against 782, 65536^2 87 ms against 66).
+bool f32_sums(int algo, int64_t m, int64_t n, int KP) {
+  return algo == NMF_HALS && KP <= 64 && m * n <= ((int64_t)1 << 16);
 }
 
 template <typename T>
@@ -372,9 +394,11 @@ template <typename T>
 size_t plan_work(int64_t m, int64_t n, int KP, int iters, int64_t obj_np, int64_t extra_part,
                  Carve& cv, size_t off[18], bool sparse = false) {
   // split partials of the dense products (the sparse products use none)
-  const int64_t ps_p = sparse ? 1 : std::max(nmfk::gemm_auto_splits<T>(nmfk::GemmKind::NN, m, KP, n),
-                                             nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, m, KP, n));
-  const int64_t ps_r = sparse ? 1 : nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, n, KP, m);
+  const bool f32 = f32_sums(NMF_HALS, m, n, KP);
+  const int64_t ps_p =
+      sparse ? 1 : std::max(product_splits<T>(nmfk::GemmKind::NN, m, KP, n, f32),
+                            product_splits<T>(nmfk::GemmKind::TN, m, KP, n, f32));
+  const int64_t ps_r = sparse ? 1 : product_splits<T>(nmfk::GemmKind::TN, n, KP, m, f32);
   int64_t part = ps_p > 1 ? ps_p * m * KP : 0;
   part = std::max<int64_t>(part, ps_r > 1 ? ps_r * n * KP : 0);
   part = std::max<int64_t>(part, gram_splits(std::max(m, n)) * KP * KP);
@@ -451,6 +475,7 @@ template <typename T> struct Prob {
   bool sparse = false;
   const T* A = nullptr; int64_t lda = 0;                 // dense
   const T* At = nullptr;                                 // dense A^T (n x m, ld m) or null
+  bool f32 = false;   // float A: products by gemm_f32 (else by gemm_split)
   // Reduced-precision A (T = float): lp is NMF_BF16 (bfloat16 bits) or
   // NMF_FP8_E4M3 (FP8 bits), 0 for none. Alp is A (m x n, lda), Alpt its
   // transposed copy (n x m, row pitch ldat); fb holds the packed factor and,
@@ -491,8 +516,16 @@ nmf_status lp_product(nmf_ctx* ctx, const Prob<float>& pb, bool tn, const void* 
   return NMF_OK;
 }
 
-// Ft is the factor's copy (factor_copy): float dense products need it; double
-// ones (nullable there) then read the rank side with 16-byte loads.
+template <typename T>
+hipError_t run_product(nmfk::GemmKind kind, const nmfk::GemmArgs<T>& a, int k, T* part,
+                       hipStream_t st, int* nsplit) {
+  if constexpr (sizeof(T) == 4) return nmfk::gemm_f32(kind, a, k, part, st, nsplit);
+  else return nmfk::gemm_run<T>(kind, a, 0, part, st, nsplit);
+}
+
+// Ft is the factor's copy (factor_copy): gemm_split needs the planes; double
+// products and gemm_f32 (nullable there) then read the rank side with 16-byte
+// loads.
 template <typename T>
 nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F,
                       const T* Ft, int k, int KP, T* Pout, T* part, int* nsplit = nullptr) {
@@ -509,24 +542,24 @@ nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, con
     if constexpr (sizeof(T) == 4) return lp_product(ctx, pb, false, pb.Alp, pb.lda, m, n, F, KP, Pout, part);
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
-  if constexpr (sizeof(T) == 4) {
-    if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
-    HIP_TRY(nmfk::gemm_split(false, pb.A, pb.lda, Ft, F, KP, KP, k, Pout, KP, KP, m, KP, n, part,
-                             ctx->stream, nsplit));
-    return NMF_OK;
-  } else {
-    if (pb.At) {
-      // A H^T = (A^T)^T H^T: the TN kernel streaming A^T row by row.
-      nmfk::GemmArgs<T> a{pb.At, m, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
-                          Ft != nullptr};
-      HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
+  if constexpr (sizeof(T) == 4)
+    if (!pb.f32) {
+      if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
+      HIP_TRY(nmfk::gemm_split(false, pb.A, pb.lda, Ft, F, KP, KP, k, Pout, KP, KP, m, KP, n, part,
+                               ctx->stream, nsplit));
       return NMF_OK;
     }
-    nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
+  if (pb.At) {
+    // A H^T = (A^T)^T H^T: the TN kernel streaming A^T row by row.
+    nmfk::GemmArgs<T> a{pb.At, m, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
                         Ft != nullptr};
-    HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::NN, a, 0, part, ctx->stream, nsplit));
+    HIP_TRY(run_product<T>(nmfk::GemmKind::TN, a, k, part, ctx->stream, nsplit));
     return NMF_OK;
   }
+  nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
+                      Ft != nullptr};
+  HIP_TRY(run_product<T>(nmfk::GemmKind::NN, a, k, part, ctx->stream, nsplit));
+  return NMF_OK;
 }
 
 template <typename T>
@@ -548,17 +581,17 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
     }
     return fail(ctx, NMF_EINVAL, "reduced-precision A takes float factors");
   }
-  if constexpr (sizeof(T) == 4) {
-    if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
-    HIP_TRY(nmfk::gemm_split(true, pb.A, pb.lda, Ft, F, KP, KP, k, Rout, KP, KP, n, KP, m, part,
-                             ctx->stream, nsplit));
-    return NMF_OK;
-  } else {
-    nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? m : (int64_t)KP, Rout, KP, n, KP, m,
-                        Ft != nullptr};
-    HIP_TRY(nmfk::gemm_run<T>(nmfk::GemmKind::TN, a, 0, part, ctx->stream, nsplit));
-    return NMF_OK;
-  }
+  if constexpr (sizeof(T) == 4)
+    if (!pb.f32) {
+      if (!Ft) return fail(ctx, NMF_EINVAL, "float product without the factor's planes");
+      HIP_TRY(nmfk::gemm_split(true, pb.A, pb.lda, Ft, F, KP, KP, k, Rout, KP, KP, n, KP, m, part,
+                               ctx->stream, nsplit));
+      return NMF_OK;
+    }
+  nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? m : (int64_t)KP, Rout, KP, n, KP, m,
+                      Ft != nullptr};
+  HIP_TRY(run_product<T>(nmfk::GemmKind::TN, a, k, part, ctx->stream, nsplit));
+  return NMF_OK;
 }
 
 // Relative error of the current (W, Ht) into relerr[slot]. grams_current: w.S
@@ -648,14 +681,16 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
     tm.mark(PH_OBJ);
     RUN(objective<T>(ctx, pb, m, n, KP, w, 0, true));
   }
-  // The factors' copies for the dense products: float products always read
-  // them; double ones read 16-byte runs of them, so their rows must stay
-  // 16-byte aligned, and below 2^22 entries of A they read the factors in
-  // place (the copy's launch would cost more than its loads save).
+  // The factors' copies for the dense products: gemm_split always reads them;
+  // double ones read 16-byte runs of them, so their rows must stay 16-byte
+  // aligned, and below 2^22 entries of A they (and gemm_f32, taken only there)
+  // read the factors in place (the copy's launch would cost more than its loads
+  // save).
   const bool dense = !pb.sparse && !pb.lp;
   const bool big = m * n >= ((int64_t)1 << 22);
-  const bool tH = dense && (sizeof(T) == 4 || (big && (n * (int64_t)sizeof(T)) % 16 == 0));
-  const bool tW = dense && (sizeof(T) == 4 || (big && (m * (int64_t)sizeof(T)) % 16 == 0));
+  const bool planes = sizeof(T) == 4 && !pb.f32;
+  const bool tH = dense && (planes || (big && (n * (int64_t)sizeof(T)) % 16 == 0));
+  const bool tW = dense && (planes || (big && (m * (int64_t)sizeof(T)) % 16 == 0));
   if (pgstop) {
     // H half at the initial factors
     tm.mark(PH_OBJ);
@@ -951,12 +986,13 @@ nmf_status dense_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int lp, co
   Prob<T> pb;
   pb.A = A;
   pb.lda = lda;
+  pb.f32 = sizeof(T) == 4 && !lp && f32_sums(o->algo, m, n, KP);
   if (lp) {
     if ((s = lp_bind(ctx, pb, lp, Alp, lda, m, n, lo,
                      o->iters > 0 && !nmfk::gemm_lp_reads_a(n, lda))) != NMF_OK)
       return s;
-  } else if (sizeof(T) == 8 && o->iters > 0 && o->transpose_a == 0) {
-    // float products read A in either direction at nearly the same rate
+  } else if ((sizeof(T) == 8 || pb.f32) && o->iters > 0 && o->transpose_a == 0) {
+    // the other float products read A in either direction at nearly the same rate
     // (65536^2: 3.2 and 3.3 ms), so a copy (6.5 ms) would pay only after some
     // fifty iterations
     if ((s = transposed_copy<T>(ctx, A, lda, m, n, m, &pb.At)) != NMF_OK) return s;
@@ -1687,12 +1723,12 @@ template <typename T> struct MuWork {
 };
 
 template <typename T>
-size_t mu_plan_common(int64_t m, int64_t n, int KP, Carve& cv, size_t off[8]) {
+size_t mu_plan_common(int64_t m, int64_t n, int KP, Carve& cv, size_t off[8], bool f32 = false) {
   const int64_t mx = std::max(m, n);
-  const int64_t ps = std::max({nmfk::gemm_auto_splits<T>(nmfk::GemmKind::NN, m, KP, n),
-                               nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, m, KP, n),
-                               nmfk::gemm_auto_splits<T>(nmfk::GemmKind::TN, n, KP, m),
-                               nmfk::gemm_auto_splits<T>(nmfk::GemmKind::NN, n, KP, m),
+  const int64_t ps = std::max({product_splits<T>(nmfk::GemmKind::NN, m, KP, n, f32),
+                               product_splits<T>(nmfk::GemmKind::TN, m, KP, n, f32),
+                               product_splits<T>(nmfk::GemmKind::TN, n, KP, m, f32),
+                               product_splits<T>(nmfk::GemmKind::NN, n, KP, m, f32),
                                (int64_t)1});
   const int64_t part = std::max<int64_t>(ps * mx * KP, gram_splits(mx) * KP * KP);
   off[0] = cv.take<T>(m * KP);
@@ -1713,16 +1749,21 @@ MuWork<T> mu_bind(nmf_ctx* ctx, const size_t off[8]) {
                    at<T>(ctx, off[6]), at<T>(ctx, off[7])};
 }
 
+// The copy of a factor that pb's products read.
+template <typename T> nmfk::FactorCopy copy_of(const Prob<T>& pb) {
+  return pb.f32 ? nmfk::FactorCopy::TRANSPOSE : nmfk::FactorCopy::PLANES;
+}
+
 // Rank-side operands of the dense products are read from the factor's copy
-// (w.Ft): always for float, for double when its rows are 16-byte aligned.
+// (w.Ft): always for gemm_split, otherwise when its rows are 16-byte aligned.
 // ft_ready: the producer of F has already written that copy. With parts set, a split product stays in its
 // slabs (in w.part) for the consumer to sum; otherwise Out receives it.
 template <typename T>
 nmf_status mu_prod_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F, int k,
                       int KP, T* Out, MuWork<T>& w, bool ft_ready = false,
                       nmfk::Split<T>* parts = nullptr) {
-  const bool tf = sizeof(T) == 4 || (n * (int64_t)sizeof(T)) % 16 == 0;
-  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, n, KP, w.Ft, ctx->stream));
+  const bool tf = (sizeof(T) == 4 && !pb.f32) || (n * (int64_t)sizeof(T)) % 16 == 0;
+  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, n, KP, w.Ft, ctx->stream, copy_of(pb)));
   int ns = 1;
   nmf_status s = product_AF<T>(ctx, pb, m, n, F, tf ? w.Ft : nullptr, k, KP, Out, w.part,
                                parts ? &ns : nullptr);
@@ -1734,8 +1775,8 @@ template <typename T>
 nmf_status mu_prod_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, const T* F, int k,
                        int KP, T* Out, MuWork<T>& w, bool ft_ready = false,
                        nmfk::Split<T>* parts = nullptr) {
-  const bool tf = sizeof(T) == 4 || (m * (int64_t)sizeof(T)) % 16 == 0;
-  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, m, KP, w.Ft, ctx->stream));
+  const bool tf = (sizeof(T) == 4 && !pb.f32) || (m * (int64_t)sizeof(T)) % 16 == 0;
+  if (tf && !ft_ready) HIP_TRY(factor_copy<T>(F, m, KP, w.Ft, ctx->stream, copy_of(pb)));
   int ns = 1;
   nmf_status s = product_AtF<T>(ctx, pb, m, n, F, tf ? w.Ft : nullptr, k, KP, Out, w.part,
                                 parts ? &ns : nullptr);
@@ -1746,8 +1787,8 @@ nmf_status mu_prod_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
 // Whether a row kernel can hand a rows x KP factor to the next product as
 // that copy directly (the product reads one for these rows).
 template <typename T>
-bool rows_transposable(int64_t rows, int KP) {
-  return (sizeof(T) == 4 || (rows * (int64_t)sizeof(T)) % 16 == 0) && KP <= 64;
+bool rows_transposable(int64_t rows, int KP, bool f32 = false) {
+  return ((sizeof(T) == 4 && !f32) || (rows * (int64_t)sizeof(T)) % 16 == 0) && KP <= 64;
 }
 
 // One MU iteration from (W, Ht) into (Wn, Htn) (which may alias W, Ht),
@@ -1803,7 +1844,7 @@ nmf_status mu_prepare_A(nmf_ctx* ctx, const T* A, int64_t lda, int64_t m, int64_
                         Prob<T>& pb) {
   pb.A = A;
   pb.lda = lda;
-  if (sizeof(T) == 4) return NMF_OK;   // float products read A in either direction
+  if (sizeof(T) == 4 && !pb.f32) return NMF_OK;   // gemm_split reads A in either direction
   return transposed_copy<T>(ctx, A, lda, m, n, m, &pb.At);
 }
 
@@ -1979,7 +2020,8 @@ nmf_status mu_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int6
 // the normalisation (W, H and S rescaled; norms into nrm), R = A^T W, the H
 // sweep. Wp and Hc (nullable) receive W after the sweep and H^T after the
 // rescaling, which the backward pass needs; every step writes its output
-// where the next one reads it, so nothing is copied. *ft: on entry, whether
+// where the next one reads it, so nothing is copied. Float products are
+// gemm_f32's (pb.f32): the gradient's masks follow the last bits of this pass. *ft: on entry, whether
 // w.Ft holds Ht's copy; on return, whether it holds Htn's. gsl
 // and *qready: the Gram shares, as for mu_iteration (with the sweeps'
 // blocking).
@@ -1989,7 +2031,7 @@ nmf_status hals_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n,
                           T* S, MuWork<T>& w, bool* ft, T* gsl, bool* qready) {
   hipStream_t st = ctx->stream;
   nmf_status s;
-  const bool tH = rows_transposable<T>(n, KP);
+  const bool tH = rows_transposable<T>(n, KP, pb.f32);
   nmfk::Split<T> sp;
   T* Wsw = Wp ? Wp : Wn;    // the W sweep's output
   T* Hsc = Hc ? Hc : Htn;   // H^T after the rescaling
@@ -2010,11 +2052,12 @@ nmf_status hals_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n,
   }
   // the normalisation writes Wn's copy for the product (w.Ft, whose
   // copy of Ht the product above has read)
-  const bool tW = rows_transposable<T>(m, KP);
+  const bool tW = rows_transposable<T>(m, KP, pb.f32);
   HIP_TRY(nmfk::hals_normalize<T>(Wsw, Wn, m, Ht, Hsc, n, S, nrm, k, KP, st,
-                                  tW ? w.Ft : nullptr));
+                                  tW ? w.Ft : nullptr, copy_of(pb)));
   if ((s = mu_prod_AtF<T>(ctx, pb, m, n, Wn, k, KP, w.R, w, tW, &sp)) != NMF_OK) return s;
-  HIP_TRY(nmfk::hals_rows<T>(Hsc, Htn, sp, S, n, k, KP, tH ? w.Ft : nullptr, gsl, st));
+  HIP_TRY(nmfk::hals_rows<T>(Hsc, Htn, sp, S, n, k, KP, tH ? w.Ft : nullptr, gsl, st, nullptr,
+                             copy_of(pb)));
   *ft = tH;
   if (gsl) *qready = true;
   return NMF_OK;
@@ -2026,7 +2069,7 @@ nmf_status hals_forward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int
   const int KP = kp_dense(k);
   Carve cv;
   size_t off[8];
-  mu_plan_common<T>(m, n, KP, cv, off);
+  mu_plan_common<T>(m, n, KP, cv, off, true);
   const size_t onrm = cv.take<T>(KP);
   const int64_t nbs = plan_shares(NMF_HALS, m, n, KP).blocks();
   const size_t ogsl = cv.take<T>(nbs * KP * KP);   // the sweeps' Gram shares
@@ -2039,6 +2082,7 @@ nmf_status hals_forward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int
   HIP_TRY(nmfk::pad_rows<T>(W, m, k, w.W, KP, st));
   HIP_TRY(nmfk::transpose_in<T>(H, k, n, w.Ht, KP, st));
   Prob<T> pb;
+  pb.f32 = sizeof(T) == 4;
   if (iters > 0 && (s = mu_prepare_A<T>(ctx, A, lda, m, n, pb)) != NMF_OK) return s;
   const int64_t slot = (m + n) * KP;
   bool ft = false, qready = false;
@@ -2071,7 +2115,7 @@ nmf_status hals_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, in
   const int seg = std::min(every, std::max(iters, 1));
   Carve cv;
   size_t off[8];
-  mu_plan_common<T>(m, n, KP, cv, off);
+  mu_plan_common<T>(m, n, KP, cv, off, true);
   const size_t oWs = cv.take<T>((seg + 1) * m * KP);   // W_t over one segment
   const size_t oHs = cv.take<T>((seg + 1) * n * KP);   // H_t^T over one segment
   const size_t oWp = cv.take<T>(seg * m * KP);         // W after the sweep
@@ -2115,8 +2159,12 @@ nmf_status hals_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, in
   HIP_TRY(nmfk::pad_rows<T>(gWT, m, k, gW, KP, st));
   HIP_TRY(nmfk::transpose_in<T>(gHT, k, n, gH, KP, st));
   if (gA && iters == 0) HIP_TRY(hipMemset2DAsync(gA, ldga * sizeof(T), 0, n * sizeof(T), m, st));
+  // pb: the recomputation's products; pbr: the gradients', which no mask follows
   Prob<T> pb;
+  pb.f32 = sizeof(T) == 4;
   if (iters > 0 && (s = mu_prepare_A<T>(ctx, A, lda, m, n, pb)) != NMF_OK) return s;
+  Prob<T> pbr = pb;
+  pbr.f32 = false;
   const int64_t slot = (m + n) * KP;
   const int64_t nck = mu_ckpt_count(iters, every);
   for (int64_t j = nck - 1; j >= 0; --j) {
@@ -2148,7 +2196,7 @@ nmf_status hals_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, in
       // M from T1 = H1^T gR and T2 = Hc^T gR, summed from the blocks' shares
       HIP_TRY(nmfk::hals_gram_grad<T>(tsl, (int)hbn, KP, M, st));
       // gW += A gR (the product's slabs) + Wn M
-      if ((s = mu_prod_AF<T>(ctx, pb, m, n, gR, k, KP, tmp, w, tH, &yp)) != NMF_OK) return s;
+      if ((s = mu_prod_AF<T>(ctx, pbr, m, n, gR, k, KP, tmp, w, tH, &yp)) != NMF_OK) return s;
       HIP_TRY(nmfk::rowmm_add<T>(W1s, M, m, k, KP, gW, st, yp));
       // normalisation: Wn = W' / s, Hc = s H
       HIP_TRY(nmfk::coldot2<T>(gW, W1s, m, gHc, H0s, n, KP, dpart, dots, st));
@@ -2159,7 +2207,7 @@ nmf_status hals_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, in
                                          tW ? w.Ft : nullptr, W0s, tsl, st));
       HIP_TRY(nmfk::hals_gram_grad<T>(tsl, (int)hbm, KP, M, st));
       // gH += A^T gP (the product's slabs) + H M
-      if ((s = mu_prod_AtF<T>(ctx, pb, m, n, gP, k, KP, tmp, w, tW, &yp)) != NMF_OK) return s;
+      if ((s = mu_prod_AtF<T>(ctx, pbr, m, n, gP, k, KP, tmp, w, tW, &yp)) != NMF_OK) return s;
       HIP_TRY(nmfk::rowmm_add<T>(H0s, M, n, k, KP, gH2, st, yp));
       std::swap(gW, gW2);
       std::swap(gH, gH2);

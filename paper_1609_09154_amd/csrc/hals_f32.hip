@@ -4,6 +4,6 @@
 namespace nmfk {
 
 template hipError_t hals_rows<float>(const float*, float*, Split<float>, const float*, int64_t, int, int,
-                                     float*, float*, hipStream_t, const float*);
+                                     float*, float*, hipStream_t, const float*, FactorCopy);
 
 }  // namespace nmfk

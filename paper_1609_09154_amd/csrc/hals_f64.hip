@@ -4,6 +4,6 @@
 namespace nmfk {
 
 template hipError_t hals_rows<double>(const double*, double*, Split<double>, const double*, int64_t, int, int,
-                                     double*, double*, hipStream_t, const double*);
+                                     double*, double*, hipStream_t, const double*, FactorCopy);
 
 }  // namespace nmfk

@@ -20,7 +20,7 @@ namespace nmfk {
 // number of rows: many rows fill the chip with small groups, which take fewer
 // permutation steps per column; few rows need larger groups to fill it.
 // With TILE (KP <= 64), after the sweep the LDS that held G takes the
-// block's new rows (zero past the end) for their transposed copy (Xt,
+// block's new rows (zero past the end) for the copy the next product reads (Xt,
 // nullable) and the block's share of Xn^T Xn (Gslab + blockIdx.x * KP * KP,
 // nullable), formed on the matrix cores. The tile shares G's space; only at
 // 64 rows per block does its padding need more (17 KB against 16 KB at KP =
@@ -35,7 +35,8 @@ __global__ __launch_bounds__(256) void hals_rows_grp_kernel(const T* X, T* Xn, S
                                                             int64_t rows, int k,
                                                             T* __restrict__ Xt,
                                                             T* __restrict__ Gslab,
-                                                            const T* __restrict__ Xscale) {
+                                                            const T* __restrict__ Xscale,
+                                                            FactorCopy copy) {
   constexpr int R = KP / TPR, ROWS = 256 / TPR;
   constexpr int VEC = Tr<T>::VEC;
   constexpr int XLD = KP + VEC;
@@ -104,59 +105,59 @@ __global__ __launch_bounds__(256) void hals_rows_grp_kernel(const T* X, T* Xn, S
     for (int q = 0; q < R; ++q) Ls[(threadIdx.x / TPR) * XLD + sub * R + q] = in ? x[q] : T(0);
     __syncthreads();
     if (Gslab) block_gram_partial<T, KP, ROWS, XLD>(Ls, Ls, Gslab + (int64_t)blockIdx.x * KP * KP);
-    if (Xt) store_rows_copy<T, KP, ROWS, XLD>(Ls, rb, rows, Xt);
+    if (Xt) store_rows_copy<T, KP, ROWS, XLD>(Ls, rb, rows, Xt, copy);
   }
 }
 
 template <typename T, int KP, bool SLABS, bool TILE>
 void launch_hals_grp_t(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int tpr,
-                       T* Xt, T* Gslab, const T* Xs, hipStream_t st) {
+                       T* Xt, T* Gslab, const T* Xs, FactorCopy copy, hipStream_t st) {
   if (tpr == 4)
     hals_rows_grp_kernel<T, KP, 4, SLABS, TILE><<<(unsigned)cdiv(rows, 64), 256, 0, st>>>(
-        X, Xn, P, G, rows, k, Xt, Gslab, Xs);
+        X, Xn, P, G, rows, k, Xt, Gslab, Xs, copy);
   else if (tpr == 8)
     hals_rows_grp_kernel<T, KP, 8, SLABS, TILE><<<(unsigned)cdiv(rows, 32), 256, 0, st>>>(
-        X, Xn, P, G, rows, k, Xt, Gslab, Xs);
+        X, Xn, P, G, rows, k, Xt, Gslab, Xs, copy);
   else
     hals_rows_grp_kernel<T, KP, 16, SLABS, TILE><<<(unsigned)cdiv(rows, 16), 256, 0, st>>>(
-        X, Xn, P, G, rows, k, Xt, Gslab, Xs);
+        X, Xn, P, G, rows, k, Xt, Gslab, Xs, copy);
 }
 
 // One slab (the product as it came) needs no double accumulation: that form
 // keeps the small register footprint that lets many blocks share a CU.
 template <typename T, int KP>
 void launch_hals_grp(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int tpr,
-                     T* Xt, T* Gslab, const T* Xs, hipStream_t st) {
+                     T* Xt, T* Gslab, const T* Xs, FactorCopy copy, hipStream_t st) {
   if constexpr (KP <= 64) {
     if (Xt || Gslab) {
       if (P.n > 1)
-        launch_hals_grp_t<T, KP, true, true>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st);
+        launch_hals_grp_t<T, KP, true, true>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st);
       else
-        launch_hals_grp_t<T, KP, false, true>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st);
+        launch_hals_grp_t<T, KP, false, true>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st);
       return;
     }
   }
-  if (P.n > 1) launch_hals_grp_t<T, KP, true, false>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st);
-  else launch_hals_grp_t<T, KP, false, false>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st);
+  if (P.n > 1) launch_hals_grp_t<T, KP, true, false>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st);
+  else launch_hals_grp_t<T, KP, false, false>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st);
 }
 
 template <typename T>
 hipError_t hals_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int KP,
-                     T* Xt, T* Gslab, hipStream_t st, const T* Xs) {
+                     T* Xt, T* Gslab, hipStream_t st, const T* Xs, FactorCopy copy) {
   if (rows <= 0) return hipSuccess;
   if (((Xt || Gslab) && KP > 64) || !P.p || P.n < 1) return hipErrorInvalidValue;
   const int tpr = hals_tpr(rows);
   // every padded rank up to NMF_MAX_K takes the grouped sweep; G (KP x KP)
   // is staged in LDS, at most 64 KB (float) or 128 KB (double) at KP = 128
   switch (KP) {
-    case 16: launch_hals_grp<T, 16>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 32: launch_hals_grp<T, 32>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 48: launch_hals_grp<T, 48>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 64: launch_hals_grp<T, 64>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 80: launch_hals_grp<T, 80>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 96: launch_hals_grp<T, 96>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 112: launch_hals_grp<T, 112>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
-    case 128: launch_hals_grp<T, 128>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, st); break;
+    case 16: launch_hals_grp<T, 16>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 32: launch_hals_grp<T, 32>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 48: launch_hals_grp<T, 48>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 64: launch_hals_grp<T, 64>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 80: launch_hals_grp<T, 80>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 96: launch_hals_grp<T, 96>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 112: launch_hals_grp<T, 112>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
+    case 128: launch_hals_grp<T, 128>(X, Xn, P, G, rows, k, tpr, Xt, Gslab, Xs, copy, st); break;
     default: return hipErrorInvalidValue;
   }
   return NMF_LAUNCH_CHECK();

@@ -11,7 +11,7 @@ namespace nmfk {
 enum class GemmKind { NN, TN, TN_GRAM };
 
 // Double products, and the Grams of both types (TN_GRAM; float takes no other
-// kind): D (M x N) = X * Y (NN, X is M x K) or X^T * Y (TN, X is K x M). Y is
+// kind here, NN and TN by gemm_split or gemm_f32): D (M x N) = X * Y (NN, X is M x K) or X^T * Y (TN, X is K x M). Y is
 // K x N, or, with yt set, its transpose N x K (ldy between its N rows; then
 // Y must be 16-byte aligned with ldy a multiple of 16 bytes). N must be a
 // multiple of 16 between 16 and 128.
@@ -71,6 +71,18 @@ hipError_t pack_split(const float* F, int64_t rows, int64_t ldf, int kv, int KP,
                       hipStream_t st);
 inline int64_t split_floats(int64_t rows, int KP) { return (rows + 31) / 32 * 48 * KP; }
 
+// Float products with the float instruction, in the sums that the unrolled HALS
+// layer's results follow (gemm_f32.hip): kinds NN and TN of `a`, N at most 64,
+// of whose columns those past nvalid are zero. `part` must hold
+// gemm_f32_splits(...) * M * N floats when that count exceeds 1; nsplit as for
+// gemm_run.
+hipError_t gemm_f32(GemmKind kind, const GemmArgs<float>& a, int nvalid, float* part,
+                    hipStream_t st, int* nsplit = nullptr);
+int64_t gemm_f32_splits(GemmKind kind, int64_t M, int64_t N, int64_t K);
+// The copy of a factor that a product reads: the packed planes of a float
+// factor (gemm_split), or its transpose (double, and gemm_f32).
+enum class FactorCopy { PLANES, TRANSPOSE };
+
 // Reduced-precision products: D (M x N float, ld ldd) = X Y^T for X (M x K;
 // tn: given as X^T, K x M, see gemm_lp_reads_a) and Y (N x K, K contiguous) stored as
 // bfloat16 bits (uint16_t) or FP8 E4M3 bits (uint8_t), rows 16-byte aligned,
@@ -100,7 +112,8 @@ hipError_t pack_fp8_t(const float* F, int64_t rows, int KP, uint8_t* Ft, int64_t
 // the true rank, entries k..KP-1 are zero padding and stay zero.
 // mu_rows and hals_rows write the updated rows of X to Xn (Xn == X: in
 // place) and, when Xt is set (KP <= 64), the copy the next product reads as
-// well (double: their transpose Xt[i * rows + r]; float: their packed planes); P is summed from its slabs (mu_rows: Pout, nullable, receives the
+// well (double, or float with `copy` TRANSPOSE: their transpose
+// Xt[i * rows + r]; float otherwise: their packed planes); P is summed from its slabs (mu_rows: Pout, nullable, receives the
 // sum). Gslab (nullable, KP <= 64) receives the row blocks' shares of
 // Xn^T Xn, one KP x KP slab per block of share_rows rows (cdiv(rows,
 // share_rows) of them), for an ordered sum (reduce_splits).
@@ -113,7 +126,8 @@ hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int 
 // x_i *= Xs[i] where Xs[i] > 0 (the normalisation's compensation of H).
 template <typename T>
 hipError_t hals_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int KP,
-                     T* Xt, T* Gslab, hipStream_t st, const T* Xs = nullptr);
+                     T* Xt, T* Gslab, hipStream_t st, const T* Xs = nullptr,
+                     FactorCopy copy = FactorCopy::PLANES);
 // Lanes per row of the HALS sweep at `rows` rows: many rows fill the chip with
 // small groups, which take fewer permutation steps per column; few rows need
 // larger groups to fill it.
@@ -133,11 +147,12 @@ hipError_t gram_shares(const T* X, int64_t rows, int KP, int rpb, T* Gslab, hipS
 
 // HALS normalisation: s_i = sqrt(S[i][i]); W[:, i] /= s_i, Ht[:, i] *= s_i and
 // S[i][j] /= s_i s_j for s_i > 0. norms receives s. Wt (nullable, KP <= 64;
-// double: m a multiple of 2) receives the copy of the rescaled W that the next
-// product reads (as mu_rows' Xt).
+// a transpose: m a multiple of 16 / sizeof(T)) receives the copy of the rescaled
+// W that the next product reads (as hals_rows' Xt).
 template <typename T>
 hipError_t hals_normalize(const T* W, T* Wn, int64_t m, const T* Ht, T* Htn, int64_t n, T* S,
-                          T* norms, int k, int KP, hipStream_t st, T* Wt = nullptr);
+                          T* norms, int k, int KP, hipStream_t st, T* Wt = nullptr,
+                          FactorCopy copy = FactorCopy::PLANES);
 
 // Copies between the caller's layouts (ld = k) and the padded row layout.
 template <typename T>

@@ -1,8 +1,8 @@
 // Store of a block of factor rows in the layout the dense products read,
 // shared by the row kernels that hand their output to one: double products
-// read the rank-side factor as KP x rows (each rank column's rows contiguous,
-// 16-byte loads along the reduction index), float products its packed
-// bfloat16 planes (split.h). A row kernel that already holds its block of
+// (and those of gemm_f32.hip) read the rank-side factor as KP x rows (each rank
+// column's rows contiguous, 16-byte loads along the reduction index), the other
+// float products its packed bfloat16 planes (split.h). A row kernel that already holds its block of
 // rows in LDS writes that copy directly instead of a separate pass.
 #pragma once
 
@@ -212,17 +212,18 @@ __device__ __forceinline__ void block_gram_partial(const T* Xs, const T* Ds, T* 
 
 // Writes rows [rb, rb + ROWS) of a rows x KP block held in LDS as
 // tile[q * LD + i] (q = row - rb) as the dense products
-// read them. double: out[i * rows + row], column i's rows of the block as
-// whole 16-byte runs when rows is a multiple of VEC (out is then 16-byte
-// aligned at every run), rows past the end skipped. float: the block's packed
+// read them. TRANSPOSE (and double): out[i * rows + row], column i's rows of the
+// block as whole 16-byte runs when rows is a multiple of VEC (out is then 16-byte
+// aligned at every run), rows past the end skipped. Float PLANES: the block's packed
 // chunks, zero past the end; the last block also writes the zero groups up to
 // the padded row count. Uses every thread of the block; the caller synchronises before (tile
 // written) and nothing after.
 template <typename T, int KP, int ROWS, int LD>
 __device__ __forceinline__ void store_rows_copy(const T* tile, int64_t rb, int64_t rows,
-                                                T* __restrict__ out) {
+                                                T* __restrict__ out,
+                                                FactorCopy copy = FactorCopy::PLANES) {
   constexpr int VEC = Tr<T>::VEC;
-  if constexpr (sizeof(T) == 4) {
+  if (sizeof(T) == 4 && copy == FactorCopy::PLANES) {
     static_assert(ROWS % 8 == 0, "whole groups per block");
     u32x4* o = reinterpret_cast<u32x4*>(out);
     for (int e = threadIdx.x; e < KP * (ROWS / 8); e += blockDim.x) {

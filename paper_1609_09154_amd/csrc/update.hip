@@ -389,15 +389,16 @@ __global__ void hals_scale_kernel(const T* W, T* Wn, int64_t m, const T* Ht, T* 
 }
 
 // The same rescaling by tiles of SCALE_ROWS rows (W's tiles, then Ht's), for
-// KP <= 64 with W's transposed copy: each tile of Wn also goes through LDS
-// and out as Wt[i * m + r], the layout the next product reads, so that copy
-// needs no launch of its own.
+// KP <= 64 with W's copy: each tile of Wn also goes through LDS and out to Wt
+// in the layout the next product reads (FactorCopy), so that copy needs no
+// launch of its own.
 constexpr int SCALE_ROWS = 64;
 template <typename T, int KP>
 __global__ __launch_bounds__(256) void hals_scale_t_kernel(const T* W, T* Wn, int64_t m,
                                                            const T* Ht, T* Htn, int64_t n,
                                                            const T* __restrict__ norms, int k,
-                                                           T* __restrict__ Wt) {
+                                                           T* __restrict__ Wt,
+                                                           FactorCopy copy) {
   constexpr int VEC = Tr<T>::VEC, CPR = KP / VEC, XLD = KP + VEC;
   __shared__ __attribute__((aligned(16))) T tile[SCALE_ROWS * XLD];
   const int64_t tw = cdiv(m, SCALE_ROWS), tt = tw + cdiv(n, SCALE_ROWS);
@@ -429,7 +430,7 @@ __global__ __launch_bounds__(256) void hals_scale_t_kernel(const T* W, T* Wn, in
     }
     if (w) {
       __syncthreads();
-      store_rows_copy<T, KP, SCALE_ROWS, XLD>(tile, rb, m, Wt);
+      store_rows_copy<T, KP, SCALE_ROWS, XLD>(tile, rb, m, Wt, copy);
       __syncthreads();  // the tile is rewritten by the block's next W tile
     }
   }
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(256) void hals_scale_t_kernel(const T* W, T* Wn, in
 
 template <typename T>
 hipError_t hals_normalize(const T* W, T* Wn, int64_t m, const T* Ht, T* Htn, int64_t n, T* S,
-                          T* norms, int k, int KP, hipStream_t st, T* Wt) {
+                          T* norms, int k, int KP, hipStream_t st, T* Wt, FactorCopy copy) {
   hals_norms_kernel<T><<<1, 256, 0, st>>>(S, norms, k, KP);
   hipError_t e = NMF_LAUNCH_CHECK();
   if (e != hipSuccess) return e;
@@ -446,10 +447,10 @@ hipError_t hals_normalize(const T* W, T* Wn, int64_t m, const T* Ht, T* Htn, int
   if (Wt) {
     const unsigned nb = capped_grid(cdiv(m, SCALE_ROWS) + cdiv(n, SCALE_ROWS));
     switch (KP) {
-      case 16: hals_scale_t_kernel<T, 16><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt); break;
-      case 32: hals_scale_t_kernel<T, 32><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt); break;
-      case 48: hals_scale_t_kernel<T, 48><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt); break;
-      case 64: hals_scale_t_kernel<T, 64><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt); break;
+      case 16: hals_scale_t_kernel<T, 16><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt, copy); break;
+      case 32: hals_scale_t_kernel<T, 32><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt, copy); break;
+      case 48: hals_scale_t_kernel<T, 48><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt, copy); break;
+      case 64: hals_scale_t_kernel<T, 64><<<nb, 256, 0, st>>>(W, Wn, m, Ht, Htn, n, norms, k, Wt, copy); break;
       default: return hipErrorInvalidValue;
     }
     return NMF_LAUNCH_CHECK();
@@ -737,7 +738,7 @@ hipError_t transpose_out(const T* Ht, int k, int64_t n, int KP, T* H, hipStream_
                                  T*, T*, hipStream_t, int); \
   template hipError_t gram_shares<T>(const T*, int64_t, int, int, T*, hipStream_t); \
   template hipError_t hals_normalize<T>(const T*, T*, int64_t, const T*, T*, int64_t, T*, T*, \
-                                        int, int, hipStream_t, T*);                         \
+                                        int, int, hipStream_t, T*, FactorCopy);             \
   template hipError_t pad_rows<T>(const T*, int64_t, int, T*, int, hipStream_t);            \
   template hipError_t pad_jobs<T>(const CopyJob<T>*, int, hipStream_t);                     \
   template hipError_t unpad_jobs<T>(const CopyJob<T>*, int, hipStream_t);                   \
