@@ -253,11 +253,14 @@ __device__ __forceinline__ void solve_pass(const double* __restrict__ M, const i
 // step on pivot q subtracts f_r times the raw pivot row from every row r, with
 // f_r = M_rq / M_qq off the pivot row and 1 - 1 / M_qq on it (which scales the
 // pivot row by 1 / M_qq), then sets column q to the inverse's column (-f_r,
-// and 1 / M_qq on the pivot row). The wavefront that holds column q passes
-// f to the others through LDS, in two buffers in turn, so a step takes one
-// barrier: its writer two steps on has passed the next step's barrier, which
-// every reader reaches after its read. Pivot rows are read with readlane;
-// steps of indices outside the live set are identity steps and are skipped.
+// and 1 / M_qq on the pivot row). Pivot rows are read with readlane; steps of
+// indices outside the live set are identity steps and are skipped. The
+// wavefront that holds column q passes f to the others through LDS, in two
+// buffers that take turns over the steps that are run (counted in `live`, not
+// by q: a dead index between two live ones would give both the same buffer).
+// So a step takes one barrier: the buffer's next writer, two run steps on, has
+// passed the barrier of the step between, which every reader reaches after its
+// read.
 // A step is a chain (a quotient, the exchange, the update); what the
 // wavefronts share is the update of KP columns, most of the 62 us (KP = 64,
 // k = 50) that a single wavefront took; 26 us now.
@@ -269,16 +272,17 @@ __device__ __forceinline__ void ginv_step(double (&a)[KP / GINV_WAVES], int lane
   constexpr int CW = KP / GINV_WAVES, QW = Q / CW, QC = Q % CW;
   if (Q >= k || !((live >> Q) & 1ull)) return;
   const bool me = lane == Q;
+  fs += (__popcll(live & ((1ull << Q) - 1)) & 1) * 64;
   double f = 0.0, s = 0.0;
   if (wave == QW) {
     const double pv = rdl(a[QC], Q);
     if (!(pv > 0.0)) good = false;
     s = pv > 0.0 ? 1.0 / pv : 1.0;
     f = me ? 1.0 - s : a[QC] * s;
-    fs[(Q & 1) * 64 + lane] = f;
+    fs[lane] = f;
   }
   __syncthreads();
-  if (wave != QW) f = fs[(Q & 1) * 64 + lane];
+  if (wave != QW) f = fs[lane];
 #pragma unroll
   for (int c = 0; c < CW; ++c)
     if (c != QC || wave != QW) a[c] = fma(-f, rdl(a[c], Q), a[c]);
