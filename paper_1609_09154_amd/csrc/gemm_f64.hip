@@ -313,17 +313,19 @@ __device__ __forceinline__ double ordered_sum(const T* __restrict__ src, int p0,
 }
 
 // out[i] = sum_s part[s * stride + i] in order s = 0, 1, ... (double sums);
-// outt (nullable) receives the transpose, outt[c * rows + r].
+// outt (nullable) receives the transpose, outt[c * rows + r]. The grid is
+// capped (70,000,001 rows of 64 pass a dispatch's 2^32 work-items).
 template <typename T>
 __global__ void reduce_splits_kernel(const T* __restrict__ part, int splits, int64_t stride,
                                      int64_t rows, int cols, int64_t ldo, T* __restrict__ out,
                                      int64_t ldp, T* __restrict__ outt) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * cols) return;
-  const int64_t r = idx / cols, cc = idx - r * cols;
-  const double s = ordered_sum<T>(part + r * ldp + cc, 0, 1, splits, stride);
-  out[r * ldo + cc] = (T)s;
-  if (outt) outt[cc * rows + r] = (T)s;
+  const int64_t total = rows * cols, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += step) {
+    const int64_t r = idx / cols, cc = idx - r * cols;
+    const double s = ordered_sum<T>(part + r * ldp + cc, 0, 1, splits, stride);
+    out[r * ldo + cc] = (T)s;
+    if (outt) outt[cc * rows + r] = (T)s;
+  }
 }
 
 // Same sums for few outputs and many splits (the k x k Grams): RS_SUB
@@ -361,8 +363,8 @@ hipError_t reduce_splits(const T* part, int splits, int64_t dsplit, int64_t M, i
     reduce_splits_wide_kernel<T><<<(unsigned)cdiv(total, RS_OUT), RS_OUT * RS_SUB, 0, st>>>(
         part, splits, dsplit, M, N, ldd, D, ldp, Dt);
   else
-    reduce_splits_kernel<T><<<(unsigned)cdiv(total, 256), 256, 0, st>>>(part, splits, dsplit, M,
-                                                                         N, ldd, D, ldp, Dt);
+    reduce_splits_kernel<T><<<capped_grid(cdiv(total, 256)), 256, 0, st>>>(part, splits, dsplit, M,
+                                                                            N, ldd, D, ldp, Dt);
   return NMF_LAUNCH_CHECK();
 }
 template hipError_t reduce_splits<float>(const float*, int, int64_t, int64_t, int, int64_t, float*,
