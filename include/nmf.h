@@ -32,8 +32,8 @@
  *   nmf_last_error() describes the most recent failure on a context.
  * - Element types: NMF_F64 runs everything in double; NMF_F32 stores A, W, H
  *   in float and accumulates the large products in float on the matrix
- *   cores (each float taken as an exact sum of three bfloat16 values; results
- *   are as accurate as with float operands), with the Gram split-sums and the
+ *   cores (each float, subnormal ones included, taken as an exact sum of three
+ *   bfloat16 values; results are as accurate as with float operands), with the Gram split-sums and the
  *   objective accumulated in double.
  *   NMF_BF16 (dense A only) stores A as bfloat16 (each element the 16 bits
  *   of the value, row pitch lda a multiple of 8 elements, rows 16-byte

@@ -381,8 +381,8 @@ __global__ __launch_bounds__(256, 2) void rank_update_split_kernel(
     }
     __syncthreads();
   }
-  // as in the products: again with the float instruction where the split does
-  // not hold
+  // as in the products: again with the float instruction where the scaled sums
+  // are not finite
   bool redo = false;
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -390,8 +390,8 @@ __global__ __launch_bounds__(256, 2) void rank_update_split_kernel(
     for (int b = 0; b < 4; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float v = fabsf(acc[a][b][r]);
-        redo = redo || !(v <= 3.402823466e38f) || (v > 0.f && v < 7.8886e-31f);
+        redo = redo || !(fabsf(acc[a][b][r]) <= 3.402823466e38f);
+        acc[a][b][r] *= SPLIT_UNSCALE;
       }
   if (__ballot(redo)) {
     int64_t xr[4], yr[4];

@@ -6,7 +6,9 @@
 //
 // Every float is the exact sum of three bfloat16 values, x = h + m + l: h is
 // x rounded to nearest even, m the remainder x - h rounded, l what is left (8
-// bits each cover the 24 of a float). A product x f is taken as
+// bits each cover the 24 of a float; both operands are scaled by 2^16 first, so
+// that this holds down to the smallest float, see split.h). A product x f is
+// taken as
 //   h h' + h m' + m h' + m m' + h l' + l h'
 // whose dropped terms are below 2^-25 |x f| with either sign, well under the
 // rounding of a float sum. The six terms of 32 values of K take six
@@ -18,7 +20,7 @@
 // the float peak) and takes 3.2 (5.3 TB/s; a device copy reaches 4.9), with
 // a quarter of the error (1.1e-6 against 3.6e-6 on the factors after ten
 // HALS iterations). Products whose A stays in the caches are bound by the
-// splits (six VALU operations an entry) and the latency of a step: 8192 x
+// splits (seven VALU operations an entry) and the latency of a step: 8192 x
 // 4096 at k = 64, 46 us before, 33 now.
 //
 // A is read in its own layout in both directions (a lane's operand is eight
@@ -103,9 +105,6 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
       acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (FLUSH) tot[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-  unsigned mx[MT];   // the bits of h of each lane's row or column of X, ored
-#pragma unroll
-  for (int t = 0; t < MT; ++t) mx[t] = 0;
 
   // REM: the lane's chunk of the last tile within a lane group's chunks
   int remo = 0;
@@ -156,12 +155,7 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
   auto compute = [&](const XStep<MT>& f, int buf) {
     Split8 a[MT];
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
-    {
-      a[t] = split8(f.v[t]);
-      mx[t] |= a[t].h[0] | a[t].h[1];
-      mx[t] |= a[t].h[2] | a[t].h[3];
-    }
+    for (int t = 0; t < MT; ++t) a[t] = split8(f.v[t]);
     const u32x4* fb = &Fs[buf][3 * NR * g + c];
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
@@ -273,26 +267,19 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
         acc[t][NF][r] = c < nrem ? (vl + vm) + v : 0.f;
       }
   }
-  // Where the split does not hold (an entry that is not finite or rounds to
-  // infinity as bfloat16, or a row so small that its last bits fall below the
-  // smallest bfloat16) the wave computes its tiles again with the float
-  // instruction.
+  // Where the scaled sums are not finite (an entry that is not, or of magnitude
+  // 2^111 and up, or a result of 2^96 and up) the wave computes its tiles again
+  // with the float instruction.
   bool redo = false;
 #pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    unsigned w = (mx[t] | mx[t] >> 16) & 0x7fffu;
-    w |= (unsigned)__shfl_xor((int)w, 16, 64);
-    w |= (unsigned)__shfl_xor((int)w, 32, 64);
-    // every exponent field below 32: every |h| below 2^-95
-    redo = redo || (w > 0 && w < (32u << 7));
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float v = fabsf(acc[t][j][r]);
-        redo = redo || !(v <= 3.402823466e38f) || (v > 0.f && v < 7.8886e-31f);
+        redo = redo || !(fabsf(acc[t][j][r]) <= 3.402823466e38f);
+        acc[t][j][r] *= SPLIT_UNSCALE;
       }
-  }
   if (__ballot(redo)) {
 #pragma unroll
     for (int t = 0; t < MT; ++t)

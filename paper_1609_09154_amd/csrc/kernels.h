@@ -57,7 +57,7 @@ hipError_t reduce_splits(const T* part, int splits, int64_t dsplit, int64_t M, i
 // Float products at any rank up to 128: D (M x nout, ld ldd) = X F (X M x K)
 // or, tn, X^T F (X K x M) for float X of any pitch ldx and F (K x kv, pitch
 // ldf, given as Fp, its packed planes for KP >= kv columns; F itself is read
-// only where the split does not hold). Columns k..kv-1 of F are zero, so are
+// only where the scaled sums are not finite). Columns k..kv-1 of F are zero, so are
 // columns k..nout-1 of D. `part`
 // must hold gemm_split_splits(M, KP, K) * M * KP floats when that count
 // exceeds 1; nsplit as for gemm_run (the slabs then have KP columns).

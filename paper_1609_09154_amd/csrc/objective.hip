@@ -205,12 +205,16 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
       load_w(p, row0 + PF * 16);
 #pragma unroll
       for (int s = 0; s < KS; ++s) split_mma(ws[s], hp[s], acc);
-      // products of entries that are not finite: again with the float instruction
+      // scaled sums that are not finite (as in the products): again with the
+      // float instruction
       bool bad = false;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
+        for (int r = 0; r < 4; ++r) {
+          bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
+          acc[j][r] *= SPLIT_UNSCALE;
+        }
       if (__ballot(bad)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();

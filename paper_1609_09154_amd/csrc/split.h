@@ -8,11 +8,19 @@ namespace nmfk {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// x = h + m + l (bits of three bfloat16 values) for every finite x of
-// magnitude 2^-110 and up: h is x rounded to nearest even (cut off instead
-// where rounding would overflow), m the remainder rounded, l the rest. NaN
-// and infinities keep m = l = 0.
+// Operands are split after scaling by 2^16, and their products scaled back by
+// 2^-32 (both exact): the last bit of any float, 2^-149 at the least, is then a
+// whole multiple of the smallest bfloat16 (2^-133), so that no split loses bits,
+// however small the entry. Unscaled, entries below 2^-110 did: with a factor
+// near 2^-122 and A near 2^40 a product was off by 1e-5.
+constexpr float SPLIT_SCALE = 65536.f, SPLIT_UNSCALE = 1.f / 4294967296.f;
+
+// 2^16 x = h + m + l (bits of three bfloat16 values) for every x of magnitude
+// below 2^111: h is 2^16 x rounded to nearest even (cut off instead where
+// rounding would overflow), m the remainder rounded, l the rest. Larger
+// entries, infinities and NaN have h infinite or NaN and m = l = 0.
 __device__ __forceinline__ void split_bf16x3(float x, unsigned& h, unsigned& m, unsigned& l) {
+  x *= SPLIT_SCALE;
   const unsigned u = __float_as_uint(x), a = u & 0x7fffffffu;
   unsigned hh = u + 0x7fffu + ((u >> 16) & 1u);
   if (a >= 0x7f7f8000u) hh = a > 0x7f800000u ? u | 0x400000u : u;

@@ -10,10 +10,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// Eight floats as three bfloat16 operand registers.
+// Eight floats (scaled by SPLIT_SCALE) as three bfloat16 operand registers.
 struct Split8 { u32x4 h, m, l; };
 
 __device__ __forceinline__ void split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  x0 *= SPLIT_SCALE;
+  x1 *= SPLIT_SCALE;
   h = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
   const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
   m = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
@@ -39,7 +41,8 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
   return s;
 }
 
-// acc[j] += the product of a with b[j], smallest terms first.
+// acc[j] += the product of a with b[j] (SPLIT_UNSCALE of it is the result),
+// smallest terms first.
 template <int N>
 __device__ __forceinline__ void split_mma(const Split8& a, const Split8 (&b)[N], f32x4 (&acc)[N]) {
 #define TERM(PA, PB) \
