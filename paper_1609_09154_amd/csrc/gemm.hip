@@ -231,8 +231,7 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
   }
   // K tail (fewer than 32 values): element loads, zero beyond kend
   const int64_t kt = kbeg + nfull * SBK;
-  if (kt < kend) {
-    XStep<MT> f;
+  auto load_tail = [&](XStep<MT>& f) {
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -242,6 +241,10 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
         const float v = TR ? X[kc * ldx + col0 + t] : xr[TR ? 0 : t][kc - 8 * g];
         f.v[t][u] = kk < kend ? v : 0.f;
       }
+  };
+  if (kt < kend) {
+    XStep<MT> f;
+    load_tail(f);
     const u32x4* src = Fp + (kt >> 3) * (3 * NR);   // zero past the last row
     for (int e = tid; e < CH; e += 64 * SPW) Fs[0][e] = src[e];
     __syncthreads();
@@ -269,7 +272,11 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
   }
   // Where the scaled sums are not finite (an entry that is not, or of magnitude
   // 2^111 and up, or a result of 2^96 and up) the wave computes its tiles again
-  // with the float instruction.
+  // with the float instruction, step by step as above. Where all waves do
+  // (entries of 1e15 on both sides), 30000^2 at k = 50 takes 2.2 ms (A H^T) and
+  // 2.0 (A^T W) where ordinary entries take 0.86 and 0.71 and the float
+  // instruction alone took 1.1 and 1.4; four K values at a time, one memory
+  // latency each, took 3.4 and 2.7.
   bool redo = false;
 #pragma unroll
   for (int t = 0; t < MT; ++t)
@@ -285,23 +292,39 @@ __global__ __launch_bounds__(64 * SPW, WPE) void gemm_split_kernel(
     for (int t = 0; t < MT; ++t)
 #pragma unroll
       for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t k0 = kbeg; k0 < kend; k0 += 4) {
-      const int64_t kk = k0 + g;
-      const bool ok = kk < kend;
-      const int64_t kc = ok ? kk : kbeg;
-      float a[MT], b[NT];
+    // a step's product u takes K values k0 + 8 g + u, as load_x has them; the
+    // factor's rows come from the L2, the next step's X is in flight
+    auto step = [&](const XStep<MT>& f, int64_t k0) {
+      constexpr int UB = NT <= 4 ? 8 : 4;   // rows of the factor in registers
 #pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        const float v = TR ? X[kc * ldx + col0 + t] : xr[TR ? 0 : t][kc - 8 * g];
-        a[t] = ok ? v : 0.f;
+      for (int u0 = 0; u0 < 8; u0 += UB) {
+        float y[UB][NT];
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const int64_t kk = k0 + 8 * g + u0 + u, kc = kk < kend ? kk : kbeg;
+#pragma unroll
+          for (int j = 0; j < NT; ++j) y[u][j] = F[kc * ldf + (16 * j + c < kv ? 16 * j + c : 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) {
+            const float v = k0 + 8 * g + u0 + u < kend && 16 * j + c < kv ? y[u][j] : 0.f;
+#pragma unroll
+            for (int t = 0; t < MT; ++t) acc[t][j] = mfma16(f.v[t][u0 + u], v, acc[t][j]);
+          }
       }
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        b[j] = ok && 16 * j + c < kv ? F[kc * ldf + 16 * j + c] : 0.f;
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[t][j] = mfma16(a[t], b[j], acc[t][j]);
+    };
+    if (nfull > 0) load_x(xf[0], kbeg);
+    for (int64_t s = 0; s < nfull; s += 2) {
+      if (s + 1 < nfull) load_x(xf[1], kbeg + (s + 1) * SBK);
+      step(xf[0], kbeg + s * SBK);
+      if (s + 2 < nfull) load_x(xf[0], kbeg + (s + 2) * SBK);
+      if (s + 1 < nfull) step(xf[1], kbeg + (s + 1) * SBK);
+    }
+    if (kt < kend) {
+      load_tail(xf[0]);
+      step(xf[0], kt);
     }
   }
   // element r of tile (t, j): row 4 g + r of the tile, column c
