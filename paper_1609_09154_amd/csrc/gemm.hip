@@ -28,6 +28,8 @@
 // either way), so no transposed copy is made. The factor arrives packed
 // (split.h), written by the kernel that updates it; a workgroup's four waves
 // share each step's slice through LDS.
+#include <algorithm>
+
 #include "common.h"
 #include "grid.h"
 #include "kernels.h"
@@ -399,36 +401,44 @@ __global__ __launch_bounds__(256) void column_product_kernel(
 // step of X in flight ahead of the one being multiplied beat one wave with a
 // deeper ring everywhere (65536^2: 3.2 against 3.6 ms). 64 rows (or columns)
 // of A per wave halve the LDS reads of the factor per byte of A; their
-// accumulators leave no registers for the second sum (FLUSH), so their slabs
-// stay at 8192 values as float slabs did (error 3.1e-7 there, 4.2e-7 with the
-// float instruction). They pay from 2^27 entries of A at ranks up to 64
+// accumulators leave no registers for the second sum (FLUSH), so they are taken
+// only where every slab stays at 8192 values, as float slabs did, with up to
+// 2^28 elements of slabs in all (error 3.1e-7 there, 4.2e-7 with the float
+// instruction; the matrix core cuts bits off, so it grows with the length:
+// 70 x 2,000,003 of
+// nonnegative entries in slabs of 62,501 was off by 2.9e-6, 3.5e-7 now). They pay from 2^27 entries of A at ranks up to 64
 // (16384^2: 0.20 against 0.23 ms; 8192 x 4096: 0.037 against 0.032 ms);
 // below, and at larger ranks, 32 per wave fill the chip better, and every 8
 // steps their sums move to a second set of registers with one rounding, since
 // the matrix core's own accumulation cuts bits off (error 5e-8 at any length
 // up to 16384).
 constexpr int SPLIT_WGS = 512;   // two workgroups per CU
+constexpr int64_t WIDE_LEN = 8192, SLAB_ROOM = (int64_t)1 << 28;
 static bool split_wide(int64_t M, int NT, int64_t K) {
-  return NT <= 4 && M >= 64 && M * K >= ((int64_t)1 << 27);
+  return NT <= 4 && M >= 64 && M * K >= ((int64_t)1 << 27) &&
+         cdiv(K, WIDE_LEN) * M * 16 * NT <= SLAB_ROOM;
 }
 
 // Slabs: doubled from one until the grid holds SPLIT_WGS workgroups and no
-// slab is longer than the shape allows; then full_rounds. 20000^2 at k = 128:
+// slab is longer than the shape allows (up to MAX_PRODUCT_SPLITS of them, or
+// what the wide shape needs); then full_rounds, which lengthens none past that. 20000^2 at k = 128:
 // 3 slabs for 4 (471 workgroups for 628 on 512 places), 591 -> 501 us; 9000 x
 // 7000 at k = 64: 76 -> 59 us; A^T W of 24000 x 16400 at k = 50: 15 for 8, 366 ->
 // 304 us (A H^T, 5 for 8: 355 -> 367); 100003 x 5003 at k = 50: 588 -> 533 us (5 for
 // 2) and 490 -> 460 us (25 for 32).
 int64_t gemm_split_splits(int64_t M, int KP, int64_t K) {
   const bool wide = split_wide(M, KP / 16, K);
-  const int64_t wgs = cdiv(M, (wide ? 64 : 32) * SPW), maxlen = wide ? 8192 : 16384;
+  const int64_t wgs = cdiv(M, (wide ? 64 : 32) * SPW), maxlen = wide ? WIDE_LEN : 16384;
   const int64_t minlen = M * K < ((int64_t)1 << 23) ? 64 : 128;
-  auto room = [&](int64_t s) { return s * M * KP <= ((int64_t)1 << 28); };
+  auto room = [&](int64_t s) { return s * M * KP <= SLAB_ROOM; };
   int64_t s = 1;
   while (wgs * s < SPLIT_WGS && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
   while (K > s * maxlen && s < MAX_PRODUCT_SPLITS && room(2 * s)) s *= 2;
+  if (wide) s = std::max(s, cdiv(K, maxlen));
+  const int64_t most = std::max(s, MAX_PRODUCT_SPLITS);
   return full_rounds(wgs, s, SPLIT_WGS, 2.0 * KP / (double)K, [&](int64_t t) {
-    return t <= MAX_PRODUCT_SPLITS && (t == 1 || K / t >= minlen) && (t <= s || room(t)) &&
-           (K <= t * maxlen || K > s * maxlen);
+    return t <= most && (t == 1 || K / t >= minlen) && (t <= s || room(t)) &&
+           (K <= t * maxlen || (K > s * maxlen && t >= s));
   });
 }
 

@@ -414,7 +414,7 @@ static int64_t auto_splits(int64_t wgs, int64_t M, int64_t N, int64_t K) {
   return full_rounds(wgs, s, 512, 2.0 * N / (double)K, [&](int64_t t) {
     return t <= MAX_PRODUCT_SPLITS && (t == 1 || K / t >= minlen) &&
            (t <= s || t * M * N <= ((int64_t)1 << 28)) &&
-           (K <= t * MAX_SPLIT_LEN || K > s * MAX_SPLIT_LEN);
+           (K <= t * MAX_SPLIT_LEN || (K > s * MAX_SPLIT_LEN && t >= s));
   });
 }
 

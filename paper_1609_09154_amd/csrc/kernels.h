@@ -26,8 +26,9 @@ template <typename T> struct GemmArgs {
 
 // `part` must hold splits * M * N elements when splits > 1. splits <= 0 picks
 // the split count automatically (gemm_auto_splits, at most
-// MAX_PRODUCT_SPLITS for the products: 32, so that products with few output
-// rows still fill the chip).
+// MAX_PRODUCT_SPLITS for the products, 32, so that products with few output
+// rows still fill the chip; gemm_split has more where its slabs would get too
+// long).
 constexpr int64_t MAX_PRODUCT_SPLITS = 32;
 // With nsplit set, a split product is not summed: the slabs stay in part
 // (slab s at part + s M N, ld N) and *nsplit receives their count, for a
