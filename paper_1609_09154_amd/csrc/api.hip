@@ -617,8 +617,8 @@ nmf_status objective(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int 
         s = gram<T>(ctx, w.Ht, n, KP, w.Q, w.part);
         if (s != NMF_OK) return s;
       }
-      HIP_TRY(nmfk::csr_residual_sq(pb.rp, pb.ci, pb.cv, m, w.W, w.Ht, KP, w.obj_part, st));
-      HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nullptr, nmfk::csr_residual_partials(m), w.S,
+      HIP_TRY(nmfk::csr_residual_sq(pb.rp, pb.ci, pb.cv, m, pb.nnz, w.W, w.Ht, KP, w.obj_part, st));
+      HIP_TRY(nmfk::finish_relerr<T>(w.obj_part, nullptr, nmfk::csr_residual_partials(pb.nnz), w.S,
                                      w.Q, KP, w.normA, w.relerr + slot, st));
       return NMF_OK;
     }
@@ -1144,7 +1144,7 @@ nmf_status nmf_csr(nmf_ctx* ctx, int64_t m, int64_t n, int64_t nnz, const int64_
   typedef float T;
   const int KP = kp_sparse(k);
   const bool want_obj = opts->objective != NMF_OBJ_NONE;
-  const int64_t obj_np = std::max<int64_t>(nmfk::csr_residual_partials(m), 1024);
+  const int64_t obj_np = std::max<int64_t>(nmfk::csr_residual_partials(nnz), 1024);
   Carve cv;
   size_t off[18];
   plan_work<T>(m, n, KP, opts->iters, obj_np, 0, cv, off, true);
@@ -1478,7 +1478,7 @@ template <typename T>
 nmf_status relerr_impl(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int k, const T* W,
                        const T* Ht, double* out) {
   const int KP = pb.sparse ? kp_sparse(k) : kp_dense(k);
-  const int64_t obj_np = pb.sparse ? std::max<int64_t>(nmfk::csr_residual_partials(m), 1024)
+  const int64_t obj_np = pb.sparse ? std::max<int64_t>(nmfk::csr_residual_partials(pb.nnz), 1024)
                                    : 2 * nmfk::residual_partials<T>(m, n);
   Carve cv;
   size_t off[18];

@@ -237,10 +237,10 @@ hipError_t csr_transpose(const int64_t* rowptr, const int32_t* colidx, const flo
                          int64_t m, int64_t n, int64_t nnz, int64_t* rowptr_t,
                          int32_t* colidx_t, float* vals_t, void* work, hipStream_t st);
 size_t csr_transpose_work_bytes(int64_t m, int64_t n, int64_t nnz);
-int64_t csr_residual_partials(int64_t m);
+int64_t csr_residual_partials(int64_t nnz);
 hipError_t csr_residual_sq(const int64_t* rowptr, const int32_t* colidx, const float* vals,
-                           int64_t m, const float* W, const float* Ht, int KP, double* partial,
-                           hipStream_t st);
+                           int64_t m, int64_t nnz, const float* W, const float* Ht, int KP,
+                           double* partial, hipStream_t st);
 hipError_t csr_sumsq(const float* vals, int64_t nnz, double* partial, int64_t np,
                      hipStream_t st);
 // Reverse mode through unrolled multiplicative updates (row layout, KP in

@@ -412,13 +412,20 @@ hipError_t csr_long_rows(const int64_t* rowptr, int64_t m, int64_t nnz, int KP, 
 }
 
 // ---------------------------------------------------------------------------
-// Objective for sparse A: per stored entry (a - wh)^2 - wh^2. As in the SpMM
-// the wave splits into groups of KP/4 lanes that each take one stored entry
-// at a time: a group gathers the entry's whole row of Ht with one instruction
-// (a lane per entry, with 64 rows of Ht in flight at 16 bytes each, fetched
-// every line several times over: 28.7 M entries at k = 50 took 1.91 ms, and
-// take 0.93, like the SpMM), keeps its slice of the row of W in registers, and
-// adds the lanes' partial products with lane permutations. Four entries per
+// Objective for sparse A: per stored entry (a - wh)^2 - wh^2. Each wave takes a
+// run of stored entries, whatever rows they belong to (its first row by a
+// 64-way search of rowptr), so that a hub row of a power-law matrix, or a matrix
+// of few rows, is shared by all waves. An evaluation with its Grams against 64
+// rows a block: 500 x 200,000 with 4.9 M entries at k = 50 10.3 ms -> 0.33,
+// 5772 x 38182 with 5.4 M at k = 11 340 -> 114 us, 20 M power-law entries in 10^6
+// rows at k = 50 4.7 -> 1.8 ms, a row of 2 M entries among 500,000 of ten at
+// k = 50 128 -> 2.3 ms; Erdos-Renyi rows as before.
+// As in the SpMM the wave splits into groups of KP/4 lanes that each take one
+// stored entry at a time: a group gathers the entry's whole row of Ht with one
+// instruction (a lane per entry, with 64 rows of Ht in flight at 16 bytes each,
+// fetched every line several times over: 28.7 M entries at k = 50 took 1.91 ms,
+// and take 0.93, like the SpMM), keeps its slice of the row of W in registers,
+// and adds the lanes' partial products with lane permutations. Four entries per
 // group are in flight at once; the sums of squares are in double.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double wave_sum_d(double v) {
@@ -434,52 +441,78 @@ template <int G> __device__ __forceinline__ float lanes_sum(float v) {
   return v;
 }
 
-constexpr int RES_ROWS_PER_BLOCK = 64;
-
 template <int KP>
-__global__ __launch_bounds__(256) void csr_residual_kernel(const int64_t* __restrict__ rowptr,
-                                                           const int32_t* __restrict__ colidx,
-                                                           const float* __restrict__ vals,
-                                                           int64_t m, const float* __restrict__ W,
-                                                           const float* __restrict__ Ht,
-                                                           double* __restrict__ partial) {
+__global__ __launch_bounds__(256) void csr_residual_kernel(
+    const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+    const float* __restrict__ vals, int64_t m, int64_t nnz, int run, const float* __restrict__ W,
+    const float* __restrict__ Ht, double* __restrict__ partial) {
   constexpr int LPN = KP / 4, GPW = 64 / LPN, NU = 4;
+  static_assert(LPN >= NU, "a lane for each entry in flight");
   __shared__ double sh[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int grp = lane / LPN, sub = lane % LPN;
   double local = 0.0;
-  const int64_t r0 = (int64_t)blockIdx.x * RES_ROWS_PER_BLOCK;
-  for (int64_t i = r0 + wave; i < r0 + RES_ROWS_PER_BLOCK && i < m; i += 4) {
-    const float4 w = *reinterpret_cast<const float4*>(W + i * KP + 4 * sub);
-    const int64_t b = rowptr[i], e = rowptr[i + 1];
-    // wave-uniform trip count: every lane joins the lane sums; a group past
-    // the end works on a clamped entry and drops it
-    for (int64_t p0 = b; p0 < e; p0 += NU * GPW) {
-      int32_t j[NU];
-      float a[NU];
-      float4 h[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int64_t p = p0 + u * GPW + grp;
-        const int64_t q = p < e ? p : e - 1;
-        j[u] = colidx[q];
-        a[u] = vals[q];
+  // the run's entries, of those that rowptr gives to a row
+  int64_t p = ((int64_t)blockIdx.x * 4 + wave) * run, end = p + run;
+  const int64_t first = rowptr[0], last = rowptr[m] < nnz ? rowptr[m] : nnz;
+  p = p > first ? p : first;
+  end = end < last ? end : last;
+  if (p < end) {
+    // rows lo .. hi - 1 hold the one with rowptr[i] <= p < rowptr[i + 1]
+    int64_t lo = 0, hi = m;
+    while (hi - lo > 64) {
+      const int64_t step = cdiv(hi - lo, 64), i = lo + lane * step;
+      const int c = __popcll(__ballot(rowptr[i < hi ? i : lo] <= p && i < hi));
+      lo += (c - 1) * step;
+      hi = lo + step < hi ? lo + step : hi;
+    }
+    // the ends of rows lo .. lo + 63, one a lane
+    auto row_end = [&](int64_t r) { return r < m ? rowptr[r + 1] : INT64_MAX; };
+    int64_t ends = row_end(lo + lane);
+    while (p < end) {
+      const int q = __popcll(__ballot(ends <= p));   // rows of the window that end before p
+      if (q == 64) {
+        lo += 64;
+        ends = row_end(lo + lane);
+        continue;
       }
+      const int64_t e0 = (int64_t)(((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)(ends >> 32), q) << 32) |
+                                   (unsigned)__builtin_amdgcn_readlane((int)ends, q));
+      const int64_t e = e0 < end ? e0 : end;
+      const float4 w = *reinterpret_cast<const float4*>(W + (lo + q) * KP + 4 * sub);
+      // a group past the row's end works on a clamped entry and drops it
+      for (; p < e; p += NU * GPW) {
+        int32_t j[NU];
+        float a[NU];
+        float4 h[NU];
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
-        h[u] = *reinterpret_cast<const float4*>(Ht + (int64_t)j[u] * KP + 4 * sub);
+        for (int u = 0; u < NU; ++u) {
+          const int64_t s = p + u * GPW + grp, t = s < e ? s : e - 1;
+          j[u] = colidx[t];
+          a[u] = vals[t];
+        }
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        float wh = w.x * h[u].x;
-        wh = fmaf(w.y, h[u].y, wh);
-        wh = fmaf(w.z, h[u].z, wh);
-        wh = fmaf(w.w, h[u].w, wh);
-        wh = lanes_sum<LPN>(wh);
-        if (sub == 0 && p0 + u * GPW + grp < e) {
-          const double d = (double)a[u] - (double)wh;
-          local += d * d - (double)wh * (double)wh;
+        for (int u = 0; u < NU; ++u)
+          h[u] = *reinterpret_cast<const float4*>(Ht + (int64_t)j[u] * KP + 4 * sub);
+        // lane u of a group squares its entry u
+        float wu = 0.f, au = 0.f;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          float wh = w.x * h[u].x;
+          wh = fmaf(w.y, h[u].y, wh);
+          wh = fmaf(w.z, h[u].z, wh);
+          wh = fmaf(w.w, h[u].w, wh);
+          wh = lanes_sum<LPN>(wh);
+          wu = sub == u ? wh : wu;
+          au = sub == u ? a[u] : au;
+        }
+        if (sub < NU && p + sub * GPW + grp < e) {
+          const double d = (double)au - (double)wu;
+          local += d * d - (double)wu * (double)wu;
         }
       }
+      p = e;
     }
   }
   local = wave_sum_d(local);
@@ -488,14 +521,27 @@ __global__ __launch_bounds__(256) void csr_residual_kernel(const int64_t* __rest
   if (threadIdx.x == 0) partial[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-int64_t csr_residual_partials(int64_t m) { return cdiv(m, RES_ROWS_PER_BLOCK); }
+// Entries of a wave's run: so many that the chip's 8192 waves take one each, at
+// least 64 (four or more steps of a wave) and at most 2048.
+static int residual_run(int64_t nnz) {
+  const int64_t r = round_up(cdiv(nnz, 8192), 64);
+  return (int)(r < 64 ? 64 : r > 2048 ? 2048 : r);
+}
+int64_t csr_residual_partials(int64_t nnz) {
+  return nnz > 0 ? cdiv(nnz, 4 * (int64_t)residual_run(nnz)) : 1;
+}
 
 hipError_t csr_residual_sq(const int64_t* rowptr, const int32_t* colidx, const float* vals,
-                           int64_t m, const float* W, const float* Ht, int KP, double* partial,
-                           hipStream_t st) {
-  const unsigned blocks = (unsigned)cdiv(m, RES_ROWS_PER_BLOCK);
+                           int64_t m, int64_t nnz, const float* W, const float* Ht, int KP,
+                           double* partial, hipStream_t st) {
+  const unsigned blocks = (unsigned)csr_residual_partials(nnz);
+  const int run = residual_run(nnz);
   switch (KP) {
-#define C(K) case K: csr_residual_kernel<K><<<blocks, 256, 0, st>>>(rowptr, colidx, vals, m, W, Ht, partial); break;
+#define C(K)                                                                                   \
+  case K:                                                                                      \
+    csr_residual_kernel<K><<<blocks, 256, 0, st>>>(rowptr, colidx, vals, m, nnz, run, W, Ht,   \
+                                                   partial);                                   \
+    break;
     C(16) C(32) C(64) C(128)
 #undef C
     default: return hipErrorInvalidValue;
