@@ -718,8 +718,8 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
   const bool hand = (o->algo == NMF_MU || o->algo == NMF_HALS) && !pgstop && !pb.sparse &&
                     !pb.lp;
   const nmfk::ShareOf upd = o->algo == NMF_MU ? nmfk::ShareOf::MU : nmfk::ShareOf::HALS;
-  int* nsp_w = hand && nmfk::takes_slabs(upd, m) ? &nsp_w_v : nullptr;
-  int* nsp_h = hand && nmfk::takes_slabs(upd, n) ? &nsp_h_v : nullptr;
+  int* nsp_w = hand && nmfk::takes_slabs(upd, m, KP) ? &nsp_w_v : nullptr;
+  int* nsp_h = hand && nmfk::takes_slabs(upd, n, KP) ? &nsp_h_v : nullptr;
   // MU and HALS at KP <= 64 write the copies the next product
   // reads from their own output tiles (not HALS's W, which the
   // normalisation rescales after the sweep)

@@ -140,7 +140,7 @@ int share_rows(ShareOf u, int64_t rows, int KP);
 // Whether the update at `rows` rows takes a product's split slabs without
 // losing occupancy (the HALS sweep's slab sums need registers that its
 // many-row forms share out among more waves).
-bool takes_slabs(ShareOf u, int64_t rows);
+bool takes_slabs(ShareOf u, int64_t rows, int KP);
 // The same shares of X^T X over blocks of rpb rows (a share_rows value) for
 // a factor that no update produced (KP <= 64).
 template <typename T>

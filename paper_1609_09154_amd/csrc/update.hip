@@ -272,7 +272,13 @@ hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int 
   return NMF_LAUNCH_CHECK();
 }
 
-bool takes_slabs(ShareOf u, int64_t rows) { return u == ShareOf::MU || hals_tpr(rows) == 16; }
+bool takes_slabs(ShareOf u, int64_t rows, int KP) {
+  // mu_rows_lds_kernel reads P a row per thread, one slab after another: with the
+  // 16 to 32 slabs of a small product it took longer than with the ordered sum's
+  // launch in front of it (an iteration: float 3584 x 768 at k = 81 782 us, 411 with
+  // the sum apart, double 5504 x 1024 at k = 80 966 and 543)
+  return u == ShareOf::MU ? KP <= 64 : hals_tpr(rows) == 16;
+}
 
 int share_rows(ShareOf u, int64_t rows, int KP) {
   if (KP > 64 || KP % 16 || KP < 16) return 0;
