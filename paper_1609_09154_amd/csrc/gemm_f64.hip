@@ -152,18 +152,13 @@ __global__ __launch_bounds__(256, WPE) void gemm_nn_kernel(
 // ---------------------------------------------------------------------------
 // Column of X that lane column c feeds into M-tile t. Vector path: tile t
 // takes columns m0 + 16*VEC*(t/VEC) + VEC*c + t%VEC (one 16-byte load per
-// lane covers VEC tiles); scalar path: m0 + 16 t + c. Runs past the last
-// column are moved back to end there, so that every wave runs the same
-// pipelined loop; the lanes that then share a column compute and store the
-// same value. (A wave with columns past the end used to take a guarded loop of
-// one memory latency per four rows: 85 of the 93 us of a 3000 x 1700 product
-// at k = 40.)
+// lane covers VEC tiles); scalar path: m0 + 16 t + c, those past the last column
+// on a copy of it.
 template <typename T, bool VX>
 __device__ __forceinline__ int64_t tn_col(int64_t m0, int t, int c, int64_t M) {
   constexpr int VEC = Tr<T>::VEC;
   if constexpr (VX) {
-    const int64_t b = m0 + 16 * VEC * (t / VEC) + VEC * c;
-    return (b < M - VEC ? b : M - VEC) + t % VEC;
+    return m0 + 16 * VEC * (t / VEC) + VEC * c + t % VEC;
   } else {
     const int64_t b = m0 + 16 * t + c;
     return b < M ? b : M - 1;
@@ -194,8 +189,16 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
   typedef typename Tr<T>::acc4 acc4;
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4, c = lane & 15;
-  const int64_t m0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * MW);
+  int64_t m0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * MW);
   if (m0 >= M) return;
+  // A vector wave with columns past the end is moved back to end at the last
+  // one (M >= 16 MW): it runs the same loop as the others, with loads at
+  // constant distances, and computes and stores some of its neighbour's columns
+  // once more, the same values. (A guarded loop of one memory latency per four
+  // rows took 85 of the 93 us of a 3000 x 1700 product at k = 40; moving back
+  // each lane by itself cost an address per load: 7424 x 3648 at k = 35, 54 ->
+  // 68 us.)
+  if (VX && m0 > M - 16 * MW) m0 = M - 16 * MW;
   const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
   const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
   int64_t xc[NQ];
@@ -377,45 +380,51 @@ template hipError_t reduce_splits<double>(const double*, int, int64_t, int64_t, 
 // ---------------------------------------------------------------------------
 // Launch shapes of the double products, two waves per SIMD (TN above rank 80:
 // one, for its registers). A wave takes 64 rows (columns) of A where its two
-// steps in flight fit the registers (NN to rank 64, TN to rank 32: at rank 64
-// the 64-column TN wave spilled and took 2.2 ms for 20000^2, the 32-column one
-// takes 1.17) and the grid still fills the chip; smaller products halve that
-// until it does, down to 16, at low ranks with a deeper pipeline: their time
-// is the latency of a wave's steps (3000 x 1700 at k = 40: 48 workgroups of
-// 64-row waves and 93 us, now 17). 20000^2 at k = 64 runs at 44 TFLOP/s of
-// the 73 that a large matrix product reaches; its register-only pipeline of
-// two steps is what is left.
+// steps in flight fit the registers (NN to rank 64, TN to rank 48, 20000 x 12000
+// at k = 40 7.8 -> 6.1 ms for six iterations; at rank 64 the 64-column TN wave
+// spilled and took 2.2 ms for 20000^2, the 32-column one takes 1.17) and the
+// grid still fills the chip; smaller products halve that until it does, down to
+// 16, at low ranks with a deeper pipeline: their time is the latency of a wave's
+// steps (3000 x 1700 at k = 40: 48 workgroups of 64-row waves and 93 us, now
+// 17). 20000^2 at k = 64 runs at 44 TFLOP/s of the 73 that a large matrix
+// product reaches; its register-only pipeline of two steps is what is left.
 constexpr int WAVES = 4;  // waves per workgroup of the product kernels
 constexpr int prod_stages(int NT, int mw) { return mw == 1 && NT <= 2 ? 4 : 2; }
 constexpr int tn_wpe(int NT) { return NT <= 5 ? 2 : 1; }
 static int prod_mw(GemmKind kind, int NT, int64_t M, int64_t K) {
   const int64_t room = std::max<int64_t>(1, std::min<int64_t>(MAX_PRODUCT_SPLITS, K / 128));
-  int mw = NT <= (kind == GemmKind::NN ? 4 : 2) ? 4 : 2;
-  while (mw > 1 && cdiv(M, 16 * mw * WAVES) * room < 256) mw /= 2;
+  int mw = NT <= (kind == GemmKind::NN ? 4 : 3) ? 4 : 2;
+  while (mw > 1 && (cdiv(M, 16 * mw * WAVES) * room < 256 || M < 16 * mw)) mw /= 2;
   return mw;
 }
 
-// Split the reduction until the grid has two workgroups per CU, keeping every
-// split at least 128 long. A small product (under 2^26 multiply-adds, such as
-// a 2000 x 1000 matrix at k = 10) may split down to slabs of 64: at that size
-// the partials cost little. No split is longer than MAX_SPLIT_LEN while the
-// partials stay under 2^28 elements. Then full_rounds: 20000^2 at k = 64 1.14 ->
-// 1.00 ms in either direction, 9000 x 7000 at k = 64 248 -> 204 and 220 -> 199 us,
-// 12000 x 10000 at k = 100 545 -> 483 us (A^T W; A H^T 466 -> 485).
+// Slabs of the reduction: of the counts up to MAX_PRODUCT_SPLITS whose slabs are
+// at least 128 long (64 in a product under 2^26 multiply-adds, such as a 2000 x
+// 1000 matrix at k = 10, where they cost little), none longer than MAX_SPLIT_LEN
+// while all hold at most 2^28 elements, the one with the fullest rounds of a
+// workgroup per CU after what its slabs cost, 2 N / K of the product's time each:
+// the slab is written by the product and read by the row update, whose few
+// workgroups are slower at it. A second workgroup per CU brings nothing, since
+// one already keeps the CU's share of the memory busy. Runs of six HALS
+// iterations with at least 512 workgroups, and now: 7424 x 3648 at k = 24 1010 ->
+// 882 us, 8192 x 4096 at k = 8 1000 -> 924, 9000 x 7000 at k = 40 2198 -> 1982,
+// 16384 x 8192 at k = 60 4.91 -> 4.49 ms, 20000 x 12000 at k = 24 5.67 -> 4.93;
+// half that cost per slab takes 1 to 7% longer on the last.
 constexpr int64_t MAX_SPLIT_LEN = 8192;
 static int64_t auto_splits(int64_t wgs, int64_t M, int64_t N, int64_t K) {
-  const int64_t out_elems = M * N;
   const int64_t minlen = M * N * K < ((int64_t)1 << 26) ? 64 : 128;
+  auto room = [&](int64_t t) { return t * M * N <= ((int64_t)1 << 28); };
   int64_t s = 1;
-  while (wgs * s < 512 && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
-  while (K > s * MAX_SPLIT_LEN && s < MAX_PRODUCT_SPLITS &&
-         2 * s * out_elems <= ((int64_t)1 << 28))
-    s *= 2;
-  return full_rounds(wgs, s, 512, 2.0 * N / (double)K, [&](int64_t t) {
-    return t <= MAX_PRODUCT_SPLITS && (t == 1 || K / t >= minlen) &&
-           (t <= s || t * M * N <= ((int64_t)1 << 28)) &&
-           (K <= t * MAX_SPLIT_LEN || (K > s * MAX_SPLIT_LEN && t >= s));
-  });
+  while (K > s * MAX_SPLIT_LEN && s < MAX_PRODUCT_SPLITS && room(s + 1)) ++s;
+  int64_t best = s;
+  double top = 0.0;
+  for (int64_t t = s; t <= MAX_PRODUCT_SPLITS && (t == s || (K / t >= minlen && room(t))); ++t) {
+    const double rounds = (double)(wgs * t) / 256.0;
+    const double score = rounds / (double)cdiv(wgs * t, 256) /
+                         (t > 1 ? 1.0 + 4.0 * (double)N * (double)t / (double)K : 1.0);
+    if (score > top) best = t, top = score;
+  }
+  return best;
 }
 
 template <typename T, int NT, int MW>
@@ -465,22 +474,24 @@ static void gram_launch(const GemmArgs<T>& a, int64_t splits, int64_t kchunk, T*
         <<<grid, 64, 0, st>>>(a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
 }
 
-// TN streams A past the caches (non-temporal loads) where A is larger than the
-// 256 MB last-level cache that would keep it for the next product. NN's load
+// TN streams A past the caches (non-temporal loads) where A and the transposed
+// copy that the other direction reads are together larger than the 256 MB
+// last-level cache, which would keep them for the next iteration (8192 x 4096 at
+// k = 8, 268 MB each: 3 to 4% of a run). NN's load
 // instructions take half a line of a row each, and the other half has to be
 // in the cache when the next asks for it.
 template <typename T, int NT>
 static void prod_dispatch(GemmKind kind, const GemmArgs<T>& a, int64_t splits, int64_t kchunk,
                           T* D, int64_t ldd, int64_t dsplit, hipStream_t st) {
-  const int mw = a.M < 2 ? 1 : prod_mw(kind, NT, a.M, a.K);
+  const int mw = prod_mw(kind, NT, a.M, a.K);
   if (kind == GemmKind::NN) {
     if constexpr (NT <= 4)
       if (mw == 4) return nn_launch<T, NT, 4>(a, splits, kchunk, D, ldd, dsplit, st);
     if (mw == 2) return nn_launch<T, NT, 2>(a, splits, kchunk, D, ldd, dsplit, st);
     return nn_launch<T, NT, 1>(a, splits, kchunk, D, ldd, dsplit, st);
   }
-  const bool stream = a.M * a.K * (int64_t)sizeof(T) > ((int64_t)1 << 28);
-  if constexpr (NT <= 2) {
+  const bool stream = a.M * a.K * (int64_t)sizeof(T) > ((int64_t)1 << 27);
+  if constexpr (NT <= 3) {
     if (mw == 4 && stream)
       return tn_launch<T, NT, 4, true, true>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);
     if (mw == 4)
