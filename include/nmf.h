@@ -379,7 +379,7 @@ nmf_status nmf_mu_unrolled_backward(nmf_ctx* ctx, nmf_dtype dtype, int64_t m,
  * piece that is follows the last bits of the forward pass where an entry comes
  * close to zero; the forward pass and its recomputation are the same bits. Its
  * factors are nmf_dense's bit for bit in NMF_F64, and in NMF_F32 for m n <= 65536
- * (past that nmf_dense takes faster products of another order of summation:
+ * (past that nmf_dense may take faster products of another order of summation:
  * float rounding apart). Dense A, NMF_F32 or NMF_F64, 1 <= k <= 64. The checkpoint buffer has
  * nmf_mu_ckpt_elems(m, n, k, T, c) elements, as for MU, and the backward
  * pass must be given the same m, n, A, k, T and c as the forward pass. */

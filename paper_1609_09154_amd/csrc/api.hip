@@ -370,15 +370,26 @@ int64_t product_splits(nmfk::GemmKind kind, int64_t rows, int KP, int64_t red, b
   return std::max(s, nmfk::gemm_f32_splits(kind, rows, KP, red));
 }
 
-// Whether nmf_dense forms the products of a float HALS iteration with the float
-// instruction, as the unrolled layer does at every size (gemm_f32.hip says why).
-// Up to 2^16 entries of A both then give the same factors bit for bit, which a
-// program that checks one against the other on a small case relies on, for a run
-// of ten iterations on 300 x 200 at k = 10 in 513 us instead of 430; past it the
-// bfloat16 splits are worth more than the last bits (2000 x 1000 at k = 50: 2180
-// us a run against 782, 65536^2 87 ms against 66).
+// Whether nmf_dense forms its float products with the float instruction
+// (gemm_f32) rather than from bfloat16 splits (gemm_split):
+// - HALS up to 2^16 entries of A, as the unrolled layer does at every size
+//   (gemm_f32.hip says why). Both then give the same factors bit for bit, which
+//   a program that checks one against the other on a small case relies on, for
+//   a run of ten iterations on 300 x 200 at k = 10 in 513 us instead of 430.
+// - Small A of whole 64-row and 64-column waves at low rank, where a product is
+//   the latency of its launch and of a few steps, and gemm_split's packed factor
+//   is one more launch for ABPP and a longer tail for the others. Runs of ten
+//   iterations, float instruction against splits: 512^2 at k = 16 ABPP 556
+//   against 653 us, HALS 411 and 441, MU 294 and 317; 2048 x 1984 at k = 16 682,
+//   490, 360 against 762, 516, 377; 1024^2 at k = 30 812, 510, 362 against 905,
+//   532, 374. Past the lines the splits win: 4096 x 2048 at k = 16 ABPP 872 against
+//   857, HALS 574 and 537; 2048 x 1024 at k = 30 ABPP 953 and 941, HALS 631 and
+//   557; 512^2 at k = 50 MU 488 and 443. So they do where a wave is ragged, which
+//   gemm_f32 reads four rows at a time (500^2 at k = 16: HALS 559 against 480).
 bool f32_sums(int algo, int64_t m, int64_t n, int KP) {
-  return algo == NMF_HALS && KP <= 64 && m * n <= ((int64_t)1 << 16);
+  if (algo == NMF_HALS && KP <= 64 && m * n <= ((int64_t)1 << 16)) return true;
+  return m % 64 == 0 && n % 64 == 0 &&
+         ((KP == 16 && m * n < ((int64_t)1 << 22)) || (KP == 32 && m * n <= ((int64_t)1 << 20)));
 }
 
 template <typename T>
@@ -683,7 +694,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
   }
   // The factors' copies for the dense products: gemm_split always reads them;
   // double ones read 16-byte runs of them, so their rows must stay 16-byte
-  // aligned, and below 2^22 entries of A they (and gemm_f32, taken only there)
+  // aligned, and below 2^22 entries of A they (and gemm_f32, taken below that only)
   // read the factors in place (the copy's launch would cost more than its loads
   // save).
   const bool dense = !pb.sparse && !pb.lp;

@@ -4,9 +4,10 @@
 //   NN:  D (M x N) = X (M x K) Y        X = A, Y = H^T
 //   TN:  D (M x N) = X^T Y, X (K x M)   X = A, Y = W; or X = A^T, Y = H^T
 //
-// Every other float product takes gemm.hip's bfloat16 splits, which are faster
-// on large matrices. These form the forward pass of the unrolled float HALS
-// layer, where what counts is the order of the sums: the layer's gradient
+// Most float products take gemm.hip's bfloat16 splits, which are faster on large
+// matrices. These are for small ones of whole waves at low rank (f32_sums in
+// api.hip says where), and for the forward pass of the unrolled float HALS
+// layer at every size, where what counts is the order of the sums: the layer's gradient
 // jumps where an entry of the sweep passes zero (its mask is x > 0), so two
 // forward passes that differ in the last bit give gradients that agree to
 // 1e-7 on most inputs and to 1e-3 where one entry of a few thousand lies on
