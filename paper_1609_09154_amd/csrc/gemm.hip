@@ -419,9 +419,13 @@ static bool split_wide(int64_t M, int NT, int64_t K) {
          cdiv(K, WIDE_LEN) * M * 16 * NT <= SLAB_ROOM;
 }
 
-// Slabs: doubled from one until the grid holds SPLIT_WGS workgroups and no
-// slab is longer than the shape allows (up to MAX_PRODUCT_SPLITS of them, or
-// what the wide shape needs); then full_rounds, which lengthens none past that. 20000^2 at k = 128:
+// Slabs: no longer than the shape allows (up to MAX_PRODUCT_SPLITS of them, or
+// what the wide shape needs). From 2^23 entries of A on, the count with the
+// fullest rounds of SPLIT_WGS workgroups (fullest_rounds): 7552 x 3136 at k = 6 364 ->
+// 344 us a run of four HALS iterations, 1984 x 61888 968 -> 932, 20000^2 at k = 100
+// 4.93 -> 4.58 ms. Below, doubled from one until the grid holds that many, then
+// full_rounds: there a product is the latency of its slabs, and with fewer of
+// them 2048 x 2000 at k = 6 252 -> 267 us. 20000^2 at k = 128:
 // 3 slabs for 4 (471 workgroups for 628 on 512 places), 591 -> 501 us; 9000 x
 // 7000 at k = 64: 76 -> 59 us; A^T W of 24000 x 16400 at k = 50: 15 for 8, 366 ->
 // 304 us (A H^T, 5 for 8: 355 -> 367); 100003 x 5003 at k = 50: 588 -> 533 us (5 for
@@ -431,13 +435,19 @@ int64_t gemm_split_splits(int64_t M, int KP, int64_t K) {
   const int64_t wgs = cdiv(M, (wide ? 64 : 32) * SPW), maxlen = wide ? WIDE_LEN : 16384;
   const int64_t minlen = M * K < ((int64_t)1 << 23) ? 64 : 128;
   auto room = [&](int64_t s) { return s * M * KP <= SLAB_ROOM; };
+  const double cost = 2.0 * KP / (double)K;
   int64_t s = 1;
+  if (M * K >= ((int64_t)1 << 23)) {
+    while (K > s * maxlen && (wide || (s < MAX_PRODUCT_SPLITS && room(s + 1)))) ++s;
+    const int64_t most = std::max(s, MAX_PRODUCT_SPLITS);
+    return fullest_rounds(wgs, s, SPLIT_WGS, cost, [&](int64_t t) {
+      return t <= most && K / t >= minlen && room(t);
+    });
+  }
   while (wgs * s < SPLIT_WGS && K / (2 * s) >= minlen && s < MAX_PRODUCT_SPLITS) s *= 2;
   while (K > s * maxlen && s < MAX_PRODUCT_SPLITS && room(2 * s)) s *= 2;
-  if (wide) s = std::max(s, cdiv(K, maxlen));
-  const int64_t most = std::max(s, MAX_PRODUCT_SPLITS);
-  return full_rounds(wgs, s, SPLIT_WGS, 2.0 * KP / (double)K, [&](int64_t t) {
-    return t <= most && (t == 1 || K / t >= minlen) && (t <= s || room(t)) &&
+  return full_rounds(wgs, s, SPLIT_WGS, cost, [&](int64_t t) {
+    return t <= MAX_PRODUCT_SPLITS && (t == 1 || K / t >= minlen) && (t <= s || room(t)) &&
            (K <= t * maxlen || (K > s * maxlen && t >= s));
   });
 }

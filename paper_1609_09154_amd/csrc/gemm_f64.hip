@@ -416,15 +416,9 @@ static int64_t auto_splits(int64_t wgs, int64_t M, int64_t N, int64_t K) {
   auto room = [&](int64_t t) { return t * M * N <= ((int64_t)1 << 28); };
   int64_t s = 1;
   while (K > s * MAX_SPLIT_LEN && s < MAX_PRODUCT_SPLITS && room(s + 1)) ++s;
-  int64_t best = s;
-  double top = 0.0;
-  for (int64_t t = s; t <= MAX_PRODUCT_SPLITS && (t == s || (K / t >= minlen && room(t))); ++t) {
-    const double rounds = (double)(wgs * t) / 256.0;
-    const double score = rounds / (double)cdiv(wgs * t, 256) /
-                         (t > 1 ? 1.0 + 4.0 * (double)N * (double)t / (double)K : 1.0);
-    if (score > top) best = t, top = score;
-  }
-  return best;
+  return fullest_rounds(wgs, s, 256, 4.0 * (double)N / (double)K, [&](int64_t t) {
+    return t <= MAX_PRODUCT_SPLITS && K / t >= minlen && room(t);
+  });
 }
 
 template <typename T, int NT, int MW>
