@@ -172,11 +172,12 @@ struct Shares {
   int64_t blocks() const { return std::max(nbm, nbn); }
 };
 
-Shares plan_shares(int algo, int64_t m, int64_t n, int KP) {
+Shares plan_shares(int algo, int64_t m, int64_t n, int KP, int esize) {
   Shares sh;
   if (algo != NMF_MU && algo != NMF_HALS) return sh;
   const nmfk::ShareOf u = algo == NMF_MU ? nmfk::ShareOf::MU : nmfk::ShareOf::HALS;
-  const int rpm = nmfk::share_rows(u, m, KP), rpn = nmfk::share_rows(u, n, KP);
+  const int64_t mx = std::max(m, n);
+  const int rpm = nmfk::share_rows(u, m, mx, KP, esize), rpn = nmfk::share_rows(u, n, mx, KP, esize);
   if (rpm <= 0 || rpn <= 0) return sh;
   const int64_t nbm = cdiv(m, rpm), nbn = cdiv(n, rpn);
   if (nbm > SHARE_CAP || nbn > SHARE_CAP) return sh;
@@ -197,8 +198,9 @@ bool gsum_fits(const Shares& sh, int KP) {
 // Elements of the updates' share workspace for an m x n problem: room for
 // either update's shares, and for two sets (one per factor) where the MU
 // updates add them themselves.
-int64_t share_elems(int64_t m, int64_t n, int KP) {
-  const Shares mu = plan_shares(NMF_MU, m, n, KP), ha = plan_shares(NMF_HALS, m, n, KP);
+int64_t share_elems(int64_t m, int64_t n, int KP, int esize) {
+  const Shares mu = plan_shares(NMF_MU, m, n, KP, esize);
+  const Shares ha = plan_shares(NMF_HALS, m, n, KP, esize);
   int64_t need = std::max(mu.blocks(), ha.blocks()) * KP * KP;
   if (gsum_fits(mu, KP)) need = std::max<int64_t>(need, 2 * mu.blocks() * KP * KP);
   return need;
@@ -329,11 +331,13 @@ template <typename T>
 nmf_status local_update(nmf_ctx* ctx, int algo, T* X, nmfk::Split<T> P, const T* G,
                         int64_t rows, int k, int KP, const nmf_opts* o, int* status,
                         unsigned long long* pivots, double* ginv, T* Gslab = nullptr,
-                        T* Xt = nullptr, const T* Xs = nullptr, int gn = 1) {
+                        T* Xt = nullptr, const T* Xs = nullptr, int gn = 1,
+                        int rpb = 0) {
   hipStream_t st = ctx->stream;
   if (gn != 1 && algo != NMF_MU) return fail(ctx, NMF_EINVAL, "only MU sums Gram shares");
   if (algo == NMF_MU)
-    HIP_TRY(nmfk::mu_rows<T>(X, X, P, G, rows, k, KP, (T)o->eps_mu, Xt, nullptr, Gslab, st, gn));
+    HIP_TRY(nmfk::mu_rows<T>(X, X, P, G, rows, k, KP, (T)o->eps_mu, Xt, nullptr, Gslab, st, gn,
+                             rpb));
   else if (algo == NMF_HALS)
     HIP_TRY(nmfk::hals_rows<T>(X, X, P, G, rows, k, KP, Xt, Gslab, st, Xs));
   else {
@@ -434,7 +438,7 @@ size_t plan_work(int64_t m, int64_t n, int KP, int iters, int64_t obj_np, int64_
   off[16] = cv.take<double>(4);
   // the updates' Gram shares, for either update that writes them (apart from
   // the product slabs, which an update may still be reading)
-  off[17] = cv.take<T>(share_elems(m, n, KP));
+  off[17] = cv.take<T>(share_elems(m, n, KP, sizeof(T)));
   return cv.off;
 }
 
@@ -714,7 +718,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
   // the updates' Gram shares (w.gsl); qready: Q already holds the current H's
   // Gram
   int nsp_w_v = 1, nsp_h_v = 1;
-  const Shares sh = plan_shares(o->algo, m, n, KP);
+  const Shares sh = plan_shares(o->algo, m, n, KP, sizeof(T));
   T* gsl = sh.on() ? w.gsl : nullptr;
   bool qready = false;
   // small MU problems: each update sums the other factor's shares itself (S
@@ -767,7 +771,7 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
     tm.mark(PH_LUC);
     const nmfk::Split<T> spw{nsp_w_v > 1 ? w.part : w.P, nsp_w_v, m * KP};
     RUN(local_update<T>(ctx, o->algo, w.W, spw, gin ? gslq : w.Q, m, k, KP, o, w.status,
-                        w.pivots, w.ginv, gsl, Wt_upd, nullptr, gin ? (int)sh.nbn : 1));
+                        w.pivots, w.ginv, gsl, Wt_upd, nullptr, gin ? (int)sh.nbn : 1, sh.rpm));
     // H given W: S = W^T W, (HALS: normalise), R = A^T W, UpdateH.
     if (!gin) tm.mark(PH_GRAM);
     if (!sh.on()) RUN(gram<T>(ctx, w.W, m, KP, w.S, w.part));
@@ -787,7 +791,8 @@ nmf_status run_au_nmf(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, int
     const nmfk::Split<T> sph{nsp_h_v > 1 ? w.part : w.R, nsp_h_v, n * KP};
     RUN(local_update<T>(ctx, o->algo, w.Ht, sph, gin ? gsl : w.S, n, k, KP, o, w.status,
                         w.pivots, w.ginv, gslq, own_t && next_t ? w.Hk : nullptr,
-                        o->algo == NMF_HALS ? w.norms : nullptr, gin ? (int)sh.nbm : 1));
+                        o->algo == NMF_HALS ? w.norms : nullptr, gin ? (int)sh.nbm : 1,
+                        sh.rpn));
     if (sh.on()) {
       // the next iteration's Q, from the H update's shares
       if (!gin) {
@@ -1826,7 +1831,7 @@ nmf_status mu_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, i
   nmfk::Split<T> sp;
   T* Pd = P ? P : w.P;
   T* Rd = R ? R : w.R;
-  const Shares sh = gsl ? plan_shares(NMF_MU, m, n, KP) : Shares{};
+  const Shares sh = gsl ? plan_shares(NMF_MU, m, n, KP, sizeof(T)) : Shares{};
   if (!sh.on()) gsl = nullptr;
   if (gsl) {
     if (!*qready) HIP_TRY(nmfk::gram_shares<T>(Ht, n, KP, sh.rpn, gsl, st));
@@ -1836,7 +1841,7 @@ nmf_status mu_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, i
   }
   if ((s = mu_prod_AF<T>(ctx, pb, m, n, Ht, k, KP, Pd, w, *ft, &sp)) != NMF_OK) return s;
   HIP_TRY(nmfk::mu_rows<T>(W, Wn, sp, Q, m, k, KP, eps, tW ? w.Ft : nullptr,
-                           sp.n > 1 ? P : nullptr, gsl, st));
+                           sp.n > 1 ? P : nullptr, gsl, st, 1, sh.rpm));
   if (gsl) {
     if ((s = sum_shares<T>(ctx, gsl, sh.nbm, KP, S, St)) != NMF_OK) return s;
   } else if ((s = gram<T>(ctx, Wn, m, KP, S, w.part, St)) != NMF_OK) {
@@ -1844,7 +1849,7 @@ nmf_status mu_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, i
   }
   if ((s = mu_prod_AtF<T>(ctx, pb, m, n, Wn, k, KP, Rd, w, tW, &sp)) != NMF_OK) return s;
   HIP_TRY(nmfk::mu_rows<T>(Ht, Htn, sp, S, n, k, KP, eps, tH ? w.Ft : nullptr,
-                           sp.n > 1 ? R : nullptr, gsl, st));
+                           sp.n > 1 ? R : nullptr, gsl, st, 1, sh.rpn));
   *ft = tH;
   if (gsl) *qready = true;
   return NMF_OK;
@@ -1867,7 +1872,7 @@ nmf_status mu_forward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int64
   size_t off[8];
   mu_plan_common<T>(m, n, KP, cv, off);
   // the updates' Gram shares
-  const int64_t nbs = plan_shares(NMF_MU, m, n, KP).blocks();
+  const int64_t nbs = plan_shares(NMF_MU, m, n, KP, sizeof(T)).blocks();
   const size_t ogsl = cv.take<T>(nbs * KP * KP);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
@@ -1928,7 +1933,7 @@ nmf_status mu_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int6
   const int64_t nbm = nmfk::mu_adjoint_blocks<T>(m, KP), nbn = nmfk::mu_adjoint_blocks<T>(n, KP);
   const size_t ogsl = cv.take<T>(std::max(nbm, nbn) * KP * KP);
   // the recomputation's Gram shares
-  const int64_t nbs = plan_shares(NMF_MU, m, n, KP).blocks();
+  const int64_t nbs = plan_shares(NMF_MU, m, n, KP, sizeof(T)).blocks();
   const size_t orsl = cv.take<T>(nbs * KP * KP);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
@@ -2046,7 +2051,7 @@ nmf_status hals_iteration(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n,
   nmfk::Split<T> sp;
   T* Wsw = Wp ? Wp : Wn;    // the W sweep's output
   T* Hsc = Hc ? Hc : Htn;   // H^T after the rescaling
-  const Shares sh = gsl ? plan_shares(NMF_HALS, m, n, KP) : Shares{};
+  const Shares sh = gsl ? plan_shares(NMF_HALS, m, n, KP, sizeof(T)) : Shares{};
   if (!sh.on()) gsl = nullptr;
   if (gsl) {
     if (!*qready) HIP_TRY(nmfk::gram_shares<T>(Ht, n, KP, sh.rpn, gsl, st));
@@ -2082,7 +2087,7 @@ nmf_status hals_forward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, int
   size_t off[8];
   mu_plan_common<T>(m, n, KP, cv, off, true);
   const size_t onrm = cv.take<T>(KP);
-  const int64_t nbs = plan_shares(NMF_HALS, m, n, KP).blocks();
+  const int64_t nbs = plan_shares(NMF_HALS, m, n, KP, sizeof(T)).blocks();
   const size_t ogsl = cv.take<T>(nbs * KP * KP);   // the sweeps' Gram shares
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
@@ -2148,7 +2153,7 @@ nmf_status hals_backward_impl(nmf_ctx* ctx, int64_t m, int64_t n, const T* A, in
   const int64_t hbm = nmfk::hals_adjoint_blocks<T>(m, KP), hbn = nmfk::hals_adjoint_blocks<T>(n, KP);
   const size_t otsl = cv.take<T>(2 * std::max(hbm, hbn) * KP * KP);
   // the recomputation's Gram shares
-  const int64_t nbs = plan_shares(NMF_HALS, m, n, KP).blocks();
+  const int64_t nbs = plan_shares(NMF_HALS, m, n, KP, sizeof(T)).blocks();
   const size_t orsl = cv.take<T>(nbs * KP * KP);
   const size_t odots = cv.take<double>(2 * KP);
   const size_t odpart = cv.take<double>(nmfk::coldot_partials(KP));

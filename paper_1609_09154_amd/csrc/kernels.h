@@ -119,10 +119,11 @@ hipError_t pack_fp8_t(const float* F, int64_t rows, int KP, uint8_t* Ft, int64_t
 // Xn^T Xn, one KP x KP slab per block of share_rows rows (cdiv(rows,
 // share_rows) of them), for an ordered sum (reduce_splits).
 // mu_rows' gn (KP <= 64 when above 1): G is given as gn KP x KP shares at
-// stride KP * KP, which the update adds in order as it stages them.
+// stride KP * KP, which the update adds in order as it stages them. rpb: rows per
+// block, share_rows' (0: as it would be without shares to sum).
 template <typename T>
 hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int KP, T eps,
-                   T* Xt, T* Pout, T* Gslab, hipStream_t st, int gn = 1);
+                   T* Xt, T* Pout, T* Gslab, hipStream_t st, int gn = 1, int rpb = 0);
 // hals_rows' Xs (nullable, KP entries): the incoming rows are scaled first,
 // x_i *= Xs[i] where Xs[i] > 0 (the normalisation's compensation of H).
 template <typename T>
@@ -134,9 +135,10 @@ hipError_t hals_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, in
 // larger groups to fill it.
 inline int hals_tpr(int64_t rows) { return rows >= 65536 ? 4 : (rows >= 16384 ? 8 : 16); }
 // Rows per block of an update's Gram shares (0: the update writes none at
-// this KP): mu_rows at any row count, hals_rows at `rows` rows.
+// this KP), at `rows` rows of the one factor where the longer of the two has
+// `longer`, in elements of esize bytes.
 enum class ShareOf { MU, HALS };
-int share_rows(ShareOf u, int64_t rows, int KP);
+int share_rows(ShareOf u, int64_t rows, int64_t longer, int KP, int esize);
 // Whether the update at `rows` rows takes a product's split slabs without
 // losing occupancy (the HALS sweep's slab sums need registers that its
 // many-row forms share out among more waves).

@@ -36,18 +36,26 @@ namespace nmfk {
 // CU, and the update of a 2000-row factor keeps 16 CUs at that for 11 us.
 // FINE takes blocks of 32 (KP up to 32) or 16 rows, up to fine_rows; past that
 // the larger blocks fill the chip well enough, and the Gram shares, one per
-// block, would cost more than they save. An MU iteration, double: 300 x 200 at
-// k = 10 29 -> 19 us, 2000 x 1000 at k = 10 34 -> 27, 3000 x 2500 at k = 32 70 ->
-// 59, 8000 x 1000 at k = 40 73 -> 66, 2000 x 1000 at k = 64 58 -> 54; float at
-// k = 10 32 -> 27, at k = 32 47 -> 46, at k = 40 57 -> 53 (and 4000 x 1000 at
-// k = 30 38.5 -> 40.2, 8000 x 1000 at k = 64 57.2 -> 58.7: past the line).
+// block, cost more than they save. Runs of ten MU iterations, the larger blocks
+// against the finer, double: 512^2 at k = 6 370 -> 287 us, 2000 x 1000 at k = 45
+// 715 -> 555, 8000 x 1000 at k = 18 785 -> 652, 12000 x 2000 at k = 45 1670 -> 1450;
+// at k = 60 4000 x 1000 731 -> 652 and 12000 x 2000 1920 -> 1890, 1877 with H fine
+// alone. Float: 512^2 at k = 6 334 -> 303, 4000 x 1000 at k = 6 432 -> 405 with H
+// fine, 444 with both; 3000 x 2500 at k = 30 557 -> 543 and at k = 60 673 -> 638,
+// 4000 x 1000 at k = 30 504 -> 481 with H fine, 495 with both, 6000 x 3000 at k = 60
+// 856 -> 826 and 844; at k = 45 8000 x 1000 756 -> 625. Up to 1024 rows at KP = 32 the
+// larger blocks' shares are few enough for the updates to sum (gsum_fits), which
+// in float is worth more: 512^2 at k = 18 326 against 345 us, 700 x 900 381 against
+// 420 (double 386 and 349, 508 and 430).
 template <int KP, bool FINE> struct RowSplit {
   static constexpr int TPR = FINE ? (KP <= 32 ? 8 : 16) : KP == 48 ? 4 : KP / 8;
   static constexpr int RPT = KP / TPR;
   static constexpr int ROWS = 256 / TPR;
 };
-constexpr bool fine_rows(int64_t rows, int KP) {
-  return rows <= (KP == 48 ? 8192 : KP == 32 ? 3072 : 2048);
+static bool fine_rows(int64_t rows, int64_t longer, int KP, int esize) {
+  if (esize == 8) return rows <= (KP == 64 ? 8192 : 16384);
+  if (KP == 32) return longer > 1024 && rows <= 3072;
+  return rows <= (KP == 16 ? 2048 : KP == 48 ? 16384 : 3072);
 }
 
 // One element of the sum of n <= 64 shares, in double and in the order of
@@ -246,10 +254,10 @@ void launch_mu_rows_tpr_g(const T* X, T* Xn, Split<T> P, const T* G, int64_t row
 
 template <typename T, int KP>
 void launch_mu_rows_tpr(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, T eps,
-                        T* Xt, T* Pout, T* Gslab, int gn, hipStream_t st) {
+                        T* Xt, T* Pout, T* Gslab, int gn, int rpb, hipStream_t st) {
 #define CALL(GS, FI) \
   launch_mu_rows_tpr_g<T, KP, GS, FI>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, st)
-  if (fine_rows(rows, KP)) {
+  if (rpb == RowSplit<KP, true>::ROWS) {
     if (gn > 1) CALL(true, true);
     else CALL(false, true);
   } else {
@@ -261,12 +269,14 @@ void launch_mu_rows_tpr(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows,
 
 template <typename T>
 hipError_t mu_rows(const T* X, T* Xn, Split<T> P, const T* G, int64_t rows, int k, int KP, T eps,
-                   T* Xt, T* Pout, T* Gslab, hipStream_t st, int gn) {
+                   T* Xt, T* Pout, T* Gslab, hipStream_t st, int gn, int rpb) {
   if (rows <= 0) return hipSuccess;
   if (((Xt || Gslab || gn > 1) && KP > 64) || !P.p || P.n < 1 || gn < 1)
     return hipErrorInvalidValue;
   if (gn > (KP == 16 ? 64 : 16)) return hipErrorInvalidValue;
-  KP_SWITCH(KP, (launch_mu_rows_tpr<T, KPc>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, st)),
+  if (rpb == 0) rpb = share_rows(ShareOf::MU, rows, INT64_MAX, KP, sizeof(T));
+  KP_SWITCH(KP, (launch_mu_rows_tpr<T, KPc>(X, Xn, P, G, rows, k, eps, Xt, Pout, Gslab, gn, rpb,
+                                            st)),
             (mu_rows_lds_kernel<T><<<(unsigned)cdiv(rows, LDS_ROWS), LDS_ROWS, 0, st>>>(
                 X, Xn, P, G, rows, k, KP, eps, Pout)));
   return NMF_LAUNCH_CHECK();
@@ -280,10 +290,10 @@ bool takes_slabs(ShareOf u, int64_t rows, int KP) {
   return u == ShareOf::MU ? KP <= 64 : hals_tpr(rows) == 16;
 }
 
-int share_rows(ShareOf u, int64_t rows, int KP) {
+int share_rows(ShareOf u, int64_t rows, int64_t longer, int KP, int esize) {
   if (KP > 64 || KP % 16 || KP < 16) return 0;
   if (u == ShareOf::HALS) return 256 / hals_tpr(rows);
-  if (fine_rows(rows, KP)) return KP <= 32 ? RowSplit<32, true>::ROWS : RowSplit<64, true>::ROWS;
+  if (fine_rows(rows, longer, KP, esize)) return KP <= 32 ? RowSplit<32, true>::ROWS : RowSplit<64, true>::ROWS;
   switch (KP) {
     case 16: return RowSplit<16, false>::ROWS;
     case 32: return RowSplit<32, false>::ROWS;
@@ -741,7 +751,7 @@ hipError_t transpose_out(const T* Ht, int k, int64_t n, int KP, T* H, hipStream_
 
 #define INST(T)                                                                             \
   template hipError_t mu_rows<T>(const T*, T*, Split<T>, const T*, int64_t, int, int, T, T*, \
-                                 T*, T*, hipStream_t, int); \
+                                 T*, T*, hipStream_t, int, int); \
   template hipError_t gram_shares<T>(const T*, int64_t, int, int, T*, hipStream_t); \
   template hipError_t hals_normalize<T>(const T*, T*, int64_t, const T*, T*, int64_t, T*, T*, \
                                         int, int, hipStream_t, T*, FactorCopy);             \
