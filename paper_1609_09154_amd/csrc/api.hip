@@ -1259,6 +1259,18 @@ nmf_status gram_out(nmf_ctx* ctx, const T* X, int64_t rows, int k, int KP, T* G,
 }
 
 template <typename T>
+nmf_status pad_any(nmf_ctx* ctx, const T* X, int64_t rows, int k, int64_t ldx, T* Xp, int KP) {
+  if (ldx == k) {   // one array by itself: no job table to read (3.3 against 2.7 us)
+    HIP_TRY(nmfk::pad_rows<T>(X, rows, k, Xp, KP, ctx->stream));
+    return NMF_OK;
+  }
+  Copies<T> c;
+  c.pad(X, rows, k, ldx, Xp, KP, rows);
+  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
+  return NMF_OK;
+}
+
+template <typename T>
 nmf_status gram_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, int64_t ldx, T* G) {
   const int KP = kp_dense(k);
   const bool direct = in_place(X, k, ldx);
@@ -1269,20 +1281,10 @@ nmf_status gram_impl(nmf_ctx* ctx, int64_t rows, int k, const T* X, int64_t ldx,
   if (s != NMF_OK) return s;
   const T* Xp = X;
   if (!direct) {
-    Copies<T> c;
-    c.pad(X, rows, k, ldx, at<T>(ctx, oX), KP, rows);
-    HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
+    if ((s = pad_any<T>(ctx, X, rows, k, ldx, at<T>(ctx, oX), KP)) != NMF_OK) return s;
     Xp = at<T>(ctx, oX);
   }
   return gram_out<T>(ctx, Xp, rows, k, KP, G, at<T>(ctx, oP));
-}
-
-template <typename T>
-nmf_status pad_any(nmf_ctx* ctx, const T* X, int64_t rows, int k, int64_t ldx, T* Xp, int KP) {
-  Copies<T> c;
-  c.pad(X, rows, k, ldx, Xp, KP, rows);
-  HIP_TRY(nmfk::pad_jobs<T>(c.j, c.n, ctx->stream));
-  return NMF_OK;
 }
 
 nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, const float* A,
