@@ -1234,6 +1234,15 @@ namespace {
 template <typename T> bool in_place(const T* X, int k, int64_t ldx) {
   return kp_dense(k) == k && ldx == k && (uintptr_t)X % 16 == 0;
 }
+// Whether two of the caller's arrays share memory: an output that does with an
+// input, or with another output, is written only after every read and in the
+// order of the arguments, so that the call gives what it would on copies.
+template <typename T> bool overlap(const T* a, int64_t na, const T* b, int64_t nb) {
+  return a && b && na > 0 && nb > 0 && a < b + nb && b < a + na;
+}
+// Elements from the first to the last of a rows x k array of pitch ld.
+inline int64_t extent(int64_t rows, int64_t k, int64_t ld) { return (rows - 1) * ld + k; }
+
 // One launch's copies of the caller's arrays into the padded layout and back.
 template <typename T> struct Copies {
   nmfk::CopyJob<T> j[nmfk::MAX_COPY_JOBS];
@@ -1292,16 +1301,27 @@ nmf_status dense_prod_impl(nmf_ctx* ctx, bool transA, int64_t m, int64_t n, cons
   const int KP = kp_dense(k);
   const int64_t frows = transA ? m : n, orows = transA ? n : m;
   const int64_t splits = nmfk::gemm_split_splits(orows, KP, frows);
+  const bool apart = overlap(Out, orows * k, F, extent(frows, k, ldf)) ||
+                     overlap(Out, orows * k, A, extent(m, n, lda));
   Carve cv;
   const size_t oFp = cv.take<float>(nmfk::split_floats(frows, KP));
-  const size_t oP = cv.take<float>(splits > 1 ? splits * orows * KP : 1);
+  const size_t oP = cv.take<float>(splits > 1 || apart ? splits * orows * KP : 1);
   nmf_status s = ensure_ws(ctx, cv.off);
   if (s != NMF_OK) return s;
   float* Fp = at<float>(ctx, oFp);
+  float* part = at<float>(ctx, oP);
   // the planes from the caller's F, the product straight into the caller's P
+  // (as slabs first where A or F lies in it)
   HIP_TRY(nmfk::pack_split(F, frows, ldf, k, KP, Fp, ctx->stream));
-  HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, k, Out, k, k, orows, KP, frows,
-                           at<float>(ctx, oP), ctx->stream));
+  if (!apart) {
+    HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, k, Out, k, k, orows, KP, frows, part,
+                             ctx->stream));
+    return NMF_OK;
+  }
+  int ns = 1;
+  HIP_TRY(nmfk::gemm_split(transA, A, lda, Fp, F, ldf, k, k, part, KP, KP, orows, KP, frows, part,
+                           ctx->stream, &ns));
+  HIP_TRY(nmfk::reduce_splits<float>(part, ns, orows * KP, orows, k, k, Out, KP, ctx->stream));
   return NMF_OK;
 }
 
@@ -1370,7 +1390,9 @@ template <typename T>
 nmf_status update_impl(nmf_ctx* ctx, int algo, int64_t rows, int k, const T* G, const T* Pm,
                        T* X, const nmf_opts* o, long long* pivots) {
   const int KP = kp_dense(k);
-  const bool direct = in_place(G, k, k) && in_place(Pm, k, k) && in_place(X, k, k);
+  const bool direct = in_place(G, k, k) && in_place(Pm, k, k) && in_place(X, k, k) &&
+                      !overlap(X, rows * k, G, (int64_t)k * k) &&
+                      !overlap(X, rows * k, Pm, rows * k);
   Carve cv;
   const size_t oG = cv.take<T>(direct ? 0 : KP * KP);
   const size_t oP = cv.take<T>(direct ? 0 : rows * KP);
@@ -1458,7 +1480,7 @@ template <typename T>
 nmf_status normalize_impl(nmf_ctx* ctx, int64_t m, int64_t n, int k, T* W, T* Ht, T* S,
                           T* norms) {
   const int KP = kp_dense(k);
-  const bool direct = in_place(W, k, k) && in_place(Ht, k, k);
+  const bool direct = in_place(W, k, k) && in_place(Ht, k, k) && !overlap(W, m * k, Ht, n * k);
   Carve cv;
   const size_t oW = cv.take<T>(direct ? 0 : m * KP);
   const size_t oH = cv.take<T>(direct ? 0 : n * KP);
@@ -1488,7 +1510,12 @@ nmf_status normalize_impl(nmf_ctx* ctx, int64_t m, int64_t n, int k, T* W, T* Ht
   }
   if (S) c.unpad(Sp, k, k, KP, S);
   if (norms) c.unpad(Np, 1, k, KP, norms);
-  if (c.n) HIP_TRY(nmfk::unpad_jobs<T>(c.j, c.n, st));
+  bool apart = false;
+  for (int i = 0; i < c.n; ++i)
+    for (int j = 0; j < i; ++j)
+      apart = apart || overlap(c.j[i].dst, c.j[i].rows * k, c.j[j].dst, c.j[j].rows * k);
+  for (int i = 0; apart && i < c.n; ++i) HIP_TRY(nmfk::unpad_jobs<T>(c.j + i, 1, st));
+  if (!apart && c.n) HIP_TRY(nmfk::unpad_jobs<T>(c.j, c.n, st));
   return NMF_OK;
 }
 
