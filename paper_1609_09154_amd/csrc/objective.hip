@@ -116,10 +116,11 @@ __device__ __forceinline__ void load_a_tile(A4<TA> (&av)[4], const TA* __restric
   }
 }
 
-// Adds the tile's squared differences to sr and, NORM, A's squares to sa.
+// Adds the squares of the tile's A - scale acc to sr and, NORM, A's to sa
+// (scale: a power of two).
 template <bool FULL, bool NORM, typename TACC, typename TA, typename ACC>
-__device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)[4], int64_t m,
-                                         int64_t n, int64_t row0, int64_t col, int lane,
+__device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)[4], double scale,
+                                         int64_t m, int64_t n, int64_t row0, int64_t col, int lane,
                                          double& sr, double& sa) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -127,7 +128,7 @@ __device__ __forceinline__ void add_tile(const A4<TA> (&av)[4], const ACC (&acc)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (!FULL && col + j >= n) continue;
-      const double a = av[r].at(j), d = a - (double)acc[j][r];
+      const double a = av[r].at(j), d = fma(-scale, (double)acc[j][r], a);
       sr = fma(d, d, sr);
       if constexpr (NORM) sa = fma(a, a, sa);
     }
@@ -211,11 +212,10 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
-          acc[j][r] *= SPLIT_UNSCALE;
-        }
+        for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[j][r]) <= 3.402823466e38f);
+      double scale = SPLIT_UNSCALE;
       if (__ballot(bad)) {
+        scale = 1.0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = zero4<float>();
         const int64_t row = row0 + c < m ? row0 + c : m - 1;
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * RWAVES, KS <= 2 ? 2 : 1) void residual_split_k
             acc[j] = mfma16(W[row * KP + k0 + g],
                             Ht[(col + j < n ? col + j : n - 1) * KP + k0 + g], acc[j]);
       }
-      add_tile<FULL, NORM, float>(av[p], acc, row0 < rend ? m : 0, n, row0, col, lane, sr, sa);
+      add_tile<FULL, NORM, float>(av[p], acc, scale, row0 < rend ? m : 0, n, row0, col, lane, sr, sa);
       load_a(p, row0 + PF * 16);
     };
 #pragma unroll
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64 * RWAVES, 2) void residual_f64_kernel(
           acc[j] = mfma16(w.v[1], h.v[1], acc[j]);
         }
       }
-      add_tile<FULL, NORM, double>(cur, acc, m, n, row0, col, lane, sr, sa);
+      add_tile<FULL, NORM, double>(cur, acc, 1.0, m, n, row0, col, lane, sr, sa);
     }
   };
   if (full) run(std::true_type{});
