@@ -567,7 +567,7 @@ nmf_status product_AF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, con
   if (pb.At) {
     // A H^T = (A^T)^T H^T: the TN kernel streaming A^T row by row.
     nmfk::GemmArgs<T> a{pb.At, m, Ft ? Ft : F, Ft ? n : (int64_t)KP, Pout, KP, m, KP, n,
-                        Ft != nullptr};
+                        Ft != nullptr, nullptr, true};
     HIP_TRY(run_product<T>(nmfk::GemmKind::TN, a, k, part, ctx->stream, nsplit));
     return NMF_OK;
   }
@@ -604,7 +604,7 @@ nmf_status product_AtF(nmf_ctx* ctx, const Prob<T>& pb, int64_t m, int64_t n, co
       return NMF_OK;
     }
   nmfk::GemmArgs<T> a{pb.A, pb.lda, Ft ? Ft : F, Ft ? m : (int64_t)KP, Rout, KP, n, KP, m,
-                      Ft != nullptr};
+                      Ft != nullptr, nullptr, pb.At != nullptr};
   HIP_TRY(run_product<T>(nmfk::GemmKind::TN, a, k, part, ctx->stream, nsplit));
   return NMF_OK;
 }

@@ -152,13 +152,18 @@ __global__ __launch_bounds__(256, WPE) void gemm_nn_kernel(
 // ---------------------------------------------------------------------------
 // Column of X that lane column c feeds into M-tile t. Vector path: tile t
 // takes columns m0 + 16*VEC*(t/VEC) + VEC*c + t%VEC (one 16-byte load per
-// lane covers VEC tiles); scalar path: m0 + 16 t + c, those past the last column
-// on a copy of it.
-template <typename T, bool VX>
+// lane covers VEC tiles); scalar path: m0 + 16 t + c. What would pass the last
+// column is moved back to end there, so that every wave runs the same pipelined
+// loop, and lanes that then share a column compute and store the same value: a
+// run or column of a lane by itself, or (BACK) the whole wave, by its m0. (A
+// guarded loop of one memory latency per four rows for such waves took 85 of
+// the 93 us of a 3000 x 1700 product at k = 40.)
+template <typename T, bool VX, bool BACK>
 __device__ __forceinline__ int64_t tn_col(int64_t m0, int t, int c, int64_t M) {
   constexpr int VEC = Tr<T>::VEC;
   if constexpr (VX) {
-    return m0 + 16 * VEC * (t / VEC) + VEC * c + t % VEC;
+    const int64_t b = m0 + 16 * VEC * (t / VEC) + VEC * c;
+    return (BACK || b < M - VEC ? b : M - VEC) + t % VEC;
   } else {
     const int64_t b = m0 + 16 * t + c;
     return b < M ? b : M - 1;
@@ -191,19 +196,17 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
   const int g = lane >> 4, c = lane & 15;
   int64_t m0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * MW);
   if (m0 >= M) return;
-  // A vector wave with columns past the end is moved back to end at the last
-  // one (M >= 16 MW): it runs the same loop as the others, with loads at
-  // constant distances, and computes and stores some of its neighbour's columns
-  // once more, the same values. (A guarded loop of one memory latency per four
-  // rows took 85 of the 93 us of a 3000 x 1700 product at k = 40; moving back
-  // each lane by itself cost an address per load: 7424 x 3648 at k = 35, 54 ->
-  // 68 us.)
-  if (VX && m0 > M - 16 * MW) m0 = M - 16 * MW;
+  // Whole waves move back (M >= 16 MW) where the loads at constant distances
+  // that this leaves save the registers of an address each: 64 columns at rank
+  // 48, 20000 x 12000 at k = 40 558 -> 428 us. Below, where those fit, each lane by
+  // itself is 2 to 5% faster (11200 x 42752 at k = 24: 656 against 691 us).
+  constexpr bool BACK = VX && NQ > 1 && NT > 2 && !SYM;
+  if (BACK && m0 > M - 16 * MW) m0 = M - 16 * MW;
   const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
   const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
   int64_t xc[NQ];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) xc[q] = tn_col<T, VX>(m0, VX ? q * VEC : q, c, M);
+  for (int q = 0; q < NQ; ++q) xc[q] = tn_col<T, VX, BACK>(m0, VX ? q * VEC : q, c, M);
 
   acc4 acc[MW][NT];
 #pragma unroll
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
     const int64_t kc = okk ? kk : kbeg;
 #pragma unroll
     for (int t = 0; t < MW; ++t) {
-      const T x = X[kc * ldx + tn_col<T, VX>(m0, t, c, M)];
+      const T x = X[kc * ldx + tn_col<T, VX, BACK>(m0, t, c, M)];
       fr[0].x[0][t] = okk ? x : T(0);
     }
 #pragma unroll
@@ -285,10 +288,10 @@ __global__ __launch_bounds__(256, WPE) void gemm_tn_kernel(
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int rho = acc_row<T>(lane, r);
-      const int64_t row = tn_col<T, VX>(m0, t, rho, M);
+      const int64_t row = tn_col<T, VX, BACK>(m0, t, rho, M);
 #pragma unroll
       for (int nt = SYM == 2 ? t : 0; nt < NT; ++nt) {
-        const int64_t col = SYM ? tn_col<T, VX>(0, nt, c, M) : 16 * nt + c;
+        const int64_t col = SYM ? tn_col<T, VX, BACK>(0, nt, c, M) : 16 * nt + c;
         Dp[row * ldd + col] = acc[t][nt][r];
         if (SYM == 2 && nt > t) Dp[col * ldd + row] = acc[t][nt][r];
       }
@@ -402,21 +405,23 @@ static int prod_mw(GemmKind kind, int NT, int64_t M, int64_t K) {
 // at least 128 long (64 in a product under 2^26 multiply-adds, such as a 2000 x
 // 1000 matrix at k = 10, where they cost little), none longer than MAX_SPLIT_LEN
 // while all hold at most 2^28 elements, the one with the fullest rounds of a
-// workgroup per CU after what its slabs cost, 2 N / K of the product's time each:
-// the slab is written by the product and read by the row update, whose few
-// workgroups are slower at it. A second workgroup per CU brings nothing, since
+// workgroup per CU after what its slabs cost, 4 N / K of the product's time each
+// (it is written by the product and read by the row update, whose few workgroups
+// are slower at it; N counts to 48, past which the product is bound by its
+// operations: A^T W of 1000 x 20000 at k = 60 72 us, 92 with one slab). A second workgroup per CU brings nothing, since
 // one already keeps the CU's share of the memory busy. Runs of six HALS
 // iterations with at least 512 workgroups, and now: 7424 x 3648 at k = 24 1010 ->
 // 882 us, 8192 x 4096 at k = 8 1000 -> 924, 9000 x 7000 at k = 40 2198 -> 1982,
 // 16384 x 8192 at k = 60 4.91 -> 4.49 ms, 20000 x 12000 at k = 24 5.67 -> 4.93;
-// half that cost per slab takes 1 to 7% longer on the last.
+// half that cost per slab takes 1 to 7% longer on the last. Over 140 runs and
+// steps of fourteen sizes and five ranks none is more than 3% slower than before.
 constexpr int64_t MAX_SPLIT_LEN = 8192;
 static int64_t auto_splits(int64_t wgs, int64_t M, int64_t N, int64_t K) {
   const int64_t minlen = M * N * K < ((int64_t)1 << 26) ? 64 : 128;
   auto room = [&](int64_t t) { return t * M * N <= ((int64_t)1 << 28); };
   int64_t s = 1;
   while (K > s * MAX_SPLIT_LEN && s < MAX_PRODUCT_SPLITS && room(s + 1)) ++s;
-  return fullest_rounds(wgs, s, 256, 4.0 * (double)N / (double)K, [&](int64_t t) {
+  return fullest_rounds(wgs, s, 256, 4.0 * (double)std::min<int64_t>(N, 48) / (double)K, [&](int64_t t) {
     return t <= MAX_PRODUCT_SPLITS && K / t >= minlen && room(t);
   });
 }
@@ -468,10 +473,10 @@ static void gram_launch(const GemmArgs<T>& a, int64_t splits, int64_t kchunk, T*
         <<<grid, 64, 0, st>>>(a.X, a.ldx, a.Y, a.ldy, D, ldd, dsplit, a.M, a.K, kchunk);
 }
 
-// TN streams A past the caches (non-temporal loads) where A and the transposed
-// copy that the other direction reads are together larger than the 256 MB
-// last-level cache, which would keep them for the next iteration (8192 x 4096 at
-// k = 8, 268 MB each: 3 to 4% of a run). NN's load
+// TN streams A past the caches (non-temporal loads) where A, with its transposed
+// copy if the other direction reads one, is larger than the 256 MB last-level
+// cache, which would keep it for the next product (7424 x 3648 at k = 8, 217 MB
+// each of the two: 4% of a run). NN's load
 // instructions take half a line of a row each, and the other half has to be
 // in the cache when the next asks for it.
 template <typename T, int NT>
@@ -484,7 +489,7 @@ static void prod_dispatch(GemmKind kind, const GemmArgs<T>& a, int64_t splits, i
     if (mw == 2) return nn_launch<T, NT, 2>(a, splits, kchunk, D, ldd, dsplit, st);
     return nn_launch<T, NT, 1>(a, splits, kchunk, D, ldd, dsplit, st);
   }
-  const bool stream = a.M * a.K * (int64_t)sizeof(T) > ((int64_t)1 << 27);
+  const bool stream = a.M * a.K * (int64_t)sizeof(T) > ((int64_t)1 << (a.pair ? 27 : 28));
   if constexpr (NT <= 3) {
     if (mw == 4 && stream)
       return tn_launch<T, NT, 4, true, true>(a, WAVES, splits, kchunk, D, ldd, dsplit, st);

@@ -22,6 +22,7 @@ template <typename T> struct GemmArgs {
   int64_t M, N, K;
   bool yt;
   T* Dt;       // nullable: also receives D transposed (Dt[j * M + i]; Grams only)
+  bool pair = false;   // products: X and its transpose are both kept and take turns
 };
 
 // `part` must hold splits * M * N elements when splits > 1. splits <= 0 picks
