@@ -117,7 +117,8 @@ typedef struct {
                      /* in device memory for the call when it fits (both     */
                      /* large products then stream A row by row); -1 never   */
                      /* does. NMF_F32 products read A itself in both         */
-                     /* directions and take either value.                    */
+                     /* directions, except on some A below 2^22 entries,     */
+                     /* where either value does as it does for NMF_F64.      */
                      /* NMF_BF16 and NMF_FP8_E4M3 take 0 only; their products*/
                      /* read A itself too, except that one of fewer than 4   */
                      /* columns or a row pitch of 2^24 or more is copied     */

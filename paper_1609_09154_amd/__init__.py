@@ -135,7 +135,7 @@ def nmf_dense(A, W, H, algo="hals", iters=10, objective=True, eps_mu=1e-16, max_
               timers=False, check_input=False, transpose_a=True, stop=None, tol=0.0, ctx=None):
     """Algorithm 1 on dense A (m x n); W (m x k) and H (k x n) are updated in
     place. transpose_a=False keeps the library from holding a transposed
-    copy of a float64 A (float32 needs none). A may be bfloat16 or float8_e4m3fn (then W and H are float32,
+    copy of a float64 A (of a float32 A there is one only below 2^22 entries). A may be bfloat16 or float8_e4m3fn (then W and H are float32,
     the products run on the BF16 or FP8 matrix cores). stop = "pgrad" or "relerr" adds the tolerance
     test of nmf_opts (iters is then the cap). Returns (rel_err list or None,
     stats dict); the list ends at the last iteration performed."""

@@ -324,8 +324,8 @@ struct StopInfo {
 // ginv: KP*KP doubles of scratch for ABPP.
 // P: the product, or (MU and HALS) its split slabs, which the update adds in
 // slab order. Gslab and Xt (nullable; MU and HALS at KP <= 64): receive the
-// row blocks' shares of the updated factor's Gram and its transposed copy
-// (KP x rows). Xs (nullable; HALS): scales the incoming rows first (the
+// row blocks' shares of the updated factor's Gram and the copy that the next
+// product reads. Xs (nullable; HALS): scales the incoming rows first (the
 // normalisation's compensation of H).
 template <typename T>
 nmf_status local_update(nmf_ctx* ctx, int algo, T* X, nmfk::Split<T> P, const T* G,
@@ -928,8 +928,8 @@ LpOffsets lp_carve(Carve& cv, const LpPlan& p, int KP) {
   return o;
 }
 
-// Points pb at a reduced-precision A and its scratch; with want_t, also
-// makes the transposed copy that A^T W streams.
+// Points pb at a reduced-precision A and its scratch; with want_t (A that
+// gemm_lp_reads_a does not take), also makes the transposed copy that A^T W reads.
 nmf_status lp_bind(nmf_ctx* ctx, Prob<float>& pb, int lp, const void* Alp, int64_t lda, int64_t m,
                    int64_t n, const LpOffsets& lo, bool want_t) {
   pb.lp = lp;
@@ -1131,7 +1131,7 @@ nmf_status nmf_dense(nmf_ctx* ctx, nmf_dtype dtype, int64_t m, int64_t n, const 
   if (is_lp(dtype)) {
     if ((s = check_lp_a(ctx, dtype, A, lda)) != NMF_OK) return s;
     if (opts->transpose_a != 0)
-      return fail(ctx, NMF_EINVAL, "reduced-precision A needs its transposed copy (transpose_a 0)");
+      return fail(ctx, NMF_EINVAL, "reduced-precision A takes transpose_a 0 only");
   }
   if ((s = bind_device(ctx)) != NMF_OK) return s;
   if (is_lp(dtype))

@@ -31,11 +31,11 @@ template <int KP> struct AdjSplit {
 // Local adjoint of Xn = X * N / (X G + eps) for the rows of one block. The
 // gradient reaching Xn is gXn, plus (PRE) Y + Xn (M + M^T): what the next
 // half-step's product (Y) and Gram (M) pass back to Xn, added here rather
-// than in kernels of their own. Writes gN (and, if gNt is set, its
-// transpose), gD (= dL/dD) and gX; entries k..KP-1 are 0. G, (PRE) M + M^T
+// than in kernels of their own. Writes gN (and, if gNt is set, the
+// copy that the next product reads), gD (= dL/dD) and gX; entries k..KP-1 are 0. G, (PRE) M + M^T
 // (from M and its transpose Mtr), the block's rows of X and (PRE) of Xn live
 // in LDS; the Xn rows' buffer then holds dL/dD and the X rows' buffer gN for
-// the transposed store. With Gslab set, the block also writes its share of
+// that copy. With Gslab set, the block also writes its share of
 // dL/dG = X^T (dL/dD) to slab blockIdx.x (KP x KP) of Gslab, for an ordered
 // sum over the blocks.
 // Both G-products run in the same form: one value of the row broadcast from
@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256) void hals_adjoint_rows_kernel(
     block_gram_partial<T, KP, ROWS, DLD>(XNs, Ds, Tslab + blockIdx.x * slab);
     block_gram_partial<T, KP, ROWS, DLD>(XOs, Ds, Tslab + (gridDim.x + blockIdx.x) * slab);
   }
-  // Delta transposed (Dt[i * rows + r]), the layout the next product reads
+  // Delta in the layout the next product reads
   if (Dt) store_rows_copy<T, KP, ROWS, DLD>(Ds, rb, rows, Dt);
 }
 

@@ -24,8 +24,8 @@ namespace nmfk {
 // rows. G and the block's rows of x are staged in LDS first (so an in-place
 // update, Xn = X, reads nothing a lane has already written) and read with
 // 16-byte loads. Xn receives every entry of the new rows (entries k..KP-1
-// copied from X); Xt (nullable) receives their transpose, Xt[i * rows + r],
-// the layout the next product reads the factor in, and Gslab (nullable) the
+// copied from X); Xt (nullable) receives them in the layout the next product
+// reads the factor in, and Gslab (nullable) the
 // block's share of Xn^T Xn, formed on the matrix cores from the same staged
 // rows. P arrives as the product's slabs, summed here in slab order in double
 // (Pout, nullable, receives the sum), so that a split product needs no pass
