@@ -296,7 +296,7 @@ __global__ void add_kernel(T* __restrict__ Y, const T* __restrict__ X, int64_t n
 // once per 128 rows or columns of D. Column tile j of a wave takes columns
 // 4 c + j (c: lane column), so that a lane holds four neighbours of a row of D
 // and reads and writes them as 16 bytes. 8192 x 4096, ten iterations at k = 64
-// a pass: 765 us on the float instruction, 72% of its peak, before; 643 now, 800
+// a pass: 765 us on the float instruction, 72% of its peak, before; 660 now, 780
 // TFLOP/s of bfloat16 products where a large library product reaches 1126.
 constexpr int RS_T = 128;   // block tile
 __global__ __launch_bounds__(256, 2) void rank_update_split_kernel(

@@ -17,11 +17,12 @@
 //
 // That moves the bound of the large products from the float matrix cores to
 // the read of A: 65536^2 at k = 50 took 3.79 ms a product (113 TFLOP/s, 72% of
-// the float peak) and takes 3.2 (5.3 TB/s; a device copy reaches 4.9), with
-// a quarter of the error (1.1e-6 against 3.6e-6 on the factors after ten
-// HALS iterations). Products whose A stays in the caches are bound by the
+// the float peak) and takes 3.2 to 3.5 ms for A H^T and 2.9 to 3.1 for A^T W (5.9
+// TB/s; a device copy reaches 4.9), by how far the power limit lets the chip
+// clock, with a third of the error (1.3e-6 against 3.6e-6 on the factors after
+// ten HALS iterations). Products whose A stays in the caches are bound by the
 // splits (seven VALU operations an entry) and the latency of a step: 8192 x
-// 4096 at k = 64, 46 us before, 33 now.
+// 4096 at k = 64, 46 us before, 31 now.
 //
 // A is read in its own layout in both directions (a lane's operand is eight
 // values along K of one row or column, and the split packs neighbours along K

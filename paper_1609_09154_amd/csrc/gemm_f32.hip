@@ -19,8 +19,8 @@
 // A wave owns MW 16-row tiles of the streamed side and all rank tiles, so
 // every entry of A is loaded once, by one lane; the rank side is read through
 // the L2. What bounds them is the float instruction: 8192 x 4096 at k = 64
-// takes 46 us a product (93 TFLOP/s of the 157 that it peaks at) where the
-// splits take 33.
+// takes 47 us a product (92 TFLOP/s of the 157 that it peaks at) where the
+// splits take 32.
 //
 // Rank remainder (NR = 1): when k exceeds a multiple of 16 by at most 4
 // (k = 50 = 3 * 16 + 2), the last four columns are computed with the 4x4x1

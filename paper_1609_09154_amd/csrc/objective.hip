@@ -46,8 +46,8 @@ __device__ __forceinline__ double block_sum(double v) {
 // What bounds it is the read of A, at the occupancy that Ht's planes leave:
 // 100003 x 5003 at k = 50 took 1781 us (64 x 256 blocks, element loads after
 // the product, and 55 us more to sum their partials, and 755 for ||A||) and
-// takes 0.56 ms with ||A|| (3.6 TB/s; rows of an odd length are not 16-byte
-// aligned). Of that, loads that no branch surrounds gave 830 -> 633 us, and
+// takes 0.57 ms with ||A|| (3.5 TB/s; rows of an odd length are not 16-byte
+// aligned) and 0.48 without. Of that, loads that no branch surrounds gave 830 -> 633 us, and
 // the waves side by side 633 -> 561 (4096 x 2048 at k = 32: 14.8 -> 13.8 ->
 // 11.5; 30000^2 at k = 64: 1304 -> 985 -> 1009).
 // Four entries of a row of A, widened to what the difference is taken in.
